@@ -1581,6 +1581,371 @@ __global__ void __launch_bounds__(CTB) __attribute__((amdgpu_waves_per_eu(5, 8))
   }
 }
 
+// One DPP move within each row of 16 lanes (every lane of the group active).
+template <int CTRL>
+__device__ __forceinline__ int dpp(int v) {
+  return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false);
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E;             // quad_perm [1,0,3,2], [2,3,0,1]
+constexpr int DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;  // lanes 0..7 / 0..15 of a row reversed
+
+// Minimum and maximum over the aligned group of G lanes a lane belongs to.
+template <int G>
+__device__ __forceinline__ int group_min(int v) {
+  if (G >= 2) v = min(v, dpp<DPP_XOR1>(v));
+  if (G >= 4) v = min(v, dpp<DPP_XOR2>(v));
+  if (G >= 8) v = min(v, dpp<DPP_HALF_MIRROR>(v));
+  if (G >= 16) v = min(v, dpp<DPP_MIRROR>(v));
+  return v;
+}
+template <int G>
+__device__ __forceinline__ int group_max(int v) {
+  if (G >= 2) v = max(v, dpp<DPP_XOR1>(v));
+  if (G >= 4) v = max(v, dpp<DPP_XOR2>(v));
+  if (G >= 8) v = max(v, dpp<DPP_HALF_MIRROR>(v));
+  if (G >= 16) v = max(v, dpp<DPP_MIRROR>(v));
+  return v;
+}
+
+// The pickup of pick() by a group of G lanes that hold the same state, in two
+// parts, so that the caller's arithmetic runs while the first loads are on
+// their way.  Part one: the window of the prediction and the bounds of its
+// first ZB z bins' cells, each lane of a quad (a pair, with G = 2) reading
+// its own.  Part two: each lane takes every G-th hit of the cells, with its
+// id loaded beside it, and the group keeps the least (score, id).
+constexpr int ZB = 4;
+template <int G>
+struct GroupPick {
+  static constexpr int NB = G >= ZB ? 1 : ZB / G;  // cell bounds a lane reads
+  static constexpr int HB = G >= 4 ? 1 : 4 / G;    // hits a lane reads in one round
+  Win c;
+  int Yp, Zp, izb;
+  int qa[NB], qb[NB];
+  bool stop, none;
+
+  __device__ __forceinline__ void bounds(const Workspace &w, int sub) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int k = (sub & (G - 1) & 3) + j * G;
+      const bool v = izb + k <= c.iz1;
+      const int cb = c.cbase + (izb + (v ? k : 0)) * c.ny;
+      qa[j] = w.cell[cb + c.iy0];
+      const int e = w.cell[cb + c.iy1 + 1];
+      qb[j] = v ? e : qa[j];
+    }
+  }
+
+  __device__ __forceinline__ void begin(const Args &A, const Rec &rf, float2 inv, float yp, float zp, int Yr, int Zr,
+                                        int sub) {
+    const float vy = yp * 256.f, vz = zp * 256.f;
+    const bool wild = !(fabsf(vy) < 1.0e9f) || !(fabsf(vz) < 4.0e15f), far = !(fabsf(vz) < 1.0e9f);
+    Yp = wild ? 0 : round_offset(vy, Yr);
+    Zp = wild || far ? 0 : round_offset(vz, Zr);
+    stop = wild || abs(Yp) > rf.H + A.p.ext_edge_q;
+    const int WY = A.p.ext_win_y_q, WZ = A.p.ext_win_z_q;
+    c = window_cells(rf, inv, Yp - WY, Yp + WY, Zp - WZ, Zp + WZ);
+    none = stop || far || c.empty;
+    if (none) return;
+    izb = c.iz0;
+    bounds(A.w, sub);
+  }
+
+  // the picked hit (-1 none) and its position
+  __device__ __forceinline__ int finish(const Args &A, int sub, int2 &best_yz) {
+    if (none) return -1;
+    const Workspace &w = A.w;
+    const int WY = A.p.ext_win_y_q, WZ = A.p.ext_win_z_q;
+    int best_s = INT32_MAX, best_id = INT32_MAX, best = -1;
+    int2 yz = make_int2(0, 0);
+    for (;;) {
+      int n[ZB], a[ZB];
+      if (G >= ZB) {
+        const int cnt = qb[0] - qa[0];
+        n[0] = dpp<0x00>(cnt), n[1] = dpp<0x55>(cnt), n[2] = dpp<0xAA>(cnt), n[3] = dpp<0xFF>(cnt);
+        a[0] = dpp<0x00>(qa[0]), a[1] = dpp<0x55>(qa[0]), a[2] = dpp<0xAA>(qa[0]), a[3] = dpp<0xFF>(qa[0]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < ZB / 2; ++j) {
+          const int cnt = qb[j] - qa[j];
+          n[j * 2] = dpp<0xA0>(cnt), n[j * 2 + 1] = dpp<0xF5>(cnt);
+          a[j * 2] = dpp<0xA0>(qa[j]), a[j * 2 + 1] = dpp<0xF5>(qa[j]);
+        }
+      }
+      const int e0 = n[0], e1 = e0 + n[1], e2 = e1 + n[2], tot = e2 + n[3];
+      const int a1 = a[1] - e0, a2 = a[2] - e1, a3 = a[3] - e2;
+      for (int t0 = sub; t0 - sub < tot; t0 += G * HB) {
+        int q[HB], id[HB];
+        int2 h[HB];
+#pragma unroll
+        for (int j = 0; j < HB; ++j) {
+          const int t = t0 + j * G;
+          q[j] = t < tot ? t + (t < e0 ? a[0] : t < e1 ? a1 : t < e2 ? a2 : a3) : a[0];
+          h[j] = w.syz[q[j]];
+          id[j] = w.perm[q[j]];
+        }
+#pragma unroll
+        for (int j = 0; j < HB; ++j) {
+          const int dY = h[j].x - Yp, dZ = h[j].y - Zp;
+          if (t0 + j * G < tot && abs(dY) <= WY && abs(dZ) <= WZ) {
+            const int sc = A.p.w_y * dY * dY + A.p.w_z * dZ * dZ;
+            if (sc < best_s || (sc == best_s && id[j] < best_id)) {
+              best_s = sc;
+              best_id = id[j];
+              best = q[j];
+              yz = h[j];
+            }
+          }
+        }
+      }
+      izb += ZB;
+      if (izb > c.iz1) break;
+      bounds(w, sub);
+    }
+    const int s = group_min<G>(best_s);
+    if (s == INT32_MAX) return -1;
+    const int id = group_min<G>(best_s == s ? best_id : INT32_MAX);
+    const bool mine = best_s == s && best_id == id;
+    best_yz = make_int2(group_max<G>(mine ? yz.x : INT32_MIN), group_max<G>(mine ? yz.y : INT32_MIN));
+    return group_max<G>(mine ? best : -1);
+  }
+};
+
+// The fit with G lanes per seed and PER seeds per wave (the lanes past
+// PER * G repeat the first ones), for batches whose seeds do not fill the GPU
+// one per lane: the walk of k_fit, the same operations on the same values.
+// Every lane of a group carries the whole filter; the group shares a pickup's
+// hits.  The waves are few, and a row's time is the latency of its dependent
+// loads and arithmetic.  So whatever does not depend on the state is loaded
+// one or two rows ahead (records, planes, chain and pass-1 hits), a pickup's
+// hits come in one round instead of several, the covariance (in registers)
+// is carried to the row while the pickup's loads are on their way, and with
+// one seed per wave a row with a known hit does not wait for another seed's
+// pickup.
+template <int G, int PER>
+__global__ void __launch_bounds__(64) k_fit_group(Args A) {
+  const Workspace &w = A.w;
+  if (*A.out.status != TPC_OK) return;
+  const int64_t n_seeds = w.ctr[C_SEEDS];
+  const int64_t b = xcd_chunk(blockIdx.x, (n_seeds + PER - 1) / PER);
+  if (b * PER >= n_seeds) return;
+  const int slot = (threadIdx.x / G) % PER;
+  const int64_t i = b * PER + slot;
+  const int sub = threadIdx.x % G;
+  const bool valid = i < n_seeds;
+  const int64_t t = valid ? w.seed_list[i] : 0;
+  const tpc_params_t &P = A.p;
+  const int nr = A.n_rows;
+  int32_t *col = seed_column(w, i, nr);
+  const float sy2 = P.sigma_y * P.sigma_y, sz2 = P.sigma_z * P.sigma_z;
+  const float k = A.kcurv, smx = P.sinphi_max;
+  int nfit = 0, rlo = -1, rhi = -1;
+  int h0 = 0, u = 0, L = 0, r1 = 0, Yr = 0, Zr = 0;
+  const int32_t *segu = w.seg;
+  const float2 *invs = w.seg_inv;
+  KStateR s;
+  bool ok = false;
+  int2 yz0 = make_int2(0, 0);
+  if (valid) {
+    h0 = w.trk_start[t];
+    u = w.trk_unit[t];
+    L = w.trk_len[t];
+    r1 = w.sd_r1[i];
+    segu = w.seg + int64_t(u) * nr * SEGW;
+    invs = w.seg_inv + int64_t(u) * nr;
+    const int2 ya = w.syz[h0], ym = w.syz[w.sd_hm[i]], yb = w.syz[w.sd_hb[i]];
+    yz0 = ya;
+    Yr = ya.x;
+    Zr = ya.y;
+    const float y1 = float(ym.x - Yr) * (1.f / 256.f), y2 = float(yb.x - Yr) * (1.f / 256.f);
+    const float z2 = float(yb.y - Zr) * (1.f / 256.f);
+    ok = seed3(s, A.row_x[r1], A.row_x[r1 + L / 2], A.row_x[r1 + L - 1], y1, y2, z2, k, smx, P.cov0);
+  }
+  // pass 1
+  int r_out = r1, misses = 0, p1n = ok ? 1 : 0;
+  bool act = ok;
+  int hn = -1, hnn = -1;  // chain hits of the next row and the one after it
+  int2 yzn = make_int2(0, 0), yz_out = yz0;
+  if (ok) {
+    col[r1 * 64] = h0;
+    upd_hit(s, yz0, Yr, Zr, sy2, sz2);
+    hn = w.upc[h0];
+    if (hn >= 0) {
+      yzn = w.syz[hn];
+      hnn = w.upc[hn];
+    }
+  }
+  const int ra = wave_min(ok ? r1 : nr) + 1;
+  Rec rf{};
+  float2 inv = make_float2(0.f, 0.f);
+  float xn = 0.f;
+  if (ra < nr) {
+    rf = rec_fields_v(segu + ra * SEGW);
+    inv = invs[ra];
+    xn = A.row_x[ra];
+  }
+  for (int r = ra; r < nr; ++r) {
+    if (!__any(act)) break;
+    const Rec rc = rf;
+    const float2 ic = inv;
+    const float xr = xn;
+    const int rn = min(r + 1, nr - 1);
+    xn = A.row_x[rn];
+    const bool on = act && r > r1, chain = r < r1 + L;
+    KStateR s2 = s;
+    GroupPick<G> pk;
+    Step st;
+    bool stop = false;
+    if (on) {
+      if (step_prepare(s, xr, k, smx, st)) {
+        if (!chain) {
+          pk.begin(A, rc, ic, s.p[0] + st.dy, s.p[1] + s.p[3] * st.sT, Yr, Zr, sub);
+          stop = pk.stop;
+        }
+        step_apply(s2, st, xr, k);
+      } else {
+        stop = true;
+      }
+    }
+    rf = rec_fields_v(segu + rn * SEGW);
+    inv = invs[rn];
+    if (on && stop) act = false;
+    if (on && !stop) {
+      int h;
+      int2 yz = yzn;
+      if (chain) {
+        h = hn;
+        hn = hnn;
+        if (hn >= 0) {
+          yzn = w.syz[hn];
+          hnn = w.upc[hn];
+        }
+      } else {
+        h = pk.finish(A, sub, yz);
+      }
+      col[r * 64] = h;  // every lane of the group writes it, and reads its own write in pass 2
+      if (h >= 0) {
+        upd_hit(s2, yz, Yr, Zr, sy2, sz2);
+        s = s2;
+        r_out = r;
+        yz_out = yz;
+        ++p1n;
+        misses = 0;
+      } else if (++misses > P.max_miss) {
+        act = false;
+      }
+    }
+  }
+  // pass 2
+  act = ok;
+  if (ok) {
+    cov_reset(s, P.cov0);
+    s.chi2 = 0.f;
+    upd_hit(s, yz_out, Yr, Zr, sy2, sz2);
+    nfit = 1;
+    rhi = r_out;
+    rlo = r_out;
+    misses = 0;
+  }
+  const int rb = wave_max(ok ? r_out - 1 : -1);
+  // pass-1 hit of row r, if any: written for every row from r1 to r_out
+  auto before = [&](int r) { return ok && r >= r1 && r < r_out ? col[r * 64] : -1; };
+  hn = before(rb);
+  hnn = before(rb - 1);
+  yzn = make_int2(0, 0);
+  if (hn >= 0) yzn = w.syz[hn];
+  if (rb >= 0) {
+    rf = rec_fields_v(segu + rb * SEGW);
+    inv = invs[rb];
+    xn = A.row_x[rb];
+  }
+  for (int r = rb; r >= 0; --r) {
+    if (!__any(act)) break;
+    const Rec rc = rf;
+    const float2 ic = inv;
+    const float xr = xn;
+    const int rn = max(r - 1, 0);
+    xn = A.row_x[rn];
+    int h = hn;
+    int2 yz = yzn;
+    const bool on = act && r < r_out, known = h >= 0;
+    KStateR s2 = s;
+    GroupPick<G> pk;
+    Step st;
+    bool stop = false;
+    if (on) {
+      if (step_prepare(s, xr, k, smx, st)) {
+        if (!known) {
+          pk.begin(A, rc, ic, s.p[0] + st.dy, s.p[1] + s.p[3] * st.sT, Yr, Zr, sub);
+          stop = pk.stop;
+        }
+        step_apply(s2, st, xr, k);
+      } else {
+        stop = true;
+      }
+    }
+    rf = rec_fields_v(segu + rn * SEGW);
+    inv = invs[rn];
+    hn = hnn;
+    if (hn >= 0) yzn = w.syz[hn];
+    hnn = before(r - 2);
+    if (on && stop) act = false;
+    if (on && !stop) {
+      if (!known) {
+        h = pk.finish(A, sub, yz);
+        col[r * 64] = h;
+        if (h < 0) {
+          rlo = r;
+          if (r < r1 && ++misses > P.max_miss) act = false;
+        } else {
+          misses = 0;
+        }
+      }
+      if (h >= 0) {
+        upd_hit(s2, yz, Yr, Zr, sy2, sz2);
+        s = s2;
+        ++nfit;
+        rlo = r;
+      }
+    }
+  }
+  uint32_t key = 0;
+  if (nfit > 0) {
+    const uint32_t local = uint32_t(w.perm[h0] - A.off[u]);
+    key = (uint32_t(nfit) << 24) | (0xFFFFFFu - local);
+    s.p[0] += float(Yr) * (1.f / 256.f);
+    s.p[1] += float(Zr) * (1.f / 256.f);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 5; ++j) s.p[j] = 0.f;
+#pragma unroll
+    for (int j = 0; j < 15; ++j) s.c[j] = 0.f;
+    s.x = 0.f;
+    s.chi2 = 0.f;
+  }
+  if (valid && threadIdx.x == slot * G) {
+    w.sd_nfit[i] = nfit;
+    w.sd_p1n[i] = p1n;
+    w.sd_rlo[i] = rlo;
+    w.sd_rhi[i] = rhi;
+    w.sd_key[i] = key;
+#pragma unroll
+    for (int j = 0; j < 5; ++j) w.sd_par[i * 5 + j] = s.p[j];
+#pragma unroll
+    for (int j = 0; j < 15; ++j) w.sd_cov[i * 15 + j] = s.c[j];
+    w.sd_x[i] = s.x;
+    w.sd_chi2[i] = s.chi2;
+  }
+  if (nfit > 0) {  // ownership, the rows dealt over all lanes that hold the seed
+    constexpr int LANES = 64 / PER;
+    const int me = sub + int(threadIdx.x) / (G * PER) * G;
+#pragma unroll 4
+    for (int r = rlo + me; r <= rhi; r += LANES) {
+      const int h = col[r * 64];
+      if (h >= 0) atomicMax(&w.owner[h], key);
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // step 6: selector and output.  Keep a tracklet that owns >= n_min of its
 // hits and at least f_min of them; tracks keep the tracklet order; no refit.
@@ -1794,6 +2159,34 @@ const char *const kKernelNames[] = {
     "k_fit",         "k_select_emit"};
 constexpr int kNumKernels = int(sizeof(kKernelNames) / sizeof(kKernelNames[0]));
 
+template <int G, int PER>
+void launch_fit_group(const Args &A, hipStream_t st) {
+  hipLaunchKernelGGL((k_fit_group<G, PER>), dim3(round8(blocks_for(A.w.S_cap, PER))), dim3(64), 0, st, A);
+}
+
+// Lanes per seed by the batch's size.  Seeds (known on the device only) are
+// about one per 50 to 75 clusters; one lane each, they leave SIMDs empty up
+// to a few million clusters, and the fit then lasts as long as one wave's
+// walk.  More lanes per seed shorten the walk and add waves until the waves
+// queue.  Whole calls in us, on frames of n clusters (k_fit / <16,1> /
+// <16,4> / <8,8> / <4,16> / <2,32>):
+//   18 k  1160 /  623 /  668 /  680 /  745 /  867    (one sector)
+//   42 k  1086 /  676 /  680 /  714 /  798 /  954
+//  164 k  1196 /  778 /  734 /  750 /  841 / 1024
+//  410 k  1270 / 1110 /  869 /  934 /  983 / 1110
+//  820 k  1340 / 1797 / 1277 /  953 / 1056 / 1160
+//  1.6 M  1453 / 3302 / 2117 / 1547 / 1276 / 1368
+//  2.5 M  1814 /    - /    - / 2681 / 2109 / 1694
+//  4.1 M  2237 /    - /    - / 4355 / 3275 / 2732
+void launch_fit(const Args &A, hipStream_t st) {
+  if (A.n <= 32 * 1024) launch_fit_group<16, 1>(A, st);
+  else if (A.n <= 450 * 1024) launch_fit_group<16, 4>(A, st);
+  else if (A.n <= 1200 * 1024) launch_fit_group<8, 8>(A, st);
+  else if (A.n <= 1800 * 1024) launch_fit_group<4, 16>(A, st);
+  else if (A.n <= 3000 * 1024) launch_fit_group<2, 32>(A, st);
+  else hipLaunchKernelGGL(k_fit, dim3(round8(blocks_for(A.w.S_cap, CTB))), dim3(CTB), 0, st, A);
+}
+
 int track_impl(const tpc_clusters_t *c, const tpc_geometry_t *g, const tpc_field_t *f,
                const tpc_params_t *p, tpc_tracks_t *out, void *workspace, size_t ws_bytes,
                void *stream, void *const *events, int n_events) {
@@ -1876,7 +2269,7 @@ int track_impl(const tpc_clusters_t *c, const tpc_geometry_t *g, const tpc_field
     hipLaunchKernelGGL(k_compact_seeds, dim3(unsigned(w.KB < CHAIN_BLOCKS ? w.KB : CHAIN_BLOCKS)), dim3(TPB), 0,
                        st, A);
     mark();
-    hipLaunchKernelGGL(k_fit, dim3(round8(blocks_for(w.S_cap, CTB))), dim3(CTB), 0, st, A);
+    launch_fit(A, st);
     mark();
     hipLaunchKernelGGL(k_select_emit, dim3(unsigned(w.SB < SELECT_BLOCKS ? w.SB : SELECT_BLOCKS)), dim3(TPB), 0,
                        st, A);
