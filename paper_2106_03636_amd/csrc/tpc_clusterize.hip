@@ -3,22 +3,31 @@
 // ADC values into hits; §3.2: it runs much faster on GPUs than on CPUs).
 // The operation is stated with tpc_clusterize in include/tpc_track.h.
 //
-// Four launches on the caller's stream:
-//   k_clu_init   status and count;
-//   k_clu_count  one wave per pad: the peaks among the pad's digits (their
-//                neighbours in the pads either side found by binary search
-//                over those pads' time-ordered digits, staged in LDS with
-//                the block's own pads), counted per pad and per block of
-//                four pads; input checks;
-//   k_clu_scan   one block: exclusive scan of the per-block counts, total,
-//                capacity check;
-//   k_clu_emit   one wave per pad again: each peak recomputed and written at
-//                its block's base plus the counts of the pads and lanes
-//                before it, so clusters come in (unit, row, pad, time) order.
-// The digits are read twice (2 x 4 bytes each, once per pass into LDS, with
-// the pads either side of a block's four pads); everything else is small.
+// Two launches on the caller's stream:
+//   k_clu_init   status, count, the rows' first pads, the look-back words;
+//   k_clu_find   a block per part of a row (taken by ticket): the digits of its
+//                pads and of the pads either side go to LDS once; each wave
+//                filters a contiguous share of them (only a digit of q_min or
+//                more that its neighbours in time do not beat can be a peak:
+//                about 3 in 10), tests the survivors against the pads either
+//                side (a binary search over their time-ordered digits) and
+//                keeps the peaks' places in order; the blocks' counts are
+//                added up by a decoupled look-back, and the peaks are written
+//                at their places, so clusters come in (unit, row, pad, time)
+//                order.  Digits are read once (those of edge pads twice).
+// A look-back waits for the slowest block before it, so the blocks have to
+// cost alike: the inner rows have a third of the outer rows' pads and nearly
+// as many clusters, and every row is cut into the same number of parts (runs
+// of a fixed number of pads: 912 us where equal parts take 651).
 // Peaks and charge sums are integer; the centre and position are FP64
 // expressions rounded once to FP32, so the result is exact.
+//
+// What bounds it: instruction issue (about 190 vector instructions per 64
+// digits, half of them the searches'), then the look-back (140 us of the 605)
+// and the tickets (45 us).  60 M digits of 540 k pads: 605 us, 0.7 TB/s of the
+// bytes it cannot do without; 0.49 M digits of 15 k pads: 25 us.  Before, two
+// passes (count, emit) searched for every digit, a wave per pad: 2.39 ms and
+// 57 us.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -28,8 +37,13 @@
 namespace {
 
 constexpr int TPB = 256;
-constexpr int PADS_PER_BLOCK = TPB / 64;
+constexpr int WAVES = TPB / 64;
 constexpr int MAX_ROWS = 255;
+constexpr int MAX_PADS = 60;         // pads of a block (with one either side and an end: a wave's lanes)
+// digits a block holds in LDS, with the pads either side (60 M digits: 817, 651 and 605 us with 3072, 4096 and 6144, 682
+// with 8192 and 512 threads; fewer blocks take fewer tickets, which one counter serves, but leave fewer waves)
+constexpr int STAGE_DIGITS = 6144;
+constexpr int SPIN_MAX = 1 << 26;
 
 struct CluArgs {
   const int64_t *off;  // [n_units * pads_total + 1]
@@ -46,36 +60,55 @@ struct CluArgs {
   int32_t *qtot;
   int64_t *unit_offsets, *count;
   int32_t *status;
+  int32_t parts;       // parts of a row, a block each
+  int64_t n_blocks;
+  bool wide;  // time and q allow loads of four digits (8-byte aligned)
   // workspace
-  int32_t *pad_cnt;  // [n_pads]
-  int32_t *blk;      // [n_pads / 4 + 1]
+  unsigned long long *ticket;
+  uint64_t *lookback;  // [n_blocks] flag (bits 62-63: 1 count, 2 inclusive sum), clusters
+  int32_t *rbase;      // [n_rows] first pad of each row
 };
 
 __device__ __forceinline__ void fail(int32_t *status, int32_t code) { atomicCAS(status, TPC_OK, code); }
 
-// first digit in [lo, hi) with time >= t (times increasing)
-__device__ __forceinline__ int64_t lower_time(const uint16_t *time, int64_t lo, int64_t hi, int32_t t) {
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (int32_t(time[mid]) < t) lo = mid + 1; else hi = mid;
-  }
-  return lo;
-}
+// A digit as the searches hold it: its time above its charge, so that digits of
+// a pad compare like their times.
+__device__ __forceinline__ uint32_t pack(uint16_t t, uint16_t q) { return (uint32_t(t) << 16) | q; }
 
-// Row of pad index jr (0 <= jr < pads_total) from the rows' first pads.
-__device__ __forceinline__ int row_of(const int32_t *rbase, int n_rows, int32_t jr) {
-  int lo = 0, hi = n_rows - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (rbase[mid] <= jr) lo = mid; else hi = mid - 1;
+// A pad's time-ordered digits, n of them: packed in LDS, or in the arrays.
+// lower(key): the first digit not below key.  In LDS all lanes take the same
+// steps (top: the largest power of two up to the longest list of the block).
+struct Packed {
+  const uint32_t *d;
+  int32_t n, top;
+  __device__ __forceinline__ uint32_t at(int32_t i) const { return d[i]; }
+  static __device__ __forceinline__ void lower2(const Packed &x, const Packed &y, uint32_t key, int32_t &a, int32_t &b) {
+    a = b = 0;
+    const int32_t lx = max(x.n, 1), ly = max(y.n, 1);
+    for (int32_t st = x.top; st > 0; st >>= 1) {  // both searches step together
+      const int32_t i = a + st, j = b + st;
+      const uint32_t u = x.d[min(i, lx) - 1], v = y.d[min(j, ly) - 1];
+      if (i <= x.n && u < key) a = i;
+      if (j <= y.n && v < key) b = j;
+    }
   }
-  return lo;
-}
-
-// A pad's time-ordered digits: times and charges, n of them (LDS or global).
-struct List {
+};
+struct Arrays {
   const uint16_t *t, *q;
   int32_t n;
+  __device__ __forceinline__ uint32_t at(int32_t i) const { return pack(t[i], q[i]); }
+  __device__ __forceinline__ int32_t lower(uint32_t key) const {
+    int32_t a = 0, b = n;
+    while (a < b) {
+      const int32_t m = (a + b) >> 1;
+      if (at(m) < key) a = m + 1; else b = m;
+    }
+    return a;
+  }
+  static __device__ __forceinline__ void lower2(const Arrays &x, const Arrays &y, uint32_t key, int32_t &a, int32_t &b) {
+    a = x.lower(key);
+    b = y.lower(key);
+  }
 };
 
 struct Peak {
@@ -83,281 +116,396 @@ struct Peak {
   int32_t t, v, Q, Sp, St;
 };
 
-// The peak test and 3x3 sums of digit i of `own`: neighbours in the same pad
-// are the adjacent digits (times increase inside a pad); in the pads below
-// and above (`lo`, `hi`: empty at a row's edge), the digits with time
-// t-1..t+1, found by binary search.  A neighbour earlier in (pad, time) order
-// must be smaller, a later one at most equal.
-__device__ __forceinline__ Peak peak_at(int32_t q_min, const List &own, const List &lo, const List &hi, int32_t i) {
+// One neighbour w of a peak candidate at (dp, dt): earlier in (pad, time) order
+// it must be smaller, later at most equal.
+__device__ __forceinline__ void neighbour(Peak &k, int32_t w, int dp, int32_t dt) {
+  if (dp < 0 || (dp == 0 && dt < 0) ? !(w < k.v) : !(w <= k.v)) k.is = false;
+  k.Q += w;
+  k.Sp += dp * w;
+  k.St += dt * w;
+}
+
+// The test against the digits of the same pad: the adjacent ones (times
+// increase inside a pad), `before` and `after` where the pad has them.
+__device__ __forceinline__ Peak own_pad(int32_t q_min, uint32_t d, bool has_before, uint32_t before, bool has_after,
+                                        uint32_t after) {
   Peak k;
-  k.t = own.t[i];
-  k.v = own.q[i];
+  k.t = int32_t(d >> 16);
+  k.v = int32_t(d & 0xFFFFu);
   k.Q = k.v;
   k.Sp = 0;
   k.St = 0;
   k.is = k.v >= q_min;
-  if (!k.is) return k;
-  if (i > 0 && int32_t(own.t[i - 1]) == k.t - 1) {  // earlier in the same pad
-    const int32_t w = own.q[i - 1];
-    if (!(w < k.v)) k.is = false;
-    k.Q += w;
-    k.St -= w;
-  }
-  if (i + 1 < own.n && int32_t(own.t[i + 1]) == k.t + 1) {  // later in the same pad
-    const int32_t w = own.q[i + 1];
-    if (!(w <= k.v)) k.is = false;
-    k.Q += w;
-    k.St += w;
-  }
-#pragma unroll
-  for (int side = 0; side < 2; ++side) {
-    const List &L = side ? hi : lo;
-    const int dp = side ? 1 : -1;
-    int32_t a = 0, b = L.n;  // first digit with time >= t - 1
-    while (a < b) {
-      const int32_t mid = (a + b) >> 1;
-      if (int32_t(L.t[mid]) < k.t - 1) a = mid + 1; else b = mid;
-    }
-    for (int m = 0; m < 3 && a < L.n; ++m, ++a) {
-      const int32_t te = L.t[a];
-      if (te > k.t + 1) break;
-      const int32_t w = L.q[a];
-      // the pad above is later in (pad, time) order, the pad below earlier
-      if (side ? !(w <= k.v) : !(w < k.v)) k.is = false;
-      k.Q += w;
-      k.Sp += dp * w;
-      k.St += (te - k.t) * w;
-    }
-  }
+  if (has_before && int32_t(before >> 16) == k.t - 1) neighbour(k, int32_t(before & 0xFFFFu), 0, -1);
+  if (has_after && int32_t(after >> 16) == k.t + 1) neighbour(k, int32_t(after & 0xFFFFu), 0, 1);
   return k;
 }
 
-__device__ __forceinline__ void load_rbase(const CluArgs &A, int32_t *rbase) {
-  if (threadIdx.x == 0) {
-    int32_t s = 0;
-    for (int r = 0; r < A.n_rows; ++r) {
-      rbase[r] = s;
-      s += 2 * A.half[r];
+// The test against the pads below and above (empty at a row's edge): their
+// digits of time t-1 .. t+1, from a binary search in each.
+template <class L>
+__device__ __forceinline__ void other_pads(Peak &k, const L &lo, const L &hi) {
+  const uint32_t key = uint32_t(max(k.t - 1, 0)) << 16;  // the first digit of time >= t - 1
+  int32_t a, c;
+  L::lower2(lo, hi, key, a, c);
+#pragma unroll
+  for (int m = 0; m < 3; ++m) {
+    if (a + m < lo.n) {
+      const uint32_t w = lo.at(a + m);
+      const int32_t dt = int32_t(w >> 16) - k.t;
+      if (dt <= 1) neighbour(k, int32_t(w & 0xFFFFu), -1, dt);
+    }
+    if (c + m < hi.n) {
+      const uint32_t w = hi.at(c + m);
+      const int32_t dt = int32_t(w >> 16) - k.t;
+      if (dt <= 1) neighbour(k, int32_t(w & 0xFFFFu), 1, dt);
     }
   }
 }
 
-__global__ void k_clu_init(CluArgs A) {
-  *A.status = TPC_OK;
-  *A.count = 0;
+__global__ void __launch_bounds__(TPB) k_clu_init(CluArgs A) {
+  const int64_t i0 = int64_t(blockIdx.x) * TPB + threadIdx.x;
+  if (blockIdx.x == 0) {  // exclusive sum of the rows' pads
+    __shared__ int32_t wsum[WAVES];
+    const int lane = __lane_id(), wave = threadIdx.x >> 6;
+    const int32_t v = int32_t(threadIdx.x) < A.n_rows ? 2 * A.half[threadIdx.x] : 0;
+    int32_t x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int32_t y = __shfl_up(x, o);
+      if (lane >= o) x += y;
+    }
+    if (lane == 63) wsum[wave] = x;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) x += wsum[w];
+    if (int32_t(threadIdx.x) < A.n_rows) A.rbase[threadIdx.x] = x - v;
+    if (threadIdx.x == 0) {
+      *A.status = TPC_OK;
+      *A.count = 0;
+      *A.ticket = 0ull;
+    }
+  }
+  for (int64_t i = i0; i < A.n_blocks; i += int64_t(gridDim.x) * TPB) A.lookback[i] = 0;
 }
 
-// A block takes PADS_PER_BLOCK consecutive pads, one per wave.  The digits
-// of those pads and of the pads just before and after (a contiguous range of
-// the digit arrays) are staged in LDS when they fit, so every neighbour
-// search runs in LDS; a block whose range does not fit reads the digit
-// arrays directly.  Slot s holds pad j0 - 1 + s.
-constexpr int SLOTS = PADS_PER_BLOCK + 2;
-constexpr int STAGE_DIGITS = 6144;  // 24 KB of (time, charge)
-
-struct Stage {
-  int64_t a[SLOTS + 1];  // slot s: digits [a[s], a[s+1]) of the arrays
-  int32_t rbase[MAX_ROWS];
-  uint16_t t[STAGE_DIGITS], q[STAGE_DIGITS];
-  int32_t cnt[PADS_PER_BLOCK];
-  int ok, fits;
+// A block's run of pads: slot s holds pad first - 1 + s of the row, slots
+// 1 .. np the block's own.
+struct Run {
+  int32_t a[MAX_PADS + 3];  // slot s: digits [a[s], a[s+1]), counted from digit g0 of the arrays
+  int64_t g0;
+  int32_t first, np;        // own pads of the row
+  int32_t row, half;
+  int32_t top;              // largest power of two up to the longest slot
+  bool ok, fits;
 };
 
-// Offsets of the staged pads, checked; the digits staged if they fit.
-__device__ __forceinline__ void stage_block(const CluArgs &A, Stage &S, int64_t j0) {
-  load_rbase(A, S.rbase);
-  if (threadIdx.x <= SLOTS) {
-    const int64_t j = j0 - 1 + threadIdx.x;  // the offset at the start of pad j
-    S.a[threadIdx.x] = j < 0 ? -1 : (j > A.n_pads ? -2 : A.off[j]);
+// First slot whose end lies past digit e (own digits only).
+__device__ __forceinline__ int slot_of(const Run &R, int32_t e) {
+  int lo = 1, hi = R.np;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (R.a[mid + 1] <= e) lo = mid + 1; else hi = mid;
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    // pads before the first and after the last are empty
-    if (S.a[0] == -1) S.a[0] = S.a[1];
-    for (int s = 1; s <= SLOTS; ++s)
-      if (S.a[s] == -2) S.a[s] = S.a[s - 1];
-    bool ok = true;
-    for (int s = 0; s <= SLOTS; ++s) ok = ok && S.a[s] >= 0 && S.a[s] <= A.n && (s == 0 || S.a[s - 1] <= S.a[s]);
-    if (j0 == 0) ok = ok && S.a[1] == 0;
-    if (j0 + PADS_PER_BLOCK >= A.n_pads) ok = ok && A.off[A.n_pads] == A.n;
+  return lo;
+}
+
+// np pads of row r of unit u from pad `first` on: their offsets, checked.  Run
+// by one wave.
+__device__ __forceinline__ void load_run(const CluArgs &A, Run &R, int u, int r, int32_t first, int32_t np) {
+  const int t = __lane_id();
+  const int64_t j0 = int64_t(u) * A.pads_total + A.rbase[r] + first;
+  // the offset at the start of pad j0 - 1 + t (pads outside the arrays are empty)
+  const int64_t j = min(max(j0 - 1 + t, int64_t(0)), A.n_pads);
+  const int64_t v = t < np + 3 ? A.off[j] : 0;
+  const int64_t next = __shfl_down(v, 1);
+  bool good = t >= np + 3 || (v >= 0 && v <= A.n && (t == np + 2 || v <= next));
+  if (t == 0 && j0 == 0) good = good && A.off[0] == 0;
+  if (t == 0 && j0 + np >= A.n_pads) good = good && A.off[A.n_pads] == A.n;
+  const bool ok = __ballot(good) == ~uint64_t(0);
+  const int64_t at = __shfl(v, 0) & ~int64_t(3), last = __shfl(v, np + 2);  // loads of four start at a multiple of four
+  int32_t len = ok && t < np + 2 ? int32_t(next - v) : 0;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) len = max(len, __shfl_xor(len, o));
+  if (t < np + 3) R.a[t] = ok ? int32_t(v - at) : 0;
+  if (t == 0) {
     if (!ok) fail(A.status, TPC_E_INVALID);
-    S.ok = ok;
-    S.fits = ok && S.a[SLOTS] - S.a[0] <= STAGE_DIGITS;
+    R.g0 = at;
+    R.first = first;
+    R.np = np;
+    R.row = r;
+    R.half = A.half[r];
+    R.top = len > 0 ? 1 << (31 - __clz(len)) : 0;
+    R.ok = ok;
+    R.fits = ok && last - at <= STAGE_DIGITS;
   }
-  __syncthreads();
-  if (S.fits) {
-    const int32_t m = int32_t(S.a[SLOTS] - S.a[0]);
-    for (int32_t e = threadIdx.x; e < m; e += TPB) {
-      S.t[e] = A.time[S.a[0] + e];
-      S.q[e] = A.q[S.a[0] + e];
-    }
-  }
-  __syncthreads();
 }
 
-struct PadView {
-  List own, lo, hi;
-  int u, r, p;
-  bool valid;
-};
-
-// pad j0 + w of the block, its lists in LDS (LDS) or in the arrays
-template <bool LDS>
-__device__ __forceinline__ PadView pad_view(const CluArgs &A, const Stage &S, int64_t j0, int w) {
-  PadView v;
-  const int64_t j = j0 + w;
-  v.valid = j < A.n_pads;
-  v.u = int(j / A.pads_total);
-  const int32_t jr = int32_t(j - int64_t(v.u) * A.pads_total);
-  v.r = row_of(S.rbase, A.n_rows, jr);
-  v.p = jr - S.rbase[v.r];
-  const int np = 2 * A.half[v.r];
-  auto list = [&](int s) {
-    List L;
-    L.n = int32_t(S.a[s + 1] - S.a[s]);
-    if (LDS) {
-      L.t = S.t + (S.a[s] - S.a[0]);
-      L.q = S.q + (S.a[s] - S.a[0]);
-    } else {
-      L.t = A.time + S.a[s];
-      L.q = A.q + S.a[s];
+// Clusters of the blocks before this one: publishes the block's count, adds
+// up its predecessors' (64 at a time) until it meets an inclusive sum, and
+// publishes its own.  The count travels in the same 64-bit word as its flag,
+// so relaxed device-scope atomics suffice.  Blocks are taken by ticket, so
+// every predecessor has started, and none waits for a later one.
+__device__ __forceinline__ int64_t look_back(const CluArgs &A, int64_t vb, int32_t count) {
+  constexpr uint64_t CNT = uint64_t(1) << 62, INC = uint64_t(2) << 62, VAL = CNT - 1;
+  const int lane = __lane_id();
+  uint64_t *lb = A.lookback;
+  int64_t before = 0;
+  if (vb > 0) {
+    if (lane == 0) __hip_atomic_store(&lb[vb], CNT | uint64_t(count), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int64_t top = vb - 1;  // lane k reads block top - k
+    for (int spins = 0;;) {
+      const int64_t j = top - lane;
+      const uint64_t v = j >= 0 ? __hip_atomic_load(&lb[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : INC;
+      const uint64_t inc = __ballot((v >> 62) == 2), empty = __ballot((v >> 62) == 0);
+      const int first = inc ? __ffsll((unsigned long long)inc) - 1 : 64;
+      const uint64_t need = first < 64 ? ((uint64_t(1) << first) << 1) - 1 : ~uint64_t(0);
+      if (empty & need) {
+        if (++spins > SPIN_MAX) {
+          if (lane == 0) fail(A.status, TPC_E_HIP);
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+        continue;
+      }
+      int64_t x = lane <= first ? int64_t(v & VAL) : 0;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+      before += x;
+      if (first < 64) break;
+      top -= 64;
     }
+  }
+  if (lane == 0)
+    __hip_atomic_store(&lb[vb], INC | uint64_t(before + count), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return before;
+}
+
+// Cluster c from peak k of slot s.
+__device__ __forceinline__ void write_cluster(const CluArgs &A, const Run &R, int s, const Peak &k, int64_t c) {
+  // the oracle's order of operations, each rounded (no fused multiply-add)
+#pragma clang fp contract(off)
+  if (c >= A.cap) return;  // the last block reports it
+  const double padf = double(R.first + s - 1) + double(k.Sp) / double(k.Q);
+  const double timef = double(k.t) + double(k.St) / double(k.Q);
+  A.y[c] = float((padf + 0.5 - double(R.half)) * A.pw);
+  A.z[c] = float((timef + 0.5) * A.tb - A.zoff);
+  A.padf[c] = float(padf);
+  A.timef[c] = float(timef);
+  A.row[c] = uint16_t(R.row);
+  A.qmax[c] = uint16_t(k.v);
+  A.qtot[c] = k.Q;
+}
+
+// The lists of slot s (neighbours stay in the row).
+template <class L, class F>
+__device__ __forceinline__ void lists(const Run &R, int s, F list, L &lo, L &hi) {
+  lo = list(s - 1);
+  hi = list(s + 1);
+  if (R.first + s - 1 == 0) lo.n = 0;
+  if (R.first + s == 2 * R.half) hi.n = 0;
+}
+
+// A run whose digits do not fit in LDS: a wave per pad reads the arrays, once
+// to count (EMIT false: into cnt) and once to write from place o0 on.
+template <bool EMIT>
+__device__ __forceinline__ void sweep(const CluArgs &A, const Run &R, int32_t *cnt, int64_t o0) {
+  const int lane = __lane_id();
+  auto list = [&](int s) {
+    Arrays L;
+    L.t = A.time + R.g0 + R.a[s];
+    L.q = A.q + R.g0 + R.a[s];
+    L.n = R.a[s + 1] - R.a[s];
     return L;
   };
-  v.own = list(w + 1);
-  v.lo = list(w);
-  v.hi = list(w + 2);
-  if (v.p == 0) v.lo.n = 0;  // neighbours stay in the row
-  if (v.p == np - 1) v.hi.n = 0;
-  return v;
-}
-
-template <bool LDS>
-__device__ __forceinline__ int32_t count_pad(const CluArgs &A, const Stage &S, int64_t j0, int w) {
-  const PadView v = pad_view<LDS>(A, S, j0, w);
-  int32_t cnt = 0;
-  if (!v.valid) return 0;
-  const int lane = __lane_id();
-  for (int32_t i0 = 0; i0 < v.own.n; i0 += 64) {
-    const int32_t i = i0 + lane;
-    bool pk = false;
-    if (i < v.own.n) {
-      if (i > 0 && v.own.t[i] <= v.own.t[i - 1]) fail(A.status, TPC_E_INVALID);  // times must increase
-      pk = peak_at(A.q_min, v.own, v.lo, v.hi, i).is;
+  for (int p = threadIdx.x >> 6; p < R.np; p += WAVES) {
+    const Arrays own = list(p + 1);
+    Arrays lo, hi;
+    lists(R, p + 1, list, lo, hi);
+    int64_t o = o0;
+    if (EMIT)
+      for (int x = 0; x < p; ++x) o += cnt[x];
+    int32_t n = 0;
+    for (int32_t i0 = 0; i0 < own.n; i0 += 64) {
+      const int32_t i = i0 + lane;
+      Peak k;
+      k.is = false;
+      if (i < own.n) {
+        const bool hb = i > 0, ha = i + 1 < own.n;
+        const uint32_t d = own.at(i), b = hb ? own.at(i - 1) : 0, a = ha ? own.at(i + 1) : 0;
+        if (hb && (d >> 16) <= (b >> 16)) fail(A.status, TPC_E_INVALID);  // times must increase
+        k = own_pad(A.q_min, d, hb, b, ha, a);
+        if (k.is) other_pads(k, lo, hi);
+      }
+      const uint64_t m = __ballot(k.is);
+      if (EMIT && k.is) write_cluster(A, R, p + 1, k, o + n + __popcll(m & ((1ull << lane) - 1ull)));
+      n += __popcll(m);
     }
-    cnt += __popcll(__ballot(pk));
+    if (!EMIT && lane == 0) cnt[p] = n;
   }
-  return cnt;
 }
 
-__global__ void __launch_bounds__(TPB) k_clu_count(CluArgs A) {
-  __shared__ Stage S;
+__global__ void __launch_bounds__(TPB) k_clu_find(CluArgs A) {
+  __shared__ __align__(16) uint32_t dig[STAGE_DIGITS + 4];
+  __shared__ uint16_t found[STAGE_DIGITS];         // per wave, from its first digit's place: candidates, then peaks
+  __shared__ uint32_t starts[STAGE_DIGITS / 32 + 2];  // bit e: digit e is the first of its pad
+  __shared__ Run R;
+  __shared__ int32_t cnt[MAX_PADS];                // per pad (sweep)
+  __shared__ int32_t wcnt[WAVES];
+  __shared__ int64_t s_vb, s_before;
   const int lane = __lane_id(), wave = threadIdx.x >> 6;
-  const int64_t j0 = int64_t(blockIdx.x) * PADS_PER_BLOCK;
-  stage_block(A, S, j0);
-  int32_t cnt = 0;
-  if (S.ok) cnt = S.fits ? count_pad<true>(A, S, j0, wave) : count_pad<false>(A, S, j0, wave);
-  if (lane == 0) {
-    S.cnt[wave] = cnt;
-    if (j0 + wave < A.n_pads) A.pad_cnt[j0 + wave] = cnt;
-  }
+  if (threadIdx.x == 0) s_vb = int64_t(atomicAdd(A.ticket, 1ull));
+  for (int i = threadIdx.x; i < STAGE_DIGITS / 32 + 2; i += TPB) starts[i] = 0;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int32_t s = 0;
-    for (int w = 0; w < PADS_PER_BLOCK; ++w) s += S.cnt[w];
-    A.blk[blockIdx.x] = s;
-  }
-}
-
-// one block: exclusive scan of the per-block counts, in place; each thread
-// takes PER consecutive counts, so one block scan covers 1024 * PER of them
-__global__ void __launch_bounds__(1024) k_clu_scan(CluArgs A, int64_t nblk) {
-  constexpr int PER = 8;
-  __shared__ int64_t wsum[16];
-  __shared__ int64_t carry_s;
-  if (threadIdx.x == 0) carry_s = 0;
+  const int64_t vb = s_vb;
+  const int part = int(vb % A.parts), r = int(vb / A.parts % A.n_rows), u = int(vb / A.parts / A.n_rows);
+  const int32_t pads = min(max(2 * A.half[r], 0), A.pads_total), step = (pads + A.parts - 1) / A.parts;
+  const int32_t first = min(part * step, pads), np = min(step, pads - first);
+  if (wave == 0) load_run(A, R, u, r, first, min(np, MAX_PADS));
   __syncthreads();
-  const int lane = __lane_id(), wave = threadIdx.x >> 6;
-  for (int64_t base = 0; base < nblk; base += 1024 * PER) {
-    const int64_t i0 = base + int64_t(threadIdx.x) * PER;
-    int32_t v[PER];
-    int64_t sum = 0;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      v[e] = i0 + e < nblk ? A.blk[i0 + e] : 0;
-      sum += v[e];
+  if (np <= MAX_PADS && R.fits) {
+    int32_t mine = 0;  // peaks of this wave
+    const int32_t m = R.a[np + 2];
+    if (A.wide) {
+      for (int32_t e = int32_t(threadIdx.x) * 4; e < m; e += TPB * 4) {
+        const int64_t g = R.g0 + e;
+        uint4 v;
+        if (g + 4 <= A.n) {
+          const ushort4 t = *reinterpret_cast<const ushort4 *>(A.time + g), q = *reinterpret_cast<const ushort4 *>(A.q + g);
+          v = make_uint4(pack(t.x, q.x), pack(t.y, q.y), pack(t.z, q.z), pack(t.w, q.w));
+        } else {  // the arrays' last digits
+          v.x = g < A.n ? pack(A.time[g], A.q[g]) : 0;
+          v.y = g + 1 < A.n ? pack(A.time[g + 1], A.q[g + 1]) : 0;
+          v.z = g + 2 < A.n ? pack(A.time[g + 2], A.q[g + 2]) : 0;
+          v.w = 0;
+        }
+        *reinterpret_cast<uint4 *>(dig + e) = v;
+      }
+    } else {
+      for (int32_t e = threadIdx.x; e < m; e += TPB) {
+        const int64_t g = R.g0 + e;
+        if (g < A.n) dig[e] = pack(A.time[g], A.q[g]);
+      }
     }
-    int64_t inc = sum;
-    for (int o = 1; o < 64; o <<= 1) {
-      const int64_t x = __shfl_up(inc, o);
-      if (lane >= o) inc += x;
+    if (int(threadIdx.x) <= np) {
+      const int32_t e = R.a[threadIdx.x + 1];
+      atomicOr(&starts[e >> 5], 1u << (e & 31));
     }
-    if (lane == 63) wsum[wave] = inc;
     __syncthreads();
-    int64_t ex = carry_s + inc - sum, all = 0;
-    for (int w = 0; w < 16; ++w) {
-      if (w < wave) ex += wsum[w];
-      all += wsum[w];
+    // the wave's share of the own digits: whole groups of 64
+    const int32_t e0 = R.a[1], e1 = R.a[np + 1];
+    const int32_t groups = (e1 - e0 + 63) >> 6, per = (groups + WAVES - 1) / WAVES;
+    const int32_t w0 = min(e1, e0 + wave * per * 64), w1 = min(e1, w0 + per * 64);
+    uint16_t *list = found + (w0 - e0);
+    int32_t n_cand = 0;
+    for (int32_t eb = w0; eb < w1; eb += 64) {
+      const int32_t e = eb + lane;
+      bool c = false;
+      if (e < w1) {
+        const bool hb = !((starts[e >> 5] >> (e & 31)) & 1u), ha = !((starts[(e + 1) >> 5] >> ((e + 1) & 31)) & 1u);
+        const uint32_t d = dig[e], b = dig[max(e - 1, 0)], a = dig[e + 1];
+        if (hb && (d >> 16) <= (b >> 16)) fail(A.status, TPC_E_INVALID);  // times must increase
+        c = own_pad(A.q_min, d, hb, b, ha, a).is;
+      }
+      const uint64_t k = __ballot(c);
+      if (c) list[n_cand + __popcll(k & ((1ull << lane) - 1ull))] = uint16_t(e);
+      n_cand += __popcll(k);
     }
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      if (i0 + e < nblk) A.blk[i0 + e] = int32_t(ex);
-      ex += v[e];
+    auto slot_list = [&](int s) {
+      Packed L;
+      L.d = dig + R.a[s];
+      L.n = R.a[s + 1] - R.a[s];
+      L.top = R.top;
+      return L;
+    };
+    auto peak = [&](int32_t e, int &s) {
+      s = slot_of(R, e);
+      const bool hb = e > R.a[s], ha = e + 1 < R.a[s + 1];
+      Peak k = own_pad(A.q_min, dig[e], hb, dig[max(e - 1, 0)], ha, dig[e + 1]);
+      Packed lo, hi;
+      lists(R, s, slot_list, lo, hi);
+      other_pads(k, lo, hi);
+      return k;
+    };
+    __builtin_amdgcn_wave_barrier();
+    for (int32_t i0 = 0; i0 < n_cand; i0 += 64) {  // the peaks among them, kept in the list's front
+      const int32_t i = i0 + lane;
+      int32_t e = 0;
+      bool is = false;
+      if (i < n_cand) {
+        e = list[i];
+        int s;
+        is = peak(e, s).is;
+      }
+      const uint64_t k = __ballot(is);
+      if (is) list[mine + __popcll(k & ((1ull << lane) - 1ull))] = uint16_t(e);
+      mine += __popcll(k);
+      __builtin_amdgcn_wave_barrier();
     }
-    __syncthreads();  // every thread has read carry_s and wsum
-    if (threadIdx.x == 0) carry_s += all;
+    if (lane == 0) wcnt[wave] = mine;
     __syncthreads();
+    if (wave == 0) {
+      int32_t all = 0;
+      for (int w = 0; w < WAVES; ++w) all += wcnt[w];
+      const int64_t before = look_back(A, vb, all);
+      if (lane == 0) s_before = before;
+    }
+    __syncthreads();
+    int64_t o = s_before;
+    for (int w = 0; w < wave; ++w) o += wcnt[w];
+    for (int32_t i = lane; i < mine; i += 64) {
+      int s;
+      const Peak k = peak(list[i], s);
+      write_cluster(A, R, s, k, o + i);
+    }
+  } else {  // MAX_PADS pads at a time, from the arrays
+    int32_t all = 0;
+    for (int32_t p = 0; p < np; p += MAX_PADS) {
+      if (wave == 0) load_run(A, R, u, r, first + p, min(np - p, MAX_PADS));
+      if (int(threadIdx.x) < MAX_PADS) cnt[threadIdx.x] = 0;
+      __syncthreads();
+      if (R.ok) sweep<false>(A, R, cnt, 0);
+      __syncthreads();
+      for (int x = 0; x < R.np; ++x) all += cnt[x];
+      __syncthreads();
+    }
+    if (wave == 0) {
+      const int64_t before = look_back(A, vb, all);
+      if (lane == 0) s_before = before;
+    }
+    if (threadIdx.x < WAVES) wcnt[threadIdx.x] = threadIdx.x == 0 ? all : 0;
+    __syncthreads();
+    int64_t o = s_before;
+    for (int32_t p = 0; p < np; p += MAX_PADS) {
+      if (wave == 0) load_run(A, R, u, r, first + p, min(np - p, MAX_PADS));
+      if (int(threadIdx.x) < MAX_PADS) cnt[threadIdx.x] = 0;
+      __syncthreads();
+      if (R.ok) sweep<false>(A, R, cnt, 0);
+      __syncthreads();
+      if (R.ok) sweep<true>(A, R, cnt, o);
+      for (int x = 0; x < R.np; ++x) o += cnt[x];
+      __syncthreads();
+    }
   }
-  if (threadIdx.x == 0) {
-    *A.count = carry_s;
-    A.unit_offsets[A.n_units] = carry_s;
-    if (carry_s > A.cap) fail(A.status, TPC_E_CAPACITY);
+  if (r == 0 && part == 0 && threadIdx.x == 0) A.unit_offsets[u] = s_before;
+  if (vb == A.n_blocks - 1 && threadIdx.x == 0) {
+    int64_t total = s_before;
+    for (int w = 0; w < WAVES; ++w) total += wcnt[w];
+    *A.count = total;
+    A.unit_offsets[A.n_units] = total;
+    if (total > A.cap) fail(A.status, TPC_E_CAPACITY);
   }
 }
 
-template <bool LDS>
-__device__ __forceinline__ void emit_pad(const CluArgs &A, const Stage &S, int64_t j0, int w) {
-  const PadView v = pad_view<LDS>(A, S, j0, w);
-  if (!v.valid) return;
-  const int lane = __lane_id();
-  const int64_t j = j0 + w;
-  int64_t o = A.blk[blockIdx.x];
-  for (int64_t k = j0; k < j; ++k) o += A.pad_cnt[k];
-  if (v.p == 0 && v.r == 0 && lane == 0) A.unit_offsets[v.u] = o;  // first pad of the unit
-  const double half = double(A.half[v.r]);
-  for (int32_t i0 = 0; i0 < v.own.n; i0 += 64) {
-    const int32_t i = i0 + lane;
-    Peak k;
-    k.is = false;
-    if (i < v.own.n) k = peak_at(A.q_min, v.own, v.lo, v.hi, i);
-    const uint64_t m = __ballot(k.is);
-    if (k.is) {
-      // the oracle's order of operations, each rounded (no fused multiply-add)
-#pragma clang fp contract(off)
-      const int64_t c = o + __popcll(m & ((1ull << lane) - 1ull));
-      const double padf = double(v.p) + double(k.Sp) / double(k.Q);
-      const double timef = double(k.t) + double(k.St) / double(k.Q);
-      A.y[c] = float((padf + 0.5 - half) * A.pw);
-      A.z[c] = float((timef + 0.5) * A.tb - A.zoff);
-      A.padf[c] = float(padf);
-      A.timef[c] = float(timef);
-      A.row[c] = uint16_t(v.r);
-      A.qmax[c] = uint16_t(k.v);
-      A.qtot[c] = k.Q;
-    }
-    o += __popcll(m);
-  }
-}
-
-__global__ void __launch_bounds__(TPB) k_clu_emit(CluArgs A) {
-  __shared__ Stage S;
-  if (*A.status != TPC_OK) return;
-  const int wave = threadIdx.x >> 6;
-  const int64_t j0 = int64_t(blockIdx.x) * PADS_PER_BLOCK;
-  stage_block(A, S, j0);
-  if (!S.ok) return;
-  if (S.fits) emit_pad<true>(A, S, j0, wave);
-  else emit_pad<false>(A, S, j0, wave);
+// Parts of a row: a block's digits, with the edge pads and the densest rows
+// (a third above the mean), should fit its LDS; a block whose digits do not
+// reads the arrays.  Rows may be longer than the mean: parts of at most
+// MAX_PADS pads there too, where that is possible.
+int32_t parts_per_row(int64_t n, int64_t n_pads, int32_t n_units, int32_t n_rows) {
+  const int64_t rows = int64_t(n_units) * n_rows, pads = n_pads / rows;  // pads: of a row, on average
+  const int64_t most = pads / 2 > 1 ? pads / 2 : 1;
+  const int64_t by_digits = n / rows / (STAGE_DIGITS * 10 / 22) + 1, by_pads = pads * 8 / 5 / MAX_PADS + 1;
+  const int64_t p = by_digits > by_pads ? by_digits : by_pads;
+  return int32_t(p < most ? p : most);
 }
 
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
@@ -367,8 +515,9 @@ size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 extern "C" size_t tpc_clusterize_workspace_size(int32_t n_units, const tpc_pad_geometry_t *g) {
   if (!g || n_units < 1 || g->n_rows < 1 || g->n_rows > MAX_ROWS || g->pads_total < 1) return 0;
   const int64_t n_pads = int64_t(n_units) * g->pads_total;
-  const int64_t nblk = (n_pads + PADS_PER_BLOCK - 1) / PADS_PER_BLOCK;
-  return align256(sizeof(int32_t) * size_t(n_pads)) + align256(sizeof(int32_t) * size_t(nblk));
+  const int64_t rows = int64_t(n_units) * g->n_rows;
+  const int64_t blocks = n_pads / 2 > rows ? n_pads / 2 : rows;  // parts have at least two pads on average
+  return 256 + align256(sizeof(int32_t) * MAX_ROWS) + align256(sizeof(uint64_t) * size_t(blocks));
 }
 
 extern "C" int tpc_clusterize(const tpc_digits_t *digits, const tpc_pad_geometry_t *g,
@@ -414,14 +563,16 @@ extern "C" int tpc_clusterize(const tpc_digits_t *digits, const tpc_pad_geometry
   A.count = out->count;
   A.status = out->status;
   char *ws = static_cast<char *>(workspace);
-  A.pad_cnt = reinterpret_cast<int32_t *>(ws);
-  A.blk = reinterpret_cast<int32_t *>(ws + align256(sizeof(int32_t) * size_t(A.n_pads)));
-  const int64_t nblk = (A.n_pads + PADS_PER_BLOCK - 1) / PADS_PER_BLOCK;
+  A.ticket = reinterpret_cast<unsigned long long *>(ws);
+  A.rbase = reinterpret_cast<int32_t *>(ws + 256);
+  A.lookback = reinterpret_cast<uint64_t *>(ws + 256 + align256(sizeof(int32_t) * MAX_ROWS));
+  A.parts = parts_per_row(A.n, A.n_pads, A.n_units, A.n_rows);
+  A.n_blocks = int64_t(A.n_units) * A.n_rows * A.parts;
+  A.wide = ((reinterpret_cast<uintptr_t>(A.time) | reinterpret_cast<uintptr_t>(A.q)) & 7) == 0;
 
   hipStream_t st = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(k_clu_init, dim3(1), dim3(1), 0, st, A);
-  hipLaunchKernelGGL(k_clu_count, dim3(unsigned(nblk)), dim3(TPB), 0, st, A);
-  hipLaunchKernelGGL(k_clu_scan, dim3(1), dim3(1024), 0, st, A, nblk);
-  hipLaunchKernelGGL(k_clu_emit, dim3(unsigned(nblk)), dim3(TPB), 0, st, A);
+  const int64_t ib = (A.n_blocks + TPB - 1) / TPB;
+  hipLaunchKernelGGL(k_clu_init, dim3(unsigned(ib > 1024 ? 1024 : ib)), dim3(TPB), 0, st, A);
+  hipLaunchKernelGGL(k_clu_find, dim3(unsigned(A.n_blocks)), dim3(TPB), 0, st, A);
   return hipGetLastError() == hipSuccess ? TPC_OK : TPC_E_HIP;
 }
