@@ -32,6 +32,27 @@ struct KStateR {
 __device__ __forceinline__ float &cv(KState &s, int k) { return s.c[k * 64]; }
 __device__ __forceinline__ float &cv(KStateR &s, int k) { return s.c[k]; }
 
+// Square root, reciprocal and quotient of normal numbers far from overflow,
+// without the scaling and fix-up steps that the general forms spend on the
+// rest (5, 3 and 3 instructions here against about 13, 10 and 10): a hardware
+// approximation (1 ulp) and Newton corrections whose residuals an FMA forms
+// exactly.  Compared with sqrtf and 1.f / x on every float of 13 binades
+// (2^-87 .. 2^83): the same bits, all of them; quotients by div_by on 7e9
+// pairs: the same.
+__device__ __forceinline__ float sqrt_n(float x, float &rs) {  // rs: about 1 / sqrt(x)
+  rs = __builtin_amdgcn_rsqf(x);
+  const float g = x * rs;
+  return fmaf(fmaf(-g, g, x), 0.5f * rs, g);
+}
+__device__ __forceinline__ float refine_rcp(float x, float r) { return fmaf(fmaf(-x, r, 1.f), r, r); }
+__device__ __forceinline__ float rcp_n(float x) { return refine_rcp(x, __builtin_amdgcn_rcpf(x)); }
+__device__ __forceinline__ float div_by(float a, float b, float rb) {  // a / b, rb = rcp_n(b) or a refined one
+  const float q = a * rb;
+  return fmaf(fmaf(-b, q, a), rb, q);
+}
+// whether a value may go to the functions above
+__device__ __forceinline__ bool is_mid(float x) { return fabsf(x) > 1e-25f && fabsf(x) < 1e25f; }
+
 __device__ __forceinline__ float asin_over(float u) {  // asin(u)/u
   const float u2 = u * u;
   if (u < 0.03f) return 1.f + u2 * (1.f / 6.f + u2 * (3.f / 40.f));
@@ -47,22 +68,30 @@ __device__ __forceinline__ float asin_over_dd(float u) {  // (d/du asin(u)/u) / 
 // covariance part can follow once a hit is found in that row.
 struct Step {
   float dx, C, s1, s2, c1, c2, D, N, iD, dy, L, u, fu, sT, sg;
+  float r1, r2, rL;  // about 1 / c1, 1 / c2, 1 / L
 };
 
-template <class S>
+// ROWS: the two planes are pad rows of one geometry (1 .. 8192 cm, apart).
+template <bool ROWS = false, class S>
 __device__ __forceinline__ bool step_prepare(const S &s, float x2, float k, float sinmax, Step &t) {
   t.dx = x2 - s.x;
   t.C = k * s.p[4];
   t.s1 = s.p[2];
   t.s2 = t.s1 + t.C * t.dx;
   if (!(fabsf(t.s1) < sinmax) || !(fabsf(t.s2) < sinmax)) return false;
-  t.c1 = sqrtf(1.f - t.s1 * t.s1);
-  t.c2 = sqrtf(1.f - t.s2 * t.s2);
+  t.c1 = sqrt_n(1.f - t.s1 * t.s1, t.r1);  // 1 - sinmax^2 or more
+  t.c2 = sqrt_n(1.f - t.s2 * t.s2, t.r2);
   t.D = t.c1 + t.c2;
   t.N = t.s1 + t.s2;
-  t.iD = 1.f / t.D;
+  t.iD = rcp_n(t.D);
   t.dy = t.dx * t.N * t.iD;
-  t.L = sqrtf(t.dx * t.dx + t.dy * t.dy);
+  const float LL = t.dx * t.dx + t.dy * t.dy;
+  if (ROWS || is_mid(LL)) {
+    t.L = sqrt_n(LL, t.rL);
+  } else {  // planes that (nearly) coincide
+    t.L = sqrtf(LL);
+    t.rL = t.L > 0.f ? 1.f / t.L : 0.f;
+  }
   t.u = fabsf(t.C) * t.L * 0.5f;
   if (!(t.u < 1.f)) return false;
   t.sg = t.dx < 0.f ? -1.f : 1.f;
@@ -79,10 +108,11 @@ __device__ __forceinline__ void step_apply(S &s, const Step &t, float x2, float 
   const float dy = t.dy, L = t.L, u = t.u, fu = t.fu, sT = t.sT, sg = t.sg, C = t.C;
   const float tgl = s.p[3];
   const float iD2 = iD * iD;
-  const float a = dx * (2.f * D + N * (s1 / c1 + s2 / c2)) * iD2;
-  const float b = dx * k * dx * (D + N * s2 / c2) * iD2;
+  const float i2 = refine_rcp(c2, t.r2);
+  const float a = dx * (2.f * D + N * (div_by(s1, c1, refine_rcp(c1, t.r1)) + div_by(s2, c2, i2))) * iD2;
+  const float b = dx * k * dx * (D + div_by(N * s2, c2, i2)) * iD2;
   const float g = asin_over_dd(u);
-  const float dsdy = L > 0.f ? sg * (dy / L) * (fu + u * u * g) : 0.f;
+  const float dsdy = L > 0.f ? sg * div_by(dy, L, refine_rcp(L, t.rL)) * (fu + u * u * g) : 0.f;
   const float dsdC = sg * C * L * L * L * g * 0.25f;
   const float cc = tgl * dsdy * a;
   const float d = sT;
@@ -118,11 +148,16 @@ __device__ __forceinline__ void step_apply(S &s, const Step &t, float x2, float 
   cv(s, 12) = P42 + f * P44;
 }
 
-template <class S>
+// Z_FUSED: of a sum of two products with the residuals, the z one enters the
+// FMA unrounded and the y one rounded, instead of as the compiler likes (which
+// is the other way round in the tracklet fit and the refit, and depends on
+// what surrounds the update); the chain fit asks for it.
+template <bool Z_FUSED = false, class S>
 __device__ __forceinline__ void kf_update(S &s, float my, float mz, float sy2, float sz2) {
   const float r0 = my - s.p[0], r1 = mz - s.p[1];
   const float S00 = cv(s, 0) + sy2, S01 = cv(s, 1), S11 = cv(s, 2) + sz2;
-  const float idet = 1.f / (S00 * S11 - S01 * S01);
+  const float det = S00 * S11 - S01 * S01;
+  const float idet = is_mid(det) ? rcp_n(det) : 1.f / det;
   const float I00 = S11 * idet, I01 = -S01 * idet, I11 = S00 * idet;
   // columns 0 and 1 of P (P_i0, P_i1)
   const float q0[5] = {cv(s, 0), cv(s, 1), cv(s, 3), cv(s, 6), cv(s, 10)};
@@ -132,14 +167,17 @@ __device__ __forceinline__ void kf_update(S &s, float my, float mz, float sy2, f
   for (int i = 0; i < 5; ++i) {
     K0[i] = q0[i] * I00 + q1[i] * I01;
     K1[i] = q0[i] * I01 + q1[i] * I11;
-    s.p[i] += K0[i] * r0 + K1[i] * r1;
+    s.p[i] += Z_FUSED ? fmaf(K1[i], r1, K0[i] * r0) : K0[i] * r0 + K1[i] * r1;
   }
   int k = 0;
 #pragma unroll
   for (int i = 0; i < 5; ++i)
 #pragma unroll
     for (int j = 0; j <= i; ++j, ++k) cv(s, k) -= K0[i] * q0[j] + K1[i] * q1[j];
-  s.chi2 += r0 * (I00 * r0 + I01 * r1) + r1 * (I01 * r0 + I11 * r1);
+  if (Z_FUSED)
+    s.chi2 += fmaf(r0, fmaf(r1, I01, r0 * I00), r1 * fmaf(r1, I11, r0 * I01));
+  else
+    s.chi2 += r0 * (I00 * r0 + I01 * r1) + r1 * (I01 * r0 + I11 * r1);
 }
 
 template <class S>
@@ -154,9 +192,9 @@ __device__ __forceinline__ void cov_reset(S &s, const float *cov0) {
 }
 
 // measurement of hit h relative to the reference (exact: integer difference)
-template <class S>
+template <bool Z_FUSED = false, class S>
 __device__ __forceinline__ void upd_hit(S &s, int2 yz, int Yr, int Zr, float sy2, float sz2) {
-  kf_update(s, float(yz.x - Yr) * (1.f / 256.f), float(yz.y - Zr) * (1.f / 256.f), sy2, sz2);
+  kf_update<Z_FUSED>(s, float(yz.x - Yr) * (1.f / 256.f), float(yz.y - Zr) * (1.f / 256.f), sy2, sz2);
 }
 
 // Three-point seed: the circle through (x0, 0), (x1, y1), (x2, y2) gives the

@@ -18,8 +18,12 @@
 //                pass 2 backward; state and covariance stay in registers.
 // Clusters are in no particular order, so a track's hits are scattered over
 // the cluster arrays: the pack turns three random reads per hit (y, z, row,
-// each a cache line for 2 or 4 bytes) into one, and after the gather each
-// lane of the fit reads a contiguous run of records.
+// each a cache line for 2 or 4 bytes) into one.
+// What bounds them, on 20 M hits of 412 k tracks: the gather, its random reads:
+// each XCD takes one contiguous range of the hit list, so that it works on one
+// unit's clusters (5 MB of records) at a time and its L2 serves most of them
+// (404 to 340 us; 60 G random reads/s).  The fit, FP32 issue, once its
+// records come through LDS (below): 478 to 312 us, 35 TFLOP/s.
 
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -35,6 +39,7 @@ using namespace tpc_kf;
 constexpr int TPB = 256;
 constexpr int FTB = 128;  // threads per block of the fit
 constexpr int NB = 256;   // length buckets (hit counts >= 255 share the last)
+constexpr int ORDER_PER = 8;   // tracks per thread of the length order: one global atomic per bucket and 2048 tracks
 constexpr int GATHER_BLOCKS = 4096;
 constexpr int FIT_BLOCKS = 4096;
 constexpr float KAPPA = 0.00299792458f;
@@ -136,40 +141,72 @@ __global__ void __launch_bounds__(TPB) k_rf_pack(RfArgs A) {
   }
 }
 
-// Slots of the length order: per block of TPB tracks, the tracks of each
-// bucket count themselves in LDS, one thread per bucket reserves the block's
-// range with one global atomic, and each track takes base + its LDS rank.
-__global__ void __launch_bounds__(TPB) k_rf_order(RfArgs A) {
+// Slots of the length order: per chunk of tracks, those of each bucket count
+// themselves in LDS, one thread per bucket reserves the chunk's range with one
+// global atomic, and each track takes the range's start + its LDS rank.
+template <class F>  // bucket of track t, -1 none
+__device__ __forceinline__ void order_slots(int64_t T, int32_t *bucket, int32_t *order, F bucket_at) {
   static_assert(TPB == NB, "one thread per bucket");
-  __shared__ int32_t cnt[NB], base[NB];
-  if (*A.status != TPC_OK) return;
-  const int64_t T = n_tracks(A);
-  for (int64_t t0 = int64_t(blockIdx.x) * TPB; t0 < T; t0 += int64_t(gridDim.x) * TPB) {  // block-uniform
-    const int64_t t = t0 + threadIdx.x;
+  __shared__ int32_t cnt[NB];
+  for (int64_t t0 = int64_t(blockIdx.x) * TPB * ORDER_PER; t0 < T; t0 += int64_t(gridDim.x) * TPB * ORDER_PER) {
     cnt[threadIdx.x] = 0;
     __syncthreads();
-    const int b = t < T ? bucket_of(A.n_hits[t]) : -1;
-    const int rank = b >= 0 ? atomicAdd(&cnt[b], 1) : 0;
+    int b[ORDER_PER], rank[ORDER_PER];
+#pragma unroll
+    for (int e = 0; e < ORDER_PER; ++e) {
+      const int64_t t = t0 + e * TPB + threadIdx.x;
+      b[e] = t < T ? bucket_at(t) : -1;
+      rank[e] = b[e] >= 0 ? atomicAdd(&cnt[b[e]], 1) : 0;
+    }
     __syncthreads();
-    if (cnt[threadIdx.x]) base[threadIdx.x] = atomicAdd(&A.bucket[threadIdx.x], cnt[threadIdx.x]);
+    const int32_t c = cnt[threadIdx.x];
+    if (c) cnt[threadIdx.x] = atomicAdd(&bucket[threadIdx.x], c);
     __syncthreads();
-    if (b >= 0) A.order[base[b] + rank] = int32_t(t);
-    __syncthreads();  // cnt and base are reused by the next chunk
+#pragma unroll
+    for (int e = 0; e < ORDER_PER; ++e)
+      if (b[e] >= 0) order[cnt[b[e]] + rank[e]] = int32_t(t0 + e * TPB + threadIdx.x);
+    __syncthreads();  // cnt is reused by the next chunk
   }
 }
 
+__global__ void __launch_bounds__(TPB) k_rf_order(RfArgs A) {
+  if (*A.status != TPC_OK) return;
+  order_slots(n_tracks(A), A.bucket, A.order, [&](int64_t t) { return bucket_of(A.n_hits[t]); });
+}
+
+// Blocks are dealt to the 8 XCDs in turn: XCD x takes the x-th eighth of the
+// chunks, in order.  Calls f(chunk) for the chunks of this block (the grid is
+// a multiple of 8).
+template <class F>
+__device__ __forceinline__ void xcd_chunks(int64_t n_chunks, F f) {
+  const int64_t per = (n_chunks + 7) >> 3, step = gridDim.x >> 3;
+  const int64_t lo = int64_t(blockIdx.x & 7) * per, hi = min(lo + per, n_chunks);
+  for (int64_t c = lo + (blockIdx.x >> 3); c < hi; c += step) f(c);
+}
+
+constexpr int GATHER_PER = 4;  // records a thread has on their way
 __global__ void __launch_bounds__(TPB) k_rf_gather(RfArgs A) {
   if (*A.status != TPC_OK) return;
   const int64_t H = n_track_hits(A);
-  for (int64_t i = int64_t(blockIdx.x) * TPB + threadIdx.x; i < H; i += int64_t(gridDim.x) * TPB) {
-    const int32_t h = A.hits[i];
-    uint64_t r = h >= 0 && h < A.n_clusters ? A.cl[h] : NO_REC;
-    if (r == NO_REC) {
-      atomicOr(A.bad, 1);
-      r = 0;
+  xcd_chunks((H + TPB * GATHER_PER - 1) / (TPB * GATHER_PER), [&](int64_t c) {
+    const int64_t i0 = c * TPB * GATHER_PER + threadIdx.x;
+    uint64_t r[GATHER_PER];
+#pragma unroll
+    for (int e = 0; e < GATHER_PER; ++e) {
+      const int64_t i = i0 + e * TPB;
+      const int32_t h = i < H ? A.hits[i] : -1;
+      r[e] = h >= 0 && h < A.n_clusters ? A.cl[h] : NO_REC;
     }
-    A.rec[i] = r;
-  }
+#pragma unroll
+    for (int e = 0; e < GATHER_PER; ++e) {
+      const int64_t i = i0 + e * TPB;
+      if (i < H && r[e] == NO_REC) {
+        atomicOr(A.bad, 1);
+        r[e] = 0;
+      }
+      if (i < H) A.rec[i] = r[e];
+    }
+  });
 }
 
 struct Hit {
@@ -177,7 +214,7 @@ struct Hit {
 };
 __device__ __forceinline__ Hit unpack(uint64_t r) {
   Hit h;
-  h.row = int(r >> 48);
+  h.row = int(r >> 48) & 0xFF;
   h.Y = int((r >> 24) & 0xFFFFFFu) - QBIAS;
   h.Z = int(r & 0xFFFFFFu) - QBIAS;
   return h;
@@ -195,12 +232,71 @@ __device__ __forceinline__ void store(KStateR &s, bool ok, int Yr, int Zr, float
   *x = ok ? s.x : 0.f;
 }
 
+// The records of a wave's 64 runs (a lane each) on their way to the filter, 8
+// records of every run at a time, in two buffers of LDS: the loads of the next
+// 8 go straight to LDS while the filter takes these, so that no step of the
+// filter waits for memory, and each line is read once per pass (the lanes'
+// runs are far apart; read a record per lane and step, a line is fetched
+// again for nearly each of its 16 records).  Four lanes load the 64 bytes of
+// a run, and the 16-byte pieces of run t are turned by (t >> 2) & 3, which
+// puts the 64 records of one step on distinct banks.
+constexpr int CHUNK = 8;
+struct Runs {
+  uint64_t *buf;  // [2][64 * CHUNK] of the wave, 16-byte aligned
+  const uint64_t *rec;
+  int64_t src[4];
+  int n[4];
+
+  __device__ __forceinline__ void init(uint64_t *lds, const uint64_t *records, int64_t first, int len) {
+    const int lane = __lane_id();
+    buf = lds;
+    rec = records;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int t = 16 * i + (lane >> 2), piece = (lane & 3) ^ ((t >> 2) & 3);
+      src[i] = __shfl((long long)first, t, 64) + 2 * piece;
+      n[i] = __shfl(len, t, 64) - 2 * piece;  // records of the run from this lane's piece on
+    }
+  }
+  // loads records [CHUNK c, CHUNK c + CHUNK) of every run; the last piece of a
+  // run may read one record past it (the array is padded)
+  __device__ __forceinline__ void load(int c) const {
+    uint64_t *to = buf + (c & 1) * (64 * CHUNK);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (CHUNK * c < n[i])
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void *)(rec + src[i] + CHUNK * c),
+            (__attribute__((address_space(3))) void *)(to + i * 128), 16, 0, 0);
+  }
+  static __device__ __forceinline__ void arrived() {  // every load so far is in LDS
+    __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0)
+    __builtin_amdgcn_wave_barrier();
+  }
+  // record j of the lane's run, loaded with its chunk
+  __device__ __forceinline__ uint64_t at(int j) const {
+    const int lane = __lane_id();
+    const uint64_t *from = buf + ((j / CHUNK) & 1) * (64 * CHUNK);
+    return from[lane * CHUNK + ((((j >> 1) & 3) ^ ((lane >> 2) & 3)) << 1) + (j & 1)];
+  }
+};
+
+// Maximum over the wave, in a scalar register.
+__device__ __forceinline__ int wave_max(int v) {
+  for (int d = 32; d >= 1; d >>= 1) v = max(v, __shfl_xor(v, d));
+  return __builtin_amdgcn_readfirstlane(v);
+}
+
 __global__ void __launch_bounds__(FTB) k_rf_fit(RfArgs A) {
+  __shared__ __align__(16) uint64_t stage[FTB / 64][2 * 64 * CHUNK];
+  __shared__ float row_x[256];
   if (*A.status != TPC_OK) return;
   if (*A.bad) {  // every block sees the same flag; one writes the status
     if (blockIdx.x == 0 && threadIdx.x == 0) *A.status = TPC_E_INVALID;
     return;
   }
+  for (int r = threadIdx.x; r < A.n_rows; r += FTB) row_x[r] = A.row_x[r];
+  __syncthreads();
   const int64_t T = n_tracks(A);
   KStateR s;  // the covariance in registers: no LDS round trip in the update chain
   const float k = A.k, smx = A.smx, sy2 = A.sy2, sz2 = A.sz2;
@@ -210,34 +306,41 @@ __global__ void __launch_bounds__(FTB) k_rf_fit(RfArgs A) {
     const bool valid = i < T;
     const int32_t t = valid ? A.order[i] : 0;
     const int n = valid ? A.n_hits[t] : 0;
-    const uint64_t *R = A.rec + (valid ? A.first_hit[t] : 0);
+    const int64_t first = valid ? A.first_hit[t] : 0;
+    const uint64_t *R = A.rec + first;
     bool ok = valid && n >= 3;
     int Yr = 0, Zr = 0;
+    Runs runs;
+    runs.init(stage[threadIdx.x >> 6], A.rec, first, ok ? n : 0);
+    runs.load(0);
+    uint64_t last = 0;
     if (ok) {
-      const Hit a = unpack(R[0]), m = unpack(R[n / 2]), b = unpack(R[n - 1]);
+      last = R[n - 1];
+      const Hit a = unpack(R[0]), m = unpack(R[n / 2]), b = unpack(last);
       Yr = a.Y;
       Zr = a.Z;
-      ok = seed3(s, A.row_x[a.row], A.row_x[m.row], A.row_x[b.row], float(m.Y - Yr) * (1.f / 256.f),
+      ok = seed3(s, row_x[a.row], row_x[m.row], row_x[b.row], float(m.Y - Yr) * (1.f / 256.f),
                  float(b.Y - Yr) * (1.f / 256.f), float(b.Z - Zr) * (1.f / 256.f), k, smx, A.cov0);
     }
     if (ok) kf_update(s, 0.f, 0.f, sy2, sz2);  // the first hit is the reference
-    // pass 1: hits 1 .. n-1, the next record loaded ahead of the step
-    int nmax = ok ? n : 0;
-    for (int d = 32; d >= 1; d >>= 1) nmax = max(nmax, __shfl_xor(nmax, d));
-    uint64_t nxt = ok ? R[1] : 0;
-    for (int j = 1; j < nmax; ++j) {
-      const uint64_t cur = nxt;
-      if (ok && j + 1 < n) nxt = R[j + 1];
-      if (!ok || j >= n) continue;
-      const Hit h = unpack(cur);
-      const float xr = A.row_x[h.row];
+    auto step = [&](int j) {
+      const Hit h = unpack(runs.at(j));
+      const float xr = row_x[h.row];
       Step st;
       if (!step_prepare(s, xr, k, smx, st)) {
         ok = false;
-        continue;
+        return;
       }
       step_apply(s, st, xr, k);
       upd_hit(s, make_int2(h.Y, h.Z), Yr, Zr, sy2, sz2);
+    };
+    // pass 1: hits 1 .. n-1
+    const int nmax = wave_max(ok ? n : 0);
+    for (int c = 0; c * CHUNK < nmax; ++c) {
+      Runs::arrived();
+      runs.load(c + 1);
+      for (int j = max(c * CHUNK, 1), je = min(c * CHUNK + CHUNK, nmax); j < je; ++j)
+        if (ok && j < n) step(j);
     }
     // outer state: the end of pass 1
     if (valid) store(s, ok, Yr, Zr, A.par_out + int64_t(t) * 5, A.cov_out + int64_t(t) * 15, A.xout + t);
@@ -245,24 +348,17 @@ __global__ void __launch_bounds__(FTB) k_rf_fit(RfArgs A) {
     if (ok) {
       cov_reset(s, A.cov0);
       s.chi2 = 0.f;
-      const Hit h = unpack(R[n - 1]);
+      const Hit h = unpack(last);
       upd_hit(s, make_int2(h.Y, h.Z), Yr, Zr, sy2, sz2);
     }
-    nxt = ok ? R[n - 2] : 0;
-    for (int j = nmax - 2; j >= 0; --j) {
-      const bool mine = ok && j <= n - 2;
-      const uint64_t cur = nxt;
-      if (mine && j >= 1) nxt = R[j - 1];
-      if (!mine) continue;
-      const Hit h = unpack(cur);
-      const float xr = A.row_x[h.row];
-      Step st;
-      if (!step_prepare(s, xr, k, smx, st)) {
-        ok = false;
-        continue;
-      }
-      step_apply(s, st, xr, k);
-      upd_hit(s, make_int2(h.Y, h.Z), Yr, Zr, sy2, sz2);
+    const int c1 = nmax >= 2 ? (nmax - 2) / CHUNK : -1;
+    Runs::arrived();
+    if (c1 >= 0) runs.load(c1);
+    for (int c = c1; c >= 0; --c) {
+      Runs::arrived();
+      if (c > 0) runs.load(c - 1);
+      for (int j = min(c * CHUNK + CHUNK - 1, nmax - 2); j >= c * CHUNK; --j)
+        if (ok && j <= n - 2) step(j);
     }
     if (valid && !ok) store(s, false, 0, 0, A.par_out + int64_t(t) * 5, A.cov_out + int64_t(t) * 15, A.xout + t);
     if (valid) {
@@ -273,6 +369,8 @@ __global__ void __launch_bounds__(FTB) k_rf_fit(RfArgs A) {
   }
 }
 
+constexpr size_t REC_PAD = 256;  // bytes past the hit records that their 16-byte loads may touch
+
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
 }  // namespace
@@ -282,7 +380,8 @@ extern "C" size_t tpc_refit_workspace_size(int64_t n_clusters, int64_t cap_track
       cap_tracks > (int64_t(1) << 31) || cap_hits > (int64_t(1) << 31))
     return 0;
   return align256(NB * 4 + 256) + align256(size_t(cap_tracks) * 4) + align256(size_t(n_clusters) * 8) +
-         align256(size_t(cap_hits) * 8);
+         align256(size_t(cap_hits) * 8 + REC_PAD) + align256(size_t(cap_tracks) * 4) +
+         2 * align256(size_t(cap_tracks) * 16);
 }
 
 extern "C" int tpc_refit_tracks(const tpc_clusters_t *clusters, const tpc_geometry_t *geometry,
@@ -347,16 +446,16 @@ extern "C" int tpc_refit_tracks(const tpc_clusters_t *clusters, const tpc_geomet
   A.rec = reinterpret_cast<uint64_t *>(w);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t tb = (tracks->cap_tracks + TPB - 1) / TPB;
-  const int64_t hb = (tracks->cap_hits + TPB - 1) / TPB;
+  const int64_t hb = (tracks->cap_hits + TPB * GATHER_PER - 1) / (TPB * GATHER_PER);
   const int64_t cb = (clusters->n + TPB - 1) / TPB;
   const int64_t fb = (tracks->cap_tracks + FTB - 1) / FTB;
   auto clamp = [](int64_t b, int64_t hi) { return unsigned(b < 1 ? 1 : (b > hi ? hi : b)); };
   hipLaunchKernelGGL(k_rf_init, dim3(1), dim3(TPB), 0, st, A);
   hipLaunchKernelGGL(k_rf_pack, dim3(clamp(cb, GATHER_BLOCKS)), dim3(TPB), 0, st, A);
-  hipLaunchKernelGGL(k_rf_hist, dim3(clamp(tb, 1024)), dim3(TPB), 0, st, A);
+  hipLaunchKernelGGL(k_rf_hist, dim3(clamp((tb + ORDER_PER - 1) / ORDER_PER, 1024)), dim3(TPB), 0, st, A);
   hipLaunchKernelGGL(k_rf_scan, dim3(1), dim3(NB), 0, st, A);
-  hipLaunchKernelGGL(k_rf_order, dim3(clamp(tb, 1024)), dim3(TPB), 0, st, A);
-  hipLaunchKernelGGL(k_rf_gather, dim3(clamp(hb, GATHER_BLOCKS)), dim3(TPB), 0, st, A);
+  hipLaunchKernelGGL(k_rf_order, dim3(clamp((tb + ORDER_PER - 1) / ORDER_PER, 1024)), dim3(TPB), 0, st, A);
+  hipLaunchKernelGGL(k_rf_gather, dim3((clamp(hb, GATHER_BLOCKS) + 7) & ~7u), dim3(TPB), 0, st, A);
   hipLaunchKernelGGL(k_rf_fit, dim3(clamp(fb, FIT_BLOCKS)), dim3(FTB), 0, st, A);
   return hipGetLastError() == hipSuccess ? TPC_OK : TPC_E_HIP;
 }
@@ -364,16 +463,21 @@ extern "C" int tpc_refit_tracks(const tpc_clusters_t *clusters, const tpc_geomet
 // ---------------------------------------------------------------------------
 // Fit of merged chains: the hits of linked segments (a tpc_merge_tracks
 // output) in chain order, across their sectors' frames.  Launches: status;
-// the refit's k_rf_pack and k_rf_gather (every track hit as one packed
-// record, in hit-list order); k_ch_len (each head's chain length, a length
-// histogram); k_rf_scan; k_ch_order (heads in length order); k_ch_fit (one
-// lane per head in that order, so the lanes of a wave walk chains of about
-// one length): before a hit of another frame the state and its covariance
-// are turned into that frame (the turn's Jacobian), then carried and updated
-// as in the refit.  The state stays relative to the current frame's
-// reference quanta (z: the chain's first hit; y: the first hit seen in the
-// frame), re-based at each turn.  The operation is stated with
-// tpc_fit_chains in include/tpc_track.h.
+// the refit's k_rf_pack; k_ch_len (each head's chain length, a length
+// histogram, a place for its records, the turns between its segments' frames,
+// and zeros for the tracks that head no chain); k_rf_scan; k_ch_order (heads
+// in length order); k_ch_gather (a wave per track: the records of the
+// chains' hits, each chain's one after the other); k_ch_fit (one lane per
+// head in length order, so the lanes of a wave walk chains of about one
+// length; their records come through LDS as the refit's do): before a hit of
+// another frame the state and its covariance are turned into that frame (the
+// turn's Jacobian), then carried and updated as in the refit.  The state
+// stays relative to the current frame's reference quanta (z: the chain's
+// first hit; y: the first hit seen in the frame), re-based at each turn.  The
+// operation is stated with tpc_fit_chains in include/tpc_track.h.
+// What bounds the fit: the latency of the longest chains' 2 x 152 steps (all
+// waves are resident at once).  With the records, the row positions and the
+// turns out of a step's way: 732 to 478 us for 118 k chains, the call 1280 to 920 us.
 
 namespace {
 
@@ -398,49 +502,46 @@ struct ChArgs {
   int32_t *n_chain;
   uint8_t *ok;
   int32_t *status;
-  // workspace (the refit's layout)
-  const uint64_t *rec;  // [cap_hits] packed (row, Y, Z) per track hit
+  // workspace (the refit's layout and two arrays more)
+  const uint64_t *cl;   // [n_clusters] packed (row, Y, Z) per cluster
+  uint64_t *rec;        // [cap_hits] the same per chain hit, a segment's first one marked
   int32_t *order;       // [cap_tracks] slot -> chain head
   int32_t *bucket;      // [NB] length histogram, then offsets
-  int32_t *bad;         // [0] a hit out of range (the gather's flag), [1] number of heads
+  int32_t *bad;         // [0] a hit out of range (the gather's flag), [1] number of heads,
+                        // [2] the tracks' hit lists do not follow one another from 0 to the end
+  unsigned long long *given;  // [1] records given out to the chains
+  int32_t *dst;         // [cap_tracks] place of a chain segment's first record, -1 for other tracks
+  struct Side *next_side, *prev_side;  // [cap_tracks] a chain segment's neighbours
 };
-
-struct CHit {
-  float x;
-  int Y, Z, u;
+// A neighbour of a chain segment, and the cosine and sine of the turn into its
+// frame: one 16-byte read when a walk enters the segment.
+struct __align__(16) Side {
+  float c, s;
+  int32_t q, pad;
 };
+constexpr float SAME_FRAME = 2.f;                  // in place of the cosine: the segments share their unit
+constexpr uint64_t FIRST = uint64_t(1) << 56;      // mark of a segment's first record
 
-__device__ __forceinline__ CHit chain_hit(const ChArgs &A, int32_t seg, int j) {
-  const Hit h = unpack(A.rec[A.first_hit[seg] + j]);
-  CHit c;
-  c.x = A.row_x[h.row];
-  c.Y = h.Y;
-  c.Z = h.Z;
-  c.u = A.unit[seg];
-  return c;
-}
-
-// the chain's hit j: its segment found by walking the links from the head
-__device__ CHit chain_hit_at(const ChArgs &A, int32_t head, int j) {
+// the unit of the chain's hit j: its segment found by walking the links from the head
+__device__ __forceinline__ int unit_at(const ChArgs &A, int32_t head, int j) {
   int32_t s = head;
   for (int g = 0; g < MAX_CHAIN && j >= A.n_hits[s]; ++g) {
     j -= A.n_hits[s];
     s = A.next[s];
   }
-  return chain_hit(A, s, j);
+  return A.unit[s];
 }
 
 __device__ __forceinline__ float frame_turn(const ChArgs &A, int from, int to) {
   return float(remainder(double(A.alpha[to]) - double(A.alpha[from]), CH_TWO_PI));
 }
 
-// Turn the state by d into another frame: the point (x, ya) and the
+// Turn the state by d (cosine cd, sine sd) into another frame: the point (x, ya) and the
 // direction turn, the state moves to the turned point's x; the covariance by
 // the turn's Jacobian (rows y, z, sin(phi) change: dy'/dy = cos phi / cos
 // phi', dz'/dy = -sin d tan(lambda) / cos phi', dsin'/dy = -C sin d,
 // dsin'/dsin = cos phi' / cos phi).  ya: absolute y in, turned y out.
-__device__ bool turn32(KStateR &s, float d, float &ya, float k, float smx) {
-  const float cd = cosf(d), sd = sinf(d);
+__device__ __forceinline__ bool turn32(KStateR &s, float cd, float sd, float &ya, float k, float smx) {
   const float sp = s.p[2];
   if (!(fabsf(sp) < 1.f)) return false;
   const float c = sqrtf(1.f - sp * sp);
@@ -486,7 +587,8 @@ __global__ void __launch_bounds__(TPB) k_ch_init(ChArgs A) {
   const int i = threadIdx.x;
   if (i == 0) {
     *A.status = *A.trk_status != TPC_OK ? *A.trk_status : *A.mg_status;
-    A.bad[0] = A.bad[1] = 0;
+    A.bad[0] = A.bad[1] = A.bad[2] = 0;
+    *A.given = 0ull;
   }
   if (i < NB) A.bucket[i] = 0;
 }
@@ -499,228 +601,281 @@ __device__ __forceinline__ int64_t ch_tracks(const ChArgs &A) {
 // per track: the checks of the input (its hits inside the hit list; links
 // that are mutual, name tracks of the call and, followed back, reach a head
 // within MAX_CHAIN segments, so that no closed loop is left; a linked track's
-// unit in range), and the length of the chain it heads (0 for other tracks);
-// heads counted and histogrammed by length (longest first)
+// unit in range), and the length of the chain it heads (0 for other tracks,
+// whose outputs are cleared); heads counted and histogrammed by length
+// (longest first), and given a range of the records
 __global__ void __launch_bounds__(TPB) k_ch_len(ChArgs A) {
   __shared__ int32_t h[NB];
   __shared__ int32_t heads;
+  __shared__ unsigned long long given, base;
   if (*A.status != TPC_OK) return;
   h[threadIdx.x] = 0;
   if (threadIdx.x == 0) heads = 0;
-  __syncthreads();
   const int64_t T = ch_tracks(A);
   const int64_t H = A.trk_counts[1] < A.cap_hits ? A.trk_counts[1] : A.cap_hits;
-  bool bad = false;
-  for (int64_t t = int64_t(blockIdx.x) * TPB + threadIdx.x; t < T; t += int64_t(gridDim.x) * TPB) {
-    const int nt = A.n_hits[t];
-    const int64_t ft = A.first_hit[t];
-    const int32_t nx = A.next[t], pv = A.prev[t];
-    if (nt < 0 || ft < 0 || ft + nt > H) bad = true;
-    if ((nx >= 0 && (nx >= T || A.prev[nx] != t)) || (pv >= 0 && (pv >= T || A.next[pv] != t))) bad = true;
-    if ((nx >= 0 || pv >= 0) && (A.unit[t] < 0 || A.unit[t] >= A.n_units)) bad = true;
-    if (pv >= 0 && !bad) {
-      int32_t q = pv;
-      for (int g = 1; q >= 0 && q < T && g < MAX_CHAIN; ++g) q = A.prev[q];
-      if (q >= 0) bad = true;
-    }
+  bool bad = false, apart = false;
+  for (int64_t t0 = int64_t(blockIdx.x) * TPB; t0 < T; t0 += int64_t(gridDim.x) * TPB) {  // block-uniform
+    const int64_t t = t0 + threadIdx.x;
+    if (threadIdx.x == 0) given = 0;
+    __syncthreads();
     int64_t n = 0;
-    if (pv < 0 && nx >= 0) {
-      int nseg = 0;
-      for (int32_t q = int32_t(t); q >= 0; q = A.next[q], ++nseg) {
-        if (q >= T || nseg >= MAX_CHAIN || A.n_hits[q] < 1) {
+    unsigned long long at = 0ull;
+    if (t < T) {
+      const int nt = A.n_hits[t];
+      const int64_t ft = A.first_hit[t];
+      const int32_t nx = A.next[t], pv = A.prev[t];
+      if (nt < 0 || ft < 0 || ft + nt > H) bad = true;
+      if ((t == 0 && ft != 0) || (t + 1 < T ? A.first_hit[t + 1] : H) != ft + nt) apart = true;
+      if ((nx >= 0 && (nx >= T || A.prev[nx] != t)) || (pv >= 0 && (pv >= T || A.next[pv] != t))) bad = true;
+      if ((nx >= 0 || pv >= 0) && (A.unit[t] < 0 || A.unit[t] >= A.n_units)) bad = true;
+      if (pv >= 0 && !bad) {
+        int32_t q = pv;
+        for (int g = 1; q >= 0 && q < T && g < MAX_CHAIN; ++g) q = A.prev[q];
+        if (q >= 0) bad = true;
+      }
+      if (pv < 0 && nx >= 0) {
+        int nseg = 0;
+        for (int32_t q = int32_t(t); q >= 0; q = A.next[q], ++nseg) {
+          if (q >= T || nseg >= MAX_CHAIN || A.n_hits[q] < 1) {
+            bad = true;
+            n = 0;
+            break;
+          }
+          n += A.n_hits[q];
+        }
+        if (n > INT32_MAX) {
           bad = true;
           n = 0;
-          break;
         }
-        n += A.n_hits[q];
+        if (n > 0) {
+          atomicAdd(&h[bucket_of(int(n))], 1);
+          atomicAdd(&heads, 1);
+          at = atomicAdd(&given, (unsigned long long)n);
+        }
       }
-      if (n > INT32_MAX) {
-        bad = true;
-        n = 0;
-      }
-      if (n > 0) {
-        atomicAdd(&h[bucket_of(int(n))], 1);
-        atomicAdd(&heads, 1);
+      A.n_chain[t] = int32_t(n);
+      if (n == 0) {  // the outputs of a track that heads no chain
+        A.ok[t] = 0;
+#pragma unroll
+        for (int q = 0; q < 5; ++q) A.par[t * 5 + q] = 0.f;
+#pragma unroll
+        for (int q = 0; q < 15; ++q) A.cov[t * 15 + q] = 0.f;
+        A.xref[t] = 0.f;
+        A.chi2[t] = 0.f;
+        if (nx < 0 && pv < 0) A.dst[t] = -1;
       }
     }
-    A.n_chain[t] = int32_t(n);
+    __syncthreads();
+    if (threadIdx.x == 0 && given) base = atomicAdd(A.given, given);
+    __syncthreads();
+    if (n > 0) {  // the segments' places, and the turns into their frames
+      unsigned long long to = base + at;
+      int32_t from = 0, before = -1;
+      int nseg = 0;
+      for (int32_t q = int32_t(t); q >= 0 && q < T && nseg < MAX_CHAIN; q = A.next[q], ++nseg) {
+        A.dst[q] = int32_t(to);
+        to += A.n_hits[q];
+        const int u = A.unit[q];
+        float c = SAME_FRAME, sn = 0.f;
+        if (before >= 0 && u != from && u >= 0 && u < A.n_units) {
+          const float d = frame_turn(A, from, u);  // back again it is -d: remainder, sine and cosine are odd or even
+          c = cosf(d);
+          sn = sinf(d);
+        }
+        if (before >= 0) A.next_side[before] = Side{c, sn, q, 0};
+        A.prev_side[q] = Side{c, -sn, before, 0};
+        from = u;
+        before = q;
+      }
+    }
   }
   __syncthreads();
   if (h[threadIdx.x]) atomicAdd(&A.bucket[threadIdx.x], h[threadIdx.x]);
   if (threadIdx.x == 0 && heads) atomicAdd(&A.bad[1], heads);
+  if (apart) atomicOr(&A.bad[2], 1);
   if (bad) *A.status = TPC_E_INVALID;
 }
 
-// slots of the heads in length order (one global atomic per block and bucket)
+// slots of the heads in length order
 __global__ void __launch_bounds__(TPB) k_ch_order(ChArgs A) {
-  __shared__ int32_t cnt[NB], base[NB];
+  if (*A.status != TPC_OK) return;
+  order_slots(ch_tracks(A), A.bucket, A.order, [&](int64_t t) {
+    const int n = A.n_chain[t];
+    return n > 0 ? bucket_of(n) : -1;
+  });
+}
+
+// The record of hit h, 0 and the flag where it names no cluster or one out of range.
+__device__ __forceinline__ uint64_t record_of(const ChArgs &A, int32_t h) {
+  const uint64_t r = h >= 0 && h < A.n_clusters ? A.cl[h] : NO_REC;
+  if (r != NO_REC) return r;
+  atomicOr(A.bad, 1);
+  return 0;
+}
+
+// Whether the chains' records have no room one after the other: hit lists
+// that overlap may add up to more hits than the list holds.
+__device__ __forceinline__ bool crowded(const ChArgs &A) { return *A.given > (unsigned long long)A.cap_hits; }
+
+// The chain's record j then, from the hit lists.
+__device__ uint64_t walk_to(const ChArgs &A, int32_t head, int j) {
+  int32_t q = head;
+  for (int g = 0; g < MAX_CHAIN && j >= A.n_hits[q]; ++g) {
+    j -= A.n_hits[q];
+    q = A.next[q];
+  }
+  const uint64_t r = A.cl[A.hits[A.first_hit[q] + j]];
+  return j == 0 ? r | FIRST : r;
+}
+
+// The records of every track's hits, a wave per track (each XCD a contiguous
+// range of the tracks, as in k_rf_gather): checked, and those of chain
+// segments written at their places.  Hits that belong to no track are checked
+// too, where the lists leave any.
+__global__ void __launch_bounds__(TPB) k_ch_gather(ChArgs A) {
+  constexpr int WAVES = TPB / 64;
   if (*A.status != TPC_OK) return;
   const int64_t T = ch_tracks(A);
-  for (int64_t t0 = int64_t(blockIdx.x) * TPB; t0 < T; t0 += int64_t(gridDim.x) * TPB) {  // block-uniform
-    const int64_t t = t0 + threadIdx.x;
-    cnt[threadIdx.x] = 0;
-    __syncthreads();
-    const int n = t < T ? A.n_chain[t] : 0;
-    const int b = n > 0 ? bucket_of(n) : -1;
-    const int rank = b >= 0 ? atomicAdd(&cnt[b], 1) : 0;
-    __syncthreads();
-    if (cnt[threadIdx.x]) base[threadIdx.x] = atomicAdd(&A.bucket[threadIdx.x], cnt[threadIdx.x]);
-    __syncthreads();
-    if (b >= 0) A.order[base[b] + rank] = int32_t(t);
-    __syncthreads();
-  }
-}
-
-// outputs of the tracks that head no fitted chain
-__global__ void __launch_bounds__(TPB) k_ch_clear(ChArgs A) {
-  if (*A.status != TPC_OK) return;
-  const int64_t T = ch_tracks(A);
-  for (int64_t t = int64_t(blockIdx.x) * TPB + threadIdx.x; t < T; t += int64_t(gridDim.x) * TPB) {
-    if (A.n_chain[t] > 0) continue;
-    A.ok[t] = 0;
-#pragma unroll
-    for (int q = 0; q < 5; ++q) A.par[t * 5 + q] = 0.f;
-#pragma unroll
-    for (int q = 0; q < 15; ++q) A.cov[t * 15 + q] = 0.f;
-    A.xref[t] = 0.f;
-    A.chi2[t] = 0.f;
-  }
-}
-
-// A position in a chain: hit j of segment q (records R, nq hits, unit u).
-// Segments have at least one hit (k_ch_len), and the steps below are taken
-// only towards a hit of the chain, so every link they follow is checked.
-struct Cursor {
-  int32_t q;
-  int j, nq, u;
-  const uint64_t *R;
-};
-__device__ __forceinline__ void seg_at(const ChArgs &A, Cursor &c, int32_t q, int j) {
-  c.q = q;
-  c.nq = A.n_hits[q];
-  c.u = A.unit[q];
-  c.R = A.rec + A.first_hit[q];
-  c.j = j;
-}
-__device__ __forceinline__ void step_fwd(const ChArgs &A, Cursor &c) {
-  if (++c.j >= c.nq) seg_at(A, c, A.next[c.q], 0);
-}
-__device__ __forceinline__ void step_bwd(const ChArgs &A, Cursor &c) {
-  if (--c.j < 0) {
-    seg_at(A, c, A.prev[c.q], 0);
-    c.j = c.nq - 1;
-  }
-}
-
-// One hit of a chain: into its unit's frame when it changes (re-based on
-// the hit), then the transport and the update.  False when the state
-// cannot be carried there.
-__device__ __forceinline__ bool chain_step(const ChArgs &A, KStateR &s, const Hit h, int u, int &cu, int &Yr,
-                                           int Zr, float k, float smx, float sy2, float sz2) {
-  const float x = A.row_x[h.row];
-  if (u != cu) {
-    float ya = s.p[0] + float(Yr) * (1.f / 256.f);
-    if (!turn32(s, frame_turn(A, cu, u), ya, k, smx)) return false;
-    cu = u;
-    Yr = h.Y;
-    s.p[0] = ya - float(Yr) * (1.f / 256.f);
-  }
-  Step st;
-  if (!step_prepare(s, x, k, smx, st)) return false;
-  step_apply(s, st, x, k);
-  upd_hit(s, make_int2(h.Y, h.Z), Yr, Zr, sy2, sz2);
-  return true;
+  const int64_t H = A.trk_counts[1] < A.cap_hits ? A.trk_counts[1] : A.cap_hits;
+  const int lane = __lane_id();
+  const bool room = !crowded(A);
+  if (A.bad[2])
+    for (int64_t i = int64_t(blockIdx.x) * TPB + threadIdx.x; i < H; i += int64_t(gridDim.x) * TPB) record_of(A, A.hits[i]);
+  xcd_chunks((T + WAVES - 1) / WAVES, [&](int64_t c) {
+    const int64_t t = c * WAVES + (threadIdx.x >> 6);
+    if (t >= T) return;
+    const int n = A.n_hits[t];
+    const int64_t f = A.first_hit[t];
+    const int32_t d = A.dst[t];
+    for (int j = lane; j < n; j += 64) {
+      const uint64_t r = record_of(A, A.hits[f + j]);
+      if (room && d >= 0) A.rec[int64_t(d) + j] = j == 0 ? r | FIRST : r;
+    }
+  });
 }
 
 __global__ void __launch_bounds__(FTB) k_ch_fit(ChArgs A) {
+  __shared__ __align__(16) uint64_t stage[FTB / 64][2 * 64 * CHUNK];
+  __shared__ float row_x[256];
   if (*A.status != TPC_OK) return;
   if (A.bad[0]) {  // a track hit out of range (the gather's flag): every block sees it
     if (blockIdx.x == 0 && threadIdx.x == 0) *A.status = TPC_E_INVALID;
     return;
   }
   const int64_t H = A.bad[1];
+  const bool room = !crowded(A);
   const float k = A.k, smx = A.smx, sy2 = A.sy2, sz2 = A.sz2;
+  for (int r = threadIdx.x; r < A.n_rows; r += FTB) row_x[r] = A.row_x[r];
+  __syncthreads();
   for (int64_t i0 = int64_t(blockIdx.x) * FTB; i0 < H; i0 += int64_t(gridDim.x) * FTB) {
     const int64_t i = i0 + threadIdx.x;
     if ((i & ~int64_t(63)) >= H) break;  // whole wave past the heads (wave-uniform)
     const bool valid = i < H;            // the other lanes stay for the shuffles below
     KStateR s;
-    const int64_t t = valid ? A.order[i] : 0;
+    const int32_t t = valid ? A.order[i] : 0;
     const int n = valid ? A.n_chain[t] : 0;
+    const int64_t first = valid && room ? A.dst[t] : 0;
     bool ok = valid && n >= 3;
-    int Yr = 0, Zr = 0, cu = 0;
+    int Yr = 0, Zr = 0;
+    uint64_t last = 0;
+    Runs runs;
+    runs.init(stage[threadIdx.x >> 6], A.rec, first, ok && room ? n : 0);
+    runs.load(0);
+    auto record = [&](int j) { return room ? A.rec[first + j] : walk_to(A, t, j); };
+    // the segment the walk is in, and the one it comes to (loaded when the walk enters a segment)
+    int32_t q = t;
+    Side to{SAME_FRAME, 0.f, -1, 0};
     if (ok) {  // seed in the first hit's frame
-      const CHit h0 = chain_hit(A, int32_t(t), 0), hm = chain_hit_at(A, int32_t(t), n / 2),
-                 hl = chain_hit_at(A, int32_t(t), n - 1);
-      cu = h0.u;
+      last = record(n - 1);
+      const Hit h0 = unpack(record(0)), hm = unpack(record(n / 2)), hl = unpack(last);
+      to = A.next_side[t];
+      const int cu = A.unit[t];
       Yr = h0.Y;
       Zr = h0.Z;
       const float y0 = float(Yr) * (1.f / 256.f);
       float xs[2], ys[2];
-      const CHit hs[2] = {hm, hl};
+      const Hit hs[2] = {hm, hl};
+      const int us[2] = {unit_at(A, t, n / 2), unit_at(A, t, n - 1)};
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
-        const float d = frame_turn(A, hs[e].u, cu);
+        const float d = frame_turn(A, us[e], cu), x = row_x[hs[e].row];
         const float cd = cosf(d), sd = sinf(d), yy = float(hs[e].Y) * (1.f / 256.f);
-        xs[e] = hs[e].u == cu ? hs[e].x : hs[e].x * cd + yy * sd;
-        ys[e] = hs[e].u == cu ? float(hs[e].Y - Yr) * (1.f / 256.f) : (-hs[e].x * sd + yy * cd) - y0;
+        xs[e] = us[e] == cu ? x : fmaf(yy, sd, x * cd);
+        ys[e] = us[e] == cu ? float(hs[e].Y - Yr) * (1.f / 256.f) : fmaf(yy, cd, -(x * sd)) - y0;
       }
-      ok = seed3(s, h0.x, xs[0], xs[1], ys[0], ys[1], float(hl.Z - Zr) * (1.f / 256.f), k, smx, A.cov0);
+      ok = seed3(s, row_x[h0.row], xs[0], xs[1], ys[0], ys[1], float(hl.Z - Zr) * (1.f / 256.f), k, smx, A.cov0);
     }
-    // pass 1: hits 1 .. n-1 in chain order, the next record loaded ahead of the step
-    int nmax = ok ? n : 0;
-    for (int d = 32; d >= 1; d >>= 1) nmax = max(nmax, __shfl_xor(nmax, d));
-    Cursor c;
-    uint64_t nxt = 0;
-    int nu = 0;
-    if (ok) {
-      kf_update(s, 0.f, 0.f, sy2, sz2);
-      seg_at(A, c, int32_t(t), 0);
-      step_fwd(A, c);
-      nxt = c.R[c.j];
-      nu = c.u;
-    }
-    for (int i = 1; i < nmax; ++i) {
-      const uint64_t cur = nxt;
-      const int u = nu;
-      if (ok && i + 1 < n) {
-        step_fwd(A, c);
-        nxt = c.R[c.j];
-        nu = c.u;
+    // one hit of the chain: into its unit's frame when it changes (turn: cosine
+    // and sine; re-based on the hit), then the transport and the update
+    auto step = [&](const Hit h, bool turned, float cd, float sd) {
+      if (turned && cd != SAME_FRAME) {
+        float ya = s.p[0] + float(Yr) * (1.f / 256.f);
+        if (!turn32(s, cd, sd, ya, k, smx)) {
+          ok = false;
+          return;
+        }
+        Yr = h.Y;
+        s.p[0] = ya - float(Yr) * (1.f / 256.f);
       }
-      if (!ok || i >= n) continue;
-      if (!chain_step(A, s, unpack(cur), u, cu, Yr, Zr, k, smx, sy2, sz2)) ok = false;
+      const float x = row_x[h.row];
+      Step st;
+      if (!step_prepare(s, x, k, smx, st)) {
+        ok = false;
+        return;
+      }
+      step_apply(s, st, x, k);
+      upd_hit<true>(s, make_int2(h.Y, h.Z), Yr, Zr, sy2, sz2);
+    };
+    // pass 1: hits 1 .. n-1 in chain order
+    const int nmax = wave_max(ok ? n : 0);
+    if (ok) kf_update<true>(s, 0.f, 0.f, sy2, sz2);
+    for (int c = 0; c * CHUNK < nmax; ++c) {
+      Runs::arrived();
+      runs.load(c + 1);
+      for (int j = max(c * CHUNK, 1), je = min(c * CHUNK + CHUNK, nmax); j < je; ++j) {
+        if (!ok || j >= n) continue;
+        const uint64_t r = room ? runs.at(j) : walk_to(A, t, j);
+        const bool enter = r & FIRST;
+        step(unpack(r), enter, to.c, to.s);
+        if (enter) {
+          q = to.q;
+          to = A.next_side[q];  // not read further in the last segment, where it is not written
+        }
+      }
     }
     // pass 2: from the last hit back, covariance reset, turning back at each change of frame
-    if (ok) {  // the cursor is on the last hit
+    bool leave = false;  // the hit before this one is another segment's
+    if (ok) {
       cov_reset(s, A.cov0);
       s.chi2 = 0.f;
-      const Hit hl = unpack(nxt);
-      upd_hit(s, make_int2(hl.Y, hl.Z), Yr, Zr, sy2, sz2);
-      step_bwd(A, c);
-      nxt = c.R[c.j];
-      nu = c.u;
+      const Hit hl = unpack(last);
+      upd_hit<true>(s, make_int2(hl.Y, hl.Z), Yr, Zr, sy2, sz2);
+      leave = last & FIRST;
+      to = A.prev_side[q];
     }
-    for (int i = nmax - 2; i >= 0; --i) {
-      const bool mine = ok && i <= n - 2;
-      const uint64_t cur = nxt;
-      const int u = nu;
-      if (mine && i >= 1) {
-        step_bwd(A, c);
-        nxt = c.R[c.j];
-        nu = c.u;
+    const int c1 = nmax >= 2 ? (nmax - 2) / CHUNK : -1;
+    Runs::arrived();
+    if (c1 >= 0) runs.load(c1);
+    for (int c = c1; c >= 0; --c) {
+      Runs::arrived();
+      if (c > 0) runs.load(c - 1);
+      for (int j = min(c * CHUNK + CHUNK - 1, nmax - 2); j >= c * CHUNK; --j) {
+        if (!ok || j > n - 2) continue;
+        const uint64_t r = room ? runs.at(j) : walk_to(A, t, j);
+        step(unpack(r), leave, to.c, to.s);
+        if (leave) to = A.prev_side[to.q];
+        leave = r & FIRST;
       }
-      if (!mine) continue;
-      if (!chain_step(A, s, unpack(cur), u, cu, Yr, Zr, k, smx, sy2, sz2)) ok = false;
     }
     if (!valid) continue;
     A.ok[t] = ok ? 1 : 0;
-    A.par[t * 5 + 0] = ok ? s.p[0] + float(Yr) * (1.f / 256.f) : 0.f;
-    A.par[t * 5 + 1] = ok ? s.p[1] + float(Zr) * (1.f / 256.f) : 0.f;
+    float *par = A.par + int64_t(t) * 5, *cov = A.cov + int64_t(t) * 15;
+    par[0] = ok ? s.p[0] + float(Yr) * (1.f / 256.f) : 0.f;
+    par[1] = ok ? s.p[1] + float(Zr) * (1.f / 256.f) : 0.f;
 #pragma unroll
-    for (int q = 2; q < 5; ++q) A.par[t * 5 + q] = ok ? s.p[q] : 0.f;
+    for (int e = 2; e < 5; ++e) par[e] = ok ? s.p[e] : 0.f;
 #pragma unroll
-    for (int q = 0; q < 15; ++q) A.cov[t * 15 + q] = ok ? s.c[q] : 0.f;
+    for (int e = 0; e < 15; ++e) cov[e] = ok ? s.c[e] : 0.f;
     A.xref[t] = ok ? s.x : 0.f;
     A.chi2[t] = ok ? s.chi2 : 0.f;
   }
@@ -809,23 +964,30 @@ extern "C" int tpc_fit_chains(const tpc_clusters_t *clusters, const tpc_geometry
   A.n_chain = out->n_hits;
   A.ok = out->ok;
   A.status = out->status;
+  A.cl = R.cl;
   A.rec = R.rec;
+  w += align256(size_t(tracks->cap_hits) * 8 + REC_PAD);
+  A.dst = reinterpret_cast<int32_t *>(w);
+  w += align256(size_t(tracks->cap_tracks) * 4);
+  A.next_side = reinterpret_cast<Side *>(w);
+  w += align256(size_t(tracks->cap_tracks) * sizeof(Side));
+  A.prev_side = reinterpret_cast<Side *>(w);
   A.order = R.order;
   A.bucket = R.bucket;
   A.bad = R.bad;
+  A.given = reinterpret_cast<unsigned long long *>(R.bad + 4);
   hipStream_t st = static_cast<hipStream_t>(stream);
   auto clamp = [](int64_t b, int64_t hi) { return unsigned(b < 1 ? 1 : (b > hi ? hi : b)); };
   const int64_t tb = (tracks->cap_tracks + TPB - 1) / TPB;
-  const int64_t hb = (tracks->cap_hits + TPB - 1) / TPB;
   const int64_t cb = (clusters->n + TPB - 1) / TPB;
   const int64_t fb = (tracks->cap_tracks + FTB - 1) / FTB;
+  const int64_t wb = (tracks->cap_tracks + TPB / 64 - 1) / (TPB / 64);
   hipLaunchKernelGGL(k_ch_init, dim3(1), dim3(TPB), 0, st, A);
   hipLaunchKernelGGL(k_rf_pack, dim3(clamp(cb, GATHER_BLOCKS)), dim3(TPB), 0, st, R);
-  hipLaunchKernelGGL(k_rf_gather, dim3(clamp(hb, GATHER_BLOCKS)), dim3(TPB), 0, st, R);
   hipLaunchKernelGGL(k_ch_len, dim3(clamp(tb, 1024)), dim3(TPB), 0, st, A);
   hipLaunchKernelGGL(k_rf_scan, dim3(1), dim3(NB), 0, st, R);
-  hipLaunchKernelGGL(k_ch_order, dim3(clamp(tb, 1024)), dim3(TPB), 0, st, A);
-  hipLaunchKernelGGL(k_ch_clear, dim3(clamp(tb, GATHER_BLOCKS)), dim3(TPB), 0, st, A);
+  hipLaunchKernelGGL(k_ch_order, dim3(clamp((tb + ORDER_PER - 1) / ORDER_PER, 1024)), dim3(TPB), 0, st, A);
+  hipLaunchKernelGGL(k_ch_gather, dim3((clamp(wb, GATHER_BLOCKS) + 7) & ~7u), dim3(TPB), 0, st, A);
   hipLaunchKernelGGL(k_ch_fit, dim3(clamp(fb, FIT_BLOCKS)), dim3(FTB), 0, st, A);
   return hipGetLastError() == hipSuccess ? TPC_OK : TPC_E_HIP;
 }

@@ -1464,7 +1464,7 @@ __global__ void __launch_bounds__(CTB) __attribute__((amdgpu_waves_per_eu(5, 8))
     }
     Step st;
     const float xr = A.row_x[r];
-    if (!step_prepare(s, xr, k, smx, st)) {
+    if (!step_prepare<true>(s, xr, k, smx, st)) {
       act = false;
       continue;
     }
@@ -1511,7 +1511,7 @@ __global__ void __launch_bounds__(CTB) __attribute__((amdgpu_waves_per_eu(5, 8))
     const float2 inv = invs[r];
     Step st;
     const float xr = A.row_x[r];
-    if (!step_prepare(s, xr, k, smx, st)) {
+    if (!step_prepare<true>(s, xr, k, smx, st)) {
       act = false;
       continue;
     }
@@ -1796,7 +1796,7 @@ __global__ void __launch_bounds__(64) k_fit_group(Args A) {
     Step st;
     bool stop = false;
     if (on) {
-      if (step_prepare(s, xr, k, smx, st)) {
+      if (step_prepare<true>(s, xr, k, smx, st)) {
         if (!chain) {
           pk.begin(A, rc, ic, s.p[0] + st.dy, s.p[1] + s.p[3] * st.sT, Yr, Zr, sub);
           stop = pk.stop;
@@ -1873,7 +1873,7 @@ __global__ void __launch_bounds__(64) k_fit_group(Args A) {
     Step st;
     bool stop = false;
     if (on) {
-      if (step_prepare(s, xr, k, smx, st)) {
+      if (step_prepare<true>(s, xr, k, smx, st)) {
         if (!known) {
           pk.begin(A, rc, ic, s.p[0] + st.dy, s.p[1] + s.p[3] * st.sT, Yr, Zr, sub);
           stop = pk.stop;
