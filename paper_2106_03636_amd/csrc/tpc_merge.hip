@@ -15,19 +15,18 @@
 //   k_mg_sort   one wave per cell: its segments sorted by first row (bitonic
 //               in LDS up to SORT_MAX; larger cells by one lane), with their
 //               inner z', y, x and first row written in that order as one
-//               16-byte record each (the scan below reads one record per
-//               candidate, and neighbouring lanes share its cache lines);
-//   k_mg_pairs  one lane per segment a: for each unit on its side within
-//               max_dalpha, its outer state turned into that unit's frame
-//               (parameters, FP64); in each cell its z' window meets, two
-//               binary searches find the segments starting 1 .. max_gap rows
-//               after a's last row, whose records are loaded a few at a time
-//               and checked: z' window, then y carried along the helix
-//               (parameters only); pairs that pass are buffered per lane in
-//               LDS, and one atomic per wave reserves the list ranges of all
-//               its lanes at the end (an atomic per pair, or per lane, on the
-//               one counter would serialize them; a full buffer is flushed
-//               by its lane alone);
+//               16-byte record each;
+//   k_mg_pairs  a wave takes 8 to 64 consecutive segments a (scan_unit): a
+//               lane each, their outer states are turned into the frame of
+//               every unit on their side within max_dalpha (parameters, FP64)
+//               and the segments starting 1 .. max_gap rows after a's last
+//               row are found in the cells a's z' window meets; then, one
+//               segment after the other, the wave reads its candidates'
+//               records 64 at a time and passes over those that fail the z'
+//               or the y window by more than FP32 can err; what is left gets
+//               the exact test, z' window and y carried along the helix in
+//               FP64, a lane each; pairs that pass are buffered in LDS, and
+//               one atomic per block reserves their list ranges;
 //   k_mg_chi2   one lane per pair: the turn with its Jacobian, the helix
 //               transport with its Jacobian, both covariances summed, chi2
 //               by Cholesky (FP64); candidates take the least chi2 per
@@ -50,7 +49,6 @@ namespace {
 constexpr int TPB = 256;
 constexpr int SCAN_T = 1024;
 constexpr int SORT_MAX = 1024;  // bins sorted in LDS up to this size
-constexpr int PAIR_BUF = 16;   // pairs a lane of the scan buffers in LDS before it reserves list space
 constexpr int MAX_BLOCKS = 4096;
 constexpr double KAPPA = 0.00299792458;
 constexpr double TWO_PI = 6.283185307179586476925286766559;
@@ -95,21 +93,20 @@ struct MgArgs {
   // outputs
   int32_t *next, *prev;
   double *link_chi2;
-  int64_t *counts;
   int32_t *status;
   // workspace
   int32_t *bin;  // [nbins + 1] counts, then offsets
-  int32_t *cursor;
+  int32_t *rank;  // place of each filed segment in its cell
   int32_t *idx;
   Filed *filed;   // the filed segments, in scan order
   Inner *inner;   // their inner states, in the same order
-  int32_t *frs;    // their first rows, in filing order (the sort's key)
+  int32_t *frs;    // their first rows, in filing order (the sort's key), then in scan order
   int32_t *rows;  // first row | last row << 16
   unsigned long long *ob_chi, *ib_chi;
   int32_t *ob_idx, *ib_idx;
   int2 *pairs;
   double *pair_chi;
-  unsigned long long *ctr;  // pairs, candidates, links
+  unsigned long long *ctr;  // pairs, candidates, links (the output counts)
 };
 
 __device__ __forceinline__ int64_t n_tracks(const MgArgs &A) {
@@ -139,10 +136,10 @@ __device__ double asin_over_d(double u) {
 // new state at the new plane against the old one (a shift of the track along
 // the old y, taken back to the new plane along the track; a turn of the
 // direction).  False when the direction reaches |sin| >= smx or cos <= 0.
-__device__ __forceinline__ bool turn(const double p[5], double x, double d, double k, double smx, double q[5], double &xq,
-                     double *J) {
+// cd, sd: cosine and sine of the turn.
+__device__ __forceinline__ bool turn(const double p[5], double x, double cd, double sd, double k, double smx, double q[5],
+                                     double &xq, double *J) {
 #pragma clang fp contract(off)
-  const double cd = cos(d), sd = sin(d);
   const double s = p[2];
   if (!(fabs(s) < 1.0)) return false;
   const double c = sqrt(1.0 - s * s);
@@ -340,36 +337,52 @@ __global__ void __launch_bounds__(TPB) k_mg_rows(MgArgs A) {
       continue;
     }
     A.rows[t] = fr | (lr << 16);
-    if (A.ok[t] && fr > 0) atomicAdd(&A.bin[u * A.nzc + zcell(A, double(A.p_in[t * 5 + 1]))], 1);
+    // the rank in the cell is the segment's place there: k_mg_fill needs no second counter
+    // (6 us against 32 with an atomic there too)
+    if (A.ok[t] && fr > 0) A.rank[t] = atomicAdd(&A.bin[u * A.nzc + zcell(A, double(A.p_in[t * 5 + 1]))], 1);
   }
   if (bad) *A.status = TPC_E_INVALID;
 }
 
-// exclusive scan of the bin counts (one block), and the fill cursors
+// exclusive scan of the bin counts (one block): each thread takes PER
+// consecutive counts, so one block scan covers 1024 * PER of them (9.3 k
+// counts: 7 us; with one count a thread and turn 20)
 __global__ void __launch_bounds__(SCAN_T) k_mg_scan(MgArgs A) {
-  __shared__ int32_t s[SCAN_T];
-  __shared__ int32_t carry_in;
+  constexpr int PER = 12;
+  __shared__ int32_t wsum[2][SCAN_T / 64];
   if (*A.status != TPC_OK) return;
   const int64_t nb = int64_t(A.n_units) * A.nzc;
-  if (threadIdx.x == 0) carry_in = 0;
-  __syncthreads();
-  for (int64_t b0 = 0; b0 <= nb; b0 += SCAN_T) {
-    const int64_t b = b0 + threadIdx.x;
-    const int v = b < nb ? A.bin[b] : 0;
-    s[threadIdx.x] = v;
-    __syncthreads();
-    for (int d = 1; d < SCAN_T; d <<= 1) {
-      const int a = threadIdx.x >= d ? s[threadIdx.x - d] : 0;
-      __syncthreads();
-      s[threadIdx.x] += a;
-      __syncthreads();
+  const int lane = __lane_id(), wave = threadIdx.x >> 6;
+  int32_t carry = 0;
+  int flip = 0;
+  for (int64_t b0 = 0; b0 <= nb; b0 += SCAN_T * PER, flip ^= 1) {
+    const int64_t i0 = b0 + int64_t(threadIdx.x) * PER;
+    int32_t v[PER], sum = 0;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      v[e] = i0 + e < nb ? A.bin[i0 + e] : 0;
+      sum += v[e];
     }
-    const int ex = carry_in + s[threadIdx.x] - v;
-    if (b <= nb) A.bin[b] = ex;
-    if (b < nb) A.cursor[b] = ex;
+    int32_t inc = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int32_t x = __shfl_up(inc, o, 64);
+      if (lane >= o) inc += x;
+    }
+    if (lane == 63) wsum[flip][wave] = inc;
     __syncthreads();
-    if (threadIdx.x == SCAN_T - 1) carry_in += s[SCAN_T - 1];
-    __syncthreads();
+    int32_t ex = carry + inc - sum;
+#pragma unroll
+    for (int w = 0; w < SCAN_T / 64; ++w) {
+      const int32_t t = wsum[flip][w];
+      ex += w < wave ? t : 0;
+      carry += t;
+    }
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      if (i0 + e <= nb) A.bin[i0 + e] = ex;
+      ex += v[e];
+    }
   }
 }
 
@@ -379,7 +392,7 @@ __global__ void __launch_bounds__(TPB) k_mg_fill(MgArgs A) {
   for (int64_t t = int64_t(blockIdx.x) * TPB + threadIdx.x; t < T; t += int64_t(gridDim.x) * TPB) {
     const int fr = A.rows[t] & 0xFFFF;
     if (!A.ok[t] || fr == 0) continue;
-    const int pos = atomicAdd(&A.cursor[A.unit[t] * A.nzc + zcell(A, double(A.p_in[t * 5 + 1]))], 1);
+    const int pos = A.bin[A.unit[t] * A.nzc + zcell(A, double(A.p_in[t * 5 + 1]))] + A.rank[t];
     A.idx[pos] = int32_t(t);
     A.frs[pos] = fr;
   }
@@ -458,113 +471,281 @@ __global__ void __launch_bounds__(64) k_mg_sort(MgArgs A) {
         }
         __syncthreads();
       }
-    for (int i = threadIdx.x; i < n; i += 64)
+    for (int i = threadIdx.x; i < n; i += 64) {
       file_entry(A, s0 + i, int32_t(uint32_t(key[i])), int32_t(key[i] >> 32));
+      A.frs[s0 + i] = int32_t(key[i] >> 32);
+    }
     __syncthreads();
   }
 }
 
-// The lane's buffered pairs (a, buf[0 .. n)) written to the list at a
-// reserved range (one atomic per flush; past cap_pairs they are only counted).
-__device__ __forceinline__ void flush(const MgArgs &A, int32_t a, const int32_t *buf, int n) {
-  if (n == 0) return;
-  const unsigned long long base = atomicAdd(&A.ctr[0], (unsigned long long)n);
-  for (int i = 0; i < n; ++i)
-    if (base + i < (unsigned long long)A.cap_pairs) A.pairs[base + i] = make_int2(a, buf[i * TPB]);
+constexpr int WAVES = TPB / 64;
+constexpr int CELLS = 3;       // z' cells a window meets at most (cells are at least dz_max wide)
+constexpr int NEAR_BUF = 128;  // candidates a wave keeps for the exact test, which takes 64 at a time
+constexpr int PAIR_BUF = 512;  // pairs a wave keeps before it reserves list space
+constexpr int SEGS_MIN = 8, SEGS_MAX = 64;  // segments a wave of the scan takes
+
+// a wave's part of the scan's LDS
+struct WaveScan {
+  double y[64], x[64], s[64], q[64];  // its segments' outer states in the unit at hand, for the exact test
+  float z[64];
+  int32_t near[NEAR_BUF], pair[PAIR_BUF];            // filed slots ...
+  uint8_t near_seg[NEAR_BUF], pair_seg[PAIR_BUF];  // ... and the segments (lanes) they are candidates of
+};
+
+// what one lane wrote to its wave's LDS is there for the others
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+__device__ __forceinline__ int lanes_below(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0));
+}
+__device__ __forceinline__ int32_t lane_int(int32_t v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
+__device__ __forceinline__ float lane_float(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+__device__ __forceinline__ double lane_double(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane(int(b), lane), hi = __builtin_amdgcn_readlane(int(b >> 32), lane);
+  return __longlong_as_double((long long)((unsigned long long)unsigned(hi) << 32 | unsigned(lo)));
 }
 
-// first position in [lo, hi) of a cell (sorted by first row) whose first row is above r
-__device__ __forceinline__ int32_t after_row(const MgArgs &A, int32_t lo, int32_t hi, int r) {
-  while (lo < hi) {
-    const int32_t mid = (lo + hi) >> 1;
-    if (A.filed[mid].fr <= r) lo = mid + 1; else hi = mid;
+// n buffered pairs of the wave whose first segment is a0, written to the list
+// from base on (past cap_pairs they are only counted)
+__device__ __forceinline__ void write_pairs(const MgArgs &A, const WaveScan &L, int64_t a0, int n, unsigned long long base) {
+  for (int i = __lane_id(); i < n; i += 64)
+    if (base + i < (unsigned long long)A.cap_pairs) A.pairs[base + i] = make_int2(int32_t(a0) + L.pair_seg[i], L.pair[i]);
+}
+
+// A segment's outer state in one unit's frame, rounded for the first look at
+// its candidates.
+struct Reach {
+  float z, y, x, s, c, C;
+  int32_t plain;  // the first look's bound holds (|sin(phi)| well below 1)
+
+  // Whether the record cannot pass the z' and y windows: their test in FP32,
+  // with margins above its error.  x and y up to 8192 cm round by 5e-4 cm, z'
+  // differences by as much; for |C| < 0.05 / cm that puts sin(phi) off by less
+  // than 3e-5 and, where it is below 0.96 at both ends (tan < 3.5), the
+  // carried y by less than 3e-3 cm and 6e-4 dx.  Anything else, NaN too, is
+  // left to the exact test.  (Most segments of low-pT particles end where
+  // they turn back: the transport fails for most of their candidates.)
+  __device__ __forceinline__ bool misses(const Filed &f, float dz, float dy, float smx) const {
+    const float dx = f.x - x, s2 = s + C * dx;
+    const float c2 = __builtin_amdgcn_sqrtf(fmaxf(0.f, 1.f - s2 * s2));
+    const float off = f.y - y - dx * (s + s2) * __builtin_amdgcn_rcpf(c + c2);
+    return fabsf(f.z - z) > dz ||
+           (plain && (fabsf(s2) > smx || (fabsf(s2) < 0.96f && fabsf(off) > dy + 1e-3f * fabsf(dx))));
   }
-  return lo;
+};
+
+// The exact test of the wave's kept candidates first .. first + 63 (those
+// below n), a lane each; those that pass go to the wave's pairs.
+__device__ __forceinline__ void settle(const MgArgs &A, WaveScan &L, int64_t a0, int first, int n, int &n_pair) {
+  const int lane = __lane_id();
+  wave_sync();
+  int32_t s = 0;
+  int seg = 0;
+  bool pass = false;
+  if (first + lane < n) {
+    s = L.near[first + lane];
+    seg = L.near_seg[first + lane];
+    const Filed f = A.filed[s];
+    const double p[5] = {L.y[seg], 0.0, L.s[seg], 0.0, L.q[seg]};
+    double y;
+    pass = fabs(double(f.z) - double(L.z[seg])) <= A.dz_max && carry_y(p, L.x[seg], double(f.x), A.k, A.smx, y) &&
+           fabs(double(f.y) - y) <= A.dy_max;
+  }
+  const uint64_t m = __ballot(pass);
+  const int more = __popcll(m);
+  if (n_pair + more > PAIR_BUF) {
+    unsigned long long base = 0;
+    if (lane == 0) base = atomicAdd(&A.ctr[0], (unsigned long long)n_pair);
+    write_pairs(A, L, a0, n_pair, __shfl(base, 0, 64));
+    wave_sync();
+    n_pair = 0;
+  }
+  if (pass) {
+    const int i = n_pair + lanes_below(m);
+    L.pair[i] = s;  // the filed slot; k_mg_chi2 puts the track index in its place
+    L.pair_seg[i] = uint8_t(seg);
+  }
+  n_pair += more;
+  wave_sync();
 }
 
-constexpr int SCAN_B = 4;  // candidate records loaded together
-
-// The candidates of segment a (refitted, its last row below the last row):
-// pairs into the lane's buffer, a full buffer flushed on its own.
-__device__ __forceinline__ void scan_segment(const MgArgs &A, int64_t a, int lr, int32_t *buf, int &nbuf) {
-  const int ua = A.unit[a];
+// The candidates, in unit w, of the segments of the lanes with `mine` (a0 is
+// lane 0's): each such lane turns its outer state (pa, xa) into the unit's
+// frame by an angle of cosine cd and sine sd (same: it is its own unit) and
+// finds the ranges of the records to check; then the wave takes the segments
+// one after the other, 64 records at a time.
+__device__ __forceinline__ void scan_unit(const MgArgs &A, WaveScan &L, int64_t a0, bool mine, int lr, const double pa[5],
+                                          double xa, int w, bool same, double cd, double sd, int &n_pair) {
+  const int lane = __lane_id();
   const int r1 = min(lr + A.max_gap, A.n_rows - 1);
-  double pa[5];
-  for (int i = 0; i < 5; ++i) pa[i] = double(A.p_out[a * 5 + i]);
-  const double xa = double(A.x_out[a]);
   const double za = pa[1];
-  for (int w = 0; w < A.n_units; ++w) {
-    if (A.side[w] != A.side[ua]) continue;
-    const double d = turn_angle(A, ua, w);
-    if (!(fabs(d) <= A.max_dalpha)) continue;
+  Reach r = {};
+  if (mine) {
     double q[5], xq = xa;
-    if (w == ua) {
+    if (same) {
       for (int i = 0; i < 5; ++i) q[i] = pa[i];
-    } else if (!turn(pa, xa, d, A.k, A.smx, q, xq, nullptr)) {
-      continue;
+    } else {
+      mine = turn(pa, xa, cd, sd, A.k, A.smx, q, xq, nullptr);
     }
-    const int c0 = zcell(A, za - A.dz_max), c1 = zcell(A, za + A.dz_max);
-    for (int cz = c0; cz <= c1; ++cz) {
-      const int32_t s0 = A.bin[w * A.nzc + cz], s1 = A.bin[w * A.nzc + cz + 1];
-      if (s0 == s1) continue;
-      // the cell is sorted by first row: the segments starting in rows lr+1 .. r1,
-      // their records loaded SCAN_B at a time (the range is known, so no load
-      // waits on the one before)
-      const int32_t lo = after_row(A, s0, s1, lr), hi = after_row(A, lo, s1, r1);
-      for (int32_t s = lo; s < hi; s += SCAN_B) {
-        Filed f[SCAN_B];
+    if (mine) {
+      L.y[lane] = q[0];
+      L.x[lane] = xq;
+      L.s[lane] = q[2];
+      L.q[lane] = q[4];
+      L.z[lane] = float(za);  // exact: it came as a float
+      r.z = float(za);
+      r.y = float(q[0]);
+      r.x = float(xq);
+      r.s = float(q[2]);
+      r.C = float(A.k * q[4]);
+      r.c = __builtin_amdgcn_sqrtf(fmaxf(0.f, 1.f - r.s * r.s));
+      r.plain = fabsf(r.s) < 0.96f && fabsf(r.C) < 0.05f;
+    }
+  }
+  const float dz = float(A.dz_max) * 1.000001f + 2e-3f, dy = float(A.dy_max) * 1.000001f + 6e-3f, smx = float(A.smx) + 1e-4f;
+  const int c0 = zcell(A, za - A.dz_max), c1 = zcell(A, za + A.dz_max);
+  int n_near = 0;
+  for (int cb = c0; __ballot(mine && cb <= c1); cb += CELLS) {  // once, but for a rounded cell width
+    // Each cell is sorted by first row.  The bounds of the segments starting in
+    // rows lr+1 .. r1 are searched for in all of them together (six searches,
+    // one load each per step).
+    int32_t lo[CELLS], hi[CELLS], le[CELLS], he[CELLS], span = 0;
 #pragma unroll
-        for (int e = 0; e < SCAN_B; ++e)
-          if (s + e < hi) f[e] = A.filed[s + e];
+    for (int c = 0; c < CELLS; ++c) {
+      const bool on = mine && cb + c <= c1;
+      const int64_t cell = int64_t(w) * A.nzc + (on ? cb + c : 0);
+      const int32_t s0 = A.bin[cell], s1 = on ? A.bin[cell + 1] : s0;
+      lo[c] = hi[c] = s0;  // [lo, le): the first row above lr is sought in it; [hi, he): the first above r1
+      le[c] = he[c] = s1;
+      span = max(span, s1 - s0);
+    }
+    for (; span > 0; span >>= 1) {
 #pragma unroll
-        for (int e = 0; e < SCAN_B; ++e) {
-          if (s + e >= hi) break;
-          double y;
-          if (!(fabs(double(f[e].z) - za) <= A.dz_max) || !carry_y(q, xq, double(f[e].x), A.k, A.smx, y) ||
-              !(fabs(double(f[e].y) - y) <= A.dy_max))
-            continue;
-          if (nbuf == PAIR_BUF) {
-            flush(A, int32_t(a), buf, nbuf);
-            nbuf = 0;
-          }
-          buf[nbuf++ * TPB] = s + e;  // the filed slot; k_mg_chi2 puts the track index in its place
+      for (int c = 0; c < CELLS; ++c) {
+        const int32_t m = (lo[c] + le[c]) >> 1, n = (hi[c] + he[c]) >> 1;
+        const bool vm = lo[c] < le[c], vn = hi[c] < he[c];
+        const int32_t fm = vm ? A.frs[m] : 0, fn = vn ? A.frs[n] : 0;
+        if (vm) {
+          if (fm <= lr) lo[c] = m + 1; else le[c] = m;
         }
+        if (vn) {
+          if (fn <= r1) hi[c] = n + 1; else he[c] = n;
+        }
+      }
+    }
+    // their records as one list: record t is filed in slot t + a0_, a1 or a2
+    const int32_t e0 = hi[0] - lo[0], e1 = e0 + hi[1] - lo[1], tot = e1 + hi[2] - lo[2];
+    const int32_t b0 = lo[0], b1 = lo[1] - e0, b2 = lo[2] - e1;
+    for (uint64_t todo = __ballot(tot > 0); todo; todo &= todo - 1) {
+      const int i = __ffsll((unsigned long long)todo) - 1;
+      const Reach u = {lane_float(r.z, i), lane_float(r.y, i), lane_float(r.x, i), lane_float(r.s, i),
+                       lane_float(r.c, i), lane_float(r.C, i), lane_int(r.plain, i)};
+      const int32_t n = lane_int(tot, i), n0 = lane_int(e0, i), n1 = lane_int(e1, i);
+      const int32_t s0 = lane_int(b0, i), s1 = lane_int(b1, i), s2 = lane_int(b2, i);
+      for (int32_t t0 = 0; t0 < n; t0 += 64) {
+        const int32_t t = min(t0 + lane, n - 1), s = t + (t < n0 ? s0 : t < n1 ? s1 : s2);
+        const bool keep = !u.misses(A.filed[s], dz, dy, smx) && t0 + lane < n;
+        const uint64_t m = __ballot(keep);
+        if (keep) {
+          const int k = n_near + lanes_below(m);
+          L.near[k] = s;
+          L.near_seg[k] = uint8_t(i);
+        }
+        n_near += __popcll(m);
+        if (n_near >= 64) {
+          n_near -= 64;
+          settle(A, L, a0, n_near, n_near + 64, n_pair);
+        }
+      }
+    }
+  }
+  if (n_near) settle(A, L, a0, 0, n_near, n_pair);
+}
+
+// The candidates of a wave's segments (a lane each; on: those that look for
+// any).  The units that one of the lanes' units may continue in are found by
+// the wave's lanes together, a unit each with its angle, cosine and sine: the
+// FP64 remainder and the sincos are then paid once for a wave whose segments
+// share their unit, and nearly all waves do.
+__device__ __forceinline__ void scan_wave(const MgArgs &A, WaveScan &L, int64_t a0, bool on, int lr, int &n_pair) {
+  const int lane = __lane_id();
+  double pa[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, xa = 0.0;
+  int ua = -1;
+  if (on) {
+    ua = A.unit[a0 + lane];
+    for (int i = 0; i < 5; ++i) pa[i] = double(A.p_out[(a0 + lane) * 5 + i]);
+    xa = double(A.x_out[a0 + lane]);
+  }
+  uint64_t todo = __ballot(on);
+  while (todo) {
+    const int u = lane_int(ua, __ffsll((unsigned long long)todo) - 1);
+    const bool mine = on && ua == u;
+    todo &= ~__ballot(mine);
+    const int side = A.side[u];
+    for (int w0 = 0; w0 < A.n_units; w0 += 64) {
+      const int w = w0 + lane;
+      double cd = 1.0, sd = 0.0;
+      bool reach = false;
+      if (w < A.n_units && A.side[w] == side) {
+        const double d = turn_angle(A, u, w);
+        reach = fabs(d) <= A.max_dalpha;
+        if (reach) {
+          cd = cos(d);
+          sd = sin(d);
+        }
+      }
+      for (uint64_t m = __ballot(reach); m; m &= m - 1) {
+        const int k = __ffsll((unsigned long long)m) - 1;
+        scan_unit(A, L, a0, mine, lr, pa, xa, w0 + k, w0 + k == u, lane_double(cd, k), lane_double(sd, k), n_pair);
       }
     }
   }
 }
 
-__global__ void __launch_bounds__(TPB) k_mg_pairs(MgArgs A) {
-  // each lane's pair buffer: a column of a [PAIR_BUF][TPB] block (lanes side by side)
-  __shared__ int32_t pbuf[PAIR_BUF * TPB];
-  int32_t *buf = pbuf + threadIdx.x;
+// What bounds it: FP32 issue (95 M wave instructions for 237 k segments that
+// look on and 56 M records: 0.6 of the time) and the records' latency, which
+// six waves a SIMD cover most of.  265 us; 667 with a lane per segment that
+// tested each of its candidates in FP64: 64 lanes then read 64 far records
+// with every load.
+__global__ void __launch_bounds__(TPB, 6) k_mg_pairs(MgArgs A) {
+  __shared__ WaveScan scans[WAVES];
+  __shared__ int32_t n_wave[WAVES];
+  __shared__ unsigned long long base;
   if (*A.status != TPC_OK) return;
   const int64_t T = n_tracks(A);
-  const int lane = __lane_id();
-  for (int64_t a0 = int64_t(blockIdx.x) * TPB; a0 < T; a0 += int64_t(gridDim.x) * TPB) {
-    const int64_t a = a0 + threadIdx.x;
-    if ((a & ~int64_t(63)) >= T) break;  // whole wave past the tracks (wave-uniform)
-    int nbuf = 0;
-    const int lr = a < T ? A.rows[a] >> 16 : 0;
-    if (a < T && A.ok[a] && lr + 1 < A.n_rows) scan_segment(A, a, lr, buf, nbuf);
-    // the lanes' buffered pairs: one atomic per wave reserves all their ranges
-    // (an atomic per lane on the one counter would serialize them)
-    int incl = nbuf;
+  const int lane = __lane_id(), wave = threadIdx.x >> 6;
+  WaveScan &L = scans[wave];
+  int64_t segs = SEGS_MIN;  // small batches are spread over the chip's waves
+  while (segs < SEGS_MAX && segs * WAVES * gridDim.x < T) segs *= 2;
+  for (int64_t b0 = blockIdx.x * segs * WAVES; b0 < T; b0 += gridDim.x * segs * WAVES) {  // block-uniform
+    const int64_t a0 = b0 + wave * segs, a = a0 + lane;
+    const bool in = lane < segs && a < T;
+    const int lr = in ? A.rows[a] >> 16 : 0;
+    int n_pair = 0;
+    scan_wave(A, L, a0, in && A.ok[a] && lr + 1 < A.n_rows, lr, n_pair);
+    // the block's buffered pairs: one atomic reserves all their ranges (an
+    // atomic per wave on the one counter would serialize them)
+    if (lane == 0) n_wave[wave] = n_pair;
+    __syncthreads();
+    int32_t before = 0, total = 0;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += y;
+    for (int w = 0; w < WAVES; ++w) {
+      before += w < wave ? n_wave[w] : 0;
+      total += n_wave[w];
     }
-    const int total = __shfl(incl, 63, 64);
-    long long base = 0;
-    if (lane == 63 && total) base = (long long)atomicAdd(&A.ctr[0], (unsigned long long)total);
-    base = __shfl(base, 63, 64);
-    const unsigned long long mine = (unsigned long long)base + (unsigned long long)(incl - nbuf);
-    for (int i = 0; i < nbuf; ++i)
-      if (mine + i < (unsigned long long)A.cap_pairs) A.pairs[mine + i] = make_int2(int32_t(a), buf[i * TPB]);
+    if (threadIdx.x == 0 && total) base = atomicAdd(&A.ctr[0], (unsigned long long)total);
+    __syncthreads();
+    if (total) write_pairs(A, L, a0, n_pair, base + (unsigned long long)before);
+    __syncthreads();
   }
 }
-
 
 __global__ void __launch_bounds__(TPB) k_mg_chi2(MgArgs A) {
   if (*A.status != TPC_OK) return;
@@ -588,8 +769,9 @@ __global__ void __launch_bounds__(TPB) k_mg_chi2(MgArgs A) {
     double chi = -1.0;
     bool ok = true;
     if (ua != ub) {
+      const double d = turn_angle(A, ua, ub);
       double J[25];
-      ok = turn(pa, double(A.x_out[a]), turn_angle(A, ua, ub), A.k, A.smx, q, xq, J);
+      ok = turn(pa, double(A.x_out[a]), cos(d), sin(d), A.k, A.smx, q, xq, J);
       if (ok) sandwich(J, C);
     } else {
       for (int j = 0; j < 5; ++j) q[j] = pa[j];
@@ -647,16 +829,10 @@ __global__ void __launch_bounds__(TPB) k_mg_link(MgArgs A) {
   block_count(A.ctr[2], n_link);
 }
 
-__global__ void k_mg_counts(MgArgs A) {
-  A.counts[0] = int64_t(A.ctr[0]);
-  A.counts[1] = int64_t(A.ctr[1]);
-  A.counts[2] = int64_t(A.ctr[2]);
-}
-
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
 struct Layout {
-  size_t bin, cursor, idx, filed, inner, frs, rows, ob_chi, ib_chi, ob_idx, ib_idx, pairs, pair_chi, ctr, total;
+  size_t bin, idx, filed, inner, frs, rows, ob_chi, ib_chi, ob_idx, ib_idx, pairs, pair_chi, total;
 };
 
 Layout layout(int64_t nbins, int64_t cap_tracks, int64_t cap_pairs) {
@@ -668,7 +844,6 @@ Layout layout(int64_t nbins, int64_t cap_tracks, int64_t cap_pairs) {
     return at;
   };
   L.bin = take(size_t(nbins + 1) * 4);
-  L.cursor = take(size_t(nbins) * 4);
   L.idx = take(size_t(cap_tracks) * 4);
   L.filed = take(size_t(cap_tracks) * sizeof(Filed));
   L.inner = take(size_t(cap_tracks) * sizeof(Inner));
@@ -680,7 +855,6 @@ Layout layout(int64_t nbins, int64_t cap_tracks, int64_t cap_pairs) {
   L.ib_idx = take(size_t(cap_tracks) * 4);
   L.pairs = take(size_t(cap_pairs) * 8);
   L.pair_chi = take(size_t(cap_pairs) * 8);
-  L.ctr = take(4 * 8);
   L.total = o;
   return L;
 }
@@ -773,7 +947,6 @@ extern "C" int tpc_merge_tracks(const tpc_clusters_t *clusters, const tpc_geomet
   A.next = out->next;
   A.prev = out->prev;
   A.link_chi2 = out->link_chi2;
-  A.counts = out->counts;
   A.status = out->status;
   const Cells cz = cells(params, n_units);
   A.nzc = cz.nzc;
@@ -783,7 +956,7 @@ extern "C" int tpc_merge_tracks(const tpc_clusters_t *clusters, const tpc_geomet
   const Layout L = layout(nb, tracks->cap_tracks, params->cap_pairs);
   char *w = static_cast<char *>(workspace);
   A.bin = reinterpret_cast<int32_t *>(w + L.bin);
-  A.cursor = reinterpret_cast<int32_t *>(w + L.cursor);
+  A.rank = reinterpret_cast<int32_t *>(w + L.inner);  // read by k_mg_fill, before k_mg_sort writes the records
   A.idx = reinterpret_cast<int32_t *>(w + L.idx);
   A.filed = reinterpret_cast<Filed *>(w + L.filed);
   A.inner = reinterpret_cast<Inner *>(w + L.inner);
@@ -795,7 +968,7 @@ extern "C" int tpc_merge_tracks(const tpc_clusters_t *clusters, const tpc_geomet
   A.ib_idx = reinterpret_cast<int32_t *>(w + L.ib_idx);
   A.pairs = reinterpret_cast<int2 *>(w + L.pairs);
   A.pair_chi = reinterpret_cast<double *>(w + L.pair_chi);
-  A.ctr = reinterpret_cast<unsigned long long *>(w + L.ctr);
+  A.ctr = reinterpret_cast<unsigned long long *>(out->counts);
   hipStream_t st = static_cast<hipStream_t>(stream);
   auto blocks = [](int64_t n) { return unsigned(n < TPB ? 1 : ((n + TPB - 1) / TPB > MAX_BLOCKS ? MAX_BLOCKS : (n + TPB - 1) / TPB)); };
   const int64_t T = tracks->cap_tracks;
@@ -804,10 +977,10 @@ extern "C" int tpc_merge_tracks(const tpc_clusters_t *clusters, const tpc_geomet
   hipLaunchKernelGGL(k_mg_scan, dim3(1), dim3(SCAN_T), 0, st, A);
   hipLaunchKernelGGL(k_mg_fill, dim3(blocks(T)), dim3(TPB), 0, st, A);
   hipLaunchKernelGGL(k_mg_sort, dim3(unsigned(nb < MAX_BLOCKS ? nb : MAX_BLOCKS)), dim3(64), 0, st, A);
-  hipLaunchKernelGGL(k_mg_pairs, dim3(blocks(T)), dim3(TPB), 0, st, A);
+  const int64_t scan_blocks = (T + SEGS_MIN * WAVES - 1) / (SEGS_MIN * WAVES);
+  hipLaunchKernelGGL(k_mg_pairs, dim3(unsigned(scan_blocks < 1 ? 1 : scan_blocks < MAX_BLOCKS ? scan_blocks : MAX_BLOCKS)), dim3(TPB), 0, st, A);
   hipLaunchKernelGGL(k_mg_chi2, dim3(blocks(params->cap_pairs)), dim3(TPB), 0, st, A);
   hipLaunchKernelGGL(k_mg_pick, dim3(blocks(params->cap_pairs)), dim3(TPB), 0, st, A);
   hipLaunchKernelGGL(k_mg_link, dim3(blocks(T)), dim3(TPB), 0, st, A);
-  hipLaunchKernelGGL(k_mg_counts, dim3(1), dim3(1), 0, st, A);
   return hipGetLastError() == hipSuccess ? TPC_OK : TPC_E_HIP;
 }
