@@ -583,155 +583,6 @@ __global__ void __launch_bounds__(TPB) k_tile_scatter(Args A) {
   }
 }
 
-__device__ __forceinline__ int bin_of(const int32_t *rec, int Y, int Z) {
-  const int H = rec[S_H];
-  const int iy = clampi(Y + H, 0, 2 * H) / rec[S_BY];
-  const int iz = (Z - rec[S_ZMIN]) / rec[S_BZ];
-  return iz * rec[S_NY] + iy;
-}
-
-// step 2f: per (unit,row), counting sort by bin, stable (hits arrive in id
-// order and one wave ranks them chunk by chunk with ballots), and the cell
-// table.  Fast path: bins and per-hit ranks in LDS, data moved by all threads
-// afterwards; rows too large for LDS take the same steps with global cursors.
-constexpr int BIN_POOL = 12288;  // LDS ints shared by the bin counters and the per-hit slots
-constexpr int KREG = 24;         // hits per thread kept in registers by the bin sort (rows <= 6144)
-
-__device__ __forceinline__ void scan_bins(int *hist, int nbins, int32_t *cell_out, int start, int *tmp) {
-  const int per = (nbins + TPB - 1) / TPB;
-  const int b0 = min(nbins, int(threadIdx.x) * per), b1 = min(nbins, b0 + per);
-  int run = 0;
-  for (int b = b0; b < b1; ++b) run += hist[b];
-  int tot;
-  int pre = block_exclusive_scan<TPB>(run, tmp, &tot);
-  for (int b = b0; b < b1; ++b) {
-    const int v = hist[b];
-    hist[b] = pre;
-    cell_out[b] = start + pre;
-    pre += v;
-  }
-}
-
-__global__ void __launch_bounds__(TPB) k_bin_sort(Args A) {
-  __shared__ int pool[BIN_POOL];
-  __shared__ int tmp[4];
-  const Workspace &w = A.w;
-  if (*A.out.status != TPC_OK) return;
-  const int64_t s = blockIdx.x;
-  const int32_t *rec = w.seg + s * SEGW;
-  const int start = rec[S_START], count = rec[S_COUNT], cbase = rec[S_CBASE];
-  const int nbins = rec[S_NY] * rec[S_NZ];
-  int nbits = 1;
-  while ((1 << nbits) < nbins) ++nbits;
-  const int lane = __lane_id();
-  if (nbins + count <= BIN_POOL) {
-    int *hist_lds = pool, *slot = pool + nbins;
-    for (int b = threadIdx.x; b < nbins; b += TPB) hist_lds[b] = 0;
-    // the thread's first KREG hits stay in registers from here to the scatter
-    int2 ryz[KREG];
-    int rid[KREG];
-#pragma unroll
-    for (int k = 0; k < KREG; ++k) {
-      const int p = int(threadIdx.x) + k * TPB;
-      if (p < count) {
-        ryz[k] = w.rs_yz[start + p];
-        rid[k] = w.rs_idx[start + p];
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < KREG; ++k) {
-      const int p = int(threadIdx.x) + k * TPB;
-      if (p < count) {
-        const int bn = bin_of(rec, ryz[k].x, ryz[k].y);
-        slot[p] = bn;
-        atomicAdd(&hist_lds[bn], 1);
-      }
-    }
-    for (int p = int(threadIdx.x) + KREG * TPB; p < count; p += TPB) {
-      const int2 yz = w.rs_yz[start + p];
-      const int bn = bin_of(rec, yz.x, yz.y);
-      slot[p] = bn;
-      atomicAdd(&hist_lds[bn], 1);
-    }
-    __syncthreads();
-    scan_bins(hist_lds, nbins, w.cell + cbase, start, tmp);
-    __syncthreads();
-    if (threadIdx.x < 64) {  // stable ranks, one wave, chunk by chunk; the next chunk's bins load early
-      int nb = lane < count ? slot[lane] : 0;
-      for (int c = 0; c < count; c += 64) {
-        const int p = c + lane;
-        const bool act = p < count;
-        const int bn = nb;
-        nb = p + 64 < count ? slot[p + 64] : 0;
-        const uint64_t peers = peer_mask(uint32_t(bn), nbits, act);
-        const int lp = act ? hist_lds[bn] + __popcll(peers & lanemask_lt()) : 0;
-        __builtin_amdgcn_wave_barrier();
-        if (act && (63 - __clzll(peers)) == lane) hist_lds[bn] += __popcll(peers);
-        if (act) slot[p] = lp;
-        __builtin_amdgcn_wave_barrier();
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < KREG; ++k) {
-      const int p = int(threadIdx.x) + k * TPB;
-      if (p < count) {
-        const int lp = slot[p];
-        w.perm[start + lp] = rid[k];
-        w.syz[start + lp] = ryz[k];
-      }
-    }
-    for (int p = int(threadIdx.x) + KREG * TPB; p < count; p += TPB) {
-      const int lp = slot[p];
-      w.perm[start + lp] = w.rs_idx[start + p];
-      w.syz[start + lp] = w.rs_yz[start + p];
-    }
-    return;
-  }
-  // large rows: cursors in the workspace
-  int *hist = w.cursor + cbase;
-  for (int b = threadIdx.x; b < nbins; b += TPB) hist[b] = 0;
-  __syncthreads();
-  for (int p = threadIdx.x; p < count; p += TPB) {
-    const int2 yz = w.rs_yz[start + p];
-    atomicAdd(&hist[bin_of(rec, yz.x, yz.y)], 1);
-  }
-  __syncthreads();
-  scan_bins(hist, nbins, w.cell + cbase, start, tmp);
-  __syncthreads();
-  if (threadIdx.x >= 64) return;
-  for (int c = 0; c < count; c += 64) {
-    const int p = c + lane;
-    const bool act = p < count;
-    int2 yz = make_int2(0, 0);
-    int idx = 0, bn = 0;
-    if (act) {
-      yz = w.rs_yz[start + p];
-      idx = w.rs_idx[start + p];
-      bn = bin_of(rec, yz.x, yz.y);
-    }
-    const uint64_t peers = peer_mask(uint32_t(bn), nbits, act);
-    int pos = 0;
-    if (act) pos = start + hist[bn] + __popcll(peers & lanemask_lt());
-    __builtin_amdgcn_wave_barrier();
-    if (act && (63 - __clzll(peers)) == lane) hist[bn] += __popcll(peers);
-    __builtin_amdgcn_wave_barrier();
-    if (act) {
-      w.perm[pos] = idx;
-      w.syz[pos] = yz;
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// step 3: neighbour finder.  For hit m of row i (0 < i < n_rows-1): candidates
-// n of rows j = i-1, i+1 with |Y_n X_i - Y_m X_j| <= win_y X_i (origin-pointing
-// in the bending plane) and |Z_n - Z_m| <= win_z (no vertex pointing in z).  Of
-// all pairs (d below, u above), the least (score, id_d, id_u) with
-// score = w_y R_y^2 + w_z R_z^2, R = (V_d - V_m)(X_u - X_i) + (V_u - V_m)(X_i - X_d),
-// is kept when score <= smax_k (X_{i+1} - X_{i-1})^2.
-
 // a / b for 0 <= a < 2^24 and 0 < b < 2^24: a float quotient is within one
 // of the result, then corrected with integer products.
 __device__ __forceinline__ int div_small(int a, int b, float inv_b) {
@@ -740,6 +591,280 @@ __device__ __forceinline__ int div_small(int a, int b, float inv_b) {
   else if ((q + 1) * b <= a) ++q;
   return q;
 }
+
+// a (unit,row) as the bin sort sees it
+struct BinGrid {
+  int start, count, cbase, nbins;
+  int H, by, ny, zmin, bz;
+  float2 inv;
+  __device__ __forceinline__ BinGrid(const Workspace &w, int64_t s) {
+    const int32_t *rec = w.seg + s * SEGW;
+    start = rec[S_START], count = rec[S_COUNT], cbase = rec[S_CBASE], nbins = rec[S_NY] * rec[S_NZ];
+    H = rec[S_H], by = rec[S_BY], ny = rec[S_NY], zmin = rec[S_ZMIN], bz = rec[S_BZ];
+    inv = w.seg_inv[s];
+  }
+  // quotients up to 62 in y; in z of less than 2^23 by at least 1
+  __device__ __forceinline__ int bin(int2 yz) const {
+    return div_small(yz.y - zmin, bz, inv.y) * ny + div_small(clampi(yz.x + H, 0, 2 * H), by, inv.x);
+  }
+};
+
+// step 2f: per (unit,row), counting sort by bin, stable (ties keep the order
+// of the ids), and the cell table.  A group of NT threads (a wave or a block)
+// takes a (unit,row) whose bin counters and hits fit its LDS pool: each hit's
+// turn within its bin comes from the counting atomic, its rank there from the
+// (few) hits of the bin with smaller numbers; y, z and ids then change places
+// in LDS and go out in whole lines.  Where a bin holds so many hits that this
+// would cost more, or the hits are more than NT * KR, one wave ranks them
+// with ballots, 64 at a time.  Rows past the pool take global cursors.
+//   Measured (50 collisions, 4.6 k hits a row; 512 chunks, 80 a row): the
+// scatter straight to memory cost a write request per hit and array, which
+// bounded the first, and four waves of which one ranked the second: 705 and
+// 407 us, now 372 and 126.
+constexpr int BIN_POOL = 12288;      // LDS ints of a block that sorts one (unit,row)
+constexpr int BIN_POOL_WAVE = 1024;  // LDS ints of a wave that sorts one by itself
+
+template <int NT>
+__device__ __forceinline__ void group_sync() {
+  if constexpr (NT > 64) {
+    __syncthreads();
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+}
+template <int NT>
+__device__ __forceinline__ int group_exclusive_scan(int v, int *tmp) {
+  int tot;
+  if constexpr (NT > 64) return block_exclusive_scan<NT>(v, tmp, &tot);
+  int x = v;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int y = __shfl_up(x, d);
+    if (int(__lane_id()) >= d) x += y;
+  }
+  return x - v;
+}
+
+// Counts to offsets, in hist and in the cell table; returns the largest count
+// among the thread's bins.
+template <int NT>
+__device__ __forceinline__ int scan_bins(int *hist, int nbins, int32_t *cell_out, int start, int tid, int *tmp) {
+  const int per = (nbins + NT - 1) / NT;
+  const int b0 = min(nbins, tid * per), b1 = min(nbins, b0 + per);
+  int run = 0, most = 0;
+  for (int b = b0; b < b1; ++b) {
+    run += hist[b];
+    most = max(most, hist[b]);
+  }
+  int pre = group_exclusive_scan<NT>(run, tmp);
+  for (int b = b0; b < b1; ++b) {
+    const int v = hist[b];
+    hist[b] = pre;
+    pre += v;
+  }
+  group_sync<NT>();
+  for (int b = tid; b < nbins; b += NT) cell_out[b] = start + hist[b];
+  return most;
+}
+
+// pool: nbins + 1 counters, then a slot per hit
+template <int NT, int KR>
+__device__ __forceinline__ void bin_sort_lds(const Workspace &w, const BinGrid &g, int tid, int *pool, int *tmp) {
+  int *hist = pool, *slot = pool + g.nbins + 1;
+  for (int b = tid; b < g.nbins; b += NT) hist[b] = 0;
+  if (tid == 0) hist[g.nbins] = g.count;
+  const int n = min(g.count, NT * KR);
+  int y[KR], z[KR], id[KR], at[KR];  // the thread's hits tid + k NT; at: bin and turn, then place
+#pragma unroll
+  for (int k = 0; k < KR; ++k) {
+    const int p = tid + k * NT;
+    if (p < n) {
+      const int2 yz = w.rs_yz[g.start + p];
+      y[k] = yz.x;
+      z[k] = yz.y;
+      id[k] = w.rs_idx[g.start + p];
+    }
+  }
+  group_sync<NT>();
+#pragma unroll
+  for (int k = 0; k < KR; ++k) {
+    if (tid + k * NT < n) {
+      const int bn = g.bin(make_int2(y[k], z[k]));
+      at[k] = bn | atomicAdd(&hist[bn], 1) << 14;
+    }
+  }
+  for (int p = tid + KR * NT; p < g.count; p += NT) atomicAdd(&hist[g.bin(w.rs_yz[g.start + p])], 1);
+  group_sync<NT>();
+  const int most = scan_bins<NT>(hist, g.nbins, w.cell + g.cbase, g.start, tid, tmp);
+  // a hit looks at its bin's others one after the other; a wave ranks 64 hits
+  // with about as much work as 16 looks, but alone and in turn
+  bool turns;
+  if constexpr (NT > 64) turns = __syncthreads_or(most > 16 + g.count / 16 || g.count > n);
+  else turns = __ballot(most > 16 + g.count / 16 || g.count > n) != 0;
+  if (!turns) {
+#pragma unroll
+    for (int k = 0; k < KR; ++k)
+      if (tid + k * NT < n) slot[hist[at[k] & 0x3FFF] + (at[k] >> 14)] = tid + k * NT;
+    group_sync<NT>();
+#pragma unroll
+    for (int k = 0; k < KR; ++k) {
+      const int p = tid + k * NT;
+      if (p < n) {
+        const int bn = at[k] & 0x3FFF, lo = hist[bn], hi = hist[bn + 1];
+        int rank = 0;
+        for (int q = lo; q < hi; ++q) rank += slot[q] < p;
+        at[k] = lo + rank;
+      }
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < KR; ++k)
+      if (tid + k * NT < n) slot[tid + k * NT] = at[k] & 0x3FFF;
+    for (int p = tid + KR * NT; p < g.count; p += NT) slot[p] = g.bin(w.rs_yz[g.start + p]);
+    int nbits = 1;
+    while ((1 << nbits) < g.nbins) ++nbits;
+    group_sync<NT>();
+    if (tid < 64) {  // the next chunk's bins load early
+      int nb = tid < g.count ? slot[tid] : 0;
+      for (int c = 0; c < g.count; c += 64) {
+        const int p = c + tid;
+        const bool act = p < g.count;
+        const int bn = nb;
+        nb = p + 64 < g.count ? slot[p + 64] : 0;
+        const uint64_t peers = peer_mask(uint32_t(bn), nbits, act);
+        const int lp = act ? hist[bn] + __popcll(peers & lanemask_lt()) : 0;
+        __builtin_amdgcn_wave_barrier();
+        if (act && (63 - __clzll(peers)) == tid) hist[bn] += __popcll(peers);
+        if (act) slot[p] = lp;
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+    group_sync<NT>();
+    if (g.count > n) {  // too many to change places: straight to memory
+      for (int p = tid; p < g.count; p += NT) {
+        w.perm[g.start + slot[p]] = w.rs_idx[g.start + p];
+        w.syz[g.start + slot[p]] = w.rs_yz[g.start + p];
+      }
+      return;
+    }
+#pragma unroll
+    for (int k = 0; k < KR; ++k)
+      if (tid + k * NT < n) at[k] = slot[tid + k * NT];
+  }
+  // y, z and id to their places
+  group_sync<NT>();
+#pragma unroll
+  for (int k = 0; k < KR; ++k)
+    if (tid + k * NT < n) slot[at[k]] = y[k];
+  group_sync<NT>();
+#pragma unroll
+  for (int k = 0; k < KR; ++k)
+    if (tid + k * NT < n) y[k] = slot[tid + k * NT];
+  group_sync<NT>();
+#pragma unroll
+  for (int k = 0; k < KR; ++k)
+    if (tid + k * NT < n) slot[at[k]] = z[k];
+  group_sync<NT>();
+#pragma unroll
+  for (int k = 0; k < KR; ++k)
+    if (tid + k * NT < n) w.syz[g.start + tid + k * NT] = make_int2(y[k], slot[tid + k * NT]);
+  group_sync<NT>();
+#pragma unroll
+  for (int k = 0; k < KR; ++k)
+    if (tid + k * NT < n) slot[at[k]] = id[k];
+  group_sync<NT>();
+#pragma unroll
+  for (int k = 0; k < KR; ++k)
+    if (tid + k * NT < n) w.perm[g.start + tid + k * NT] = slot[tid + k * NT];
+}
+
+// rows past the pool: cursors in the workspace (called by the whole block)
+template <int NT>
+__device__ __forceinline__ void bin_sort_global(const Workspace &w, const BinGrid &g, int *tmp) {
+  int *hist = w.cursor + g.cbase;
+  const int tid = threadIdx.x;
+  for (int b = tid; b < g.nbins; b += NT) hist[b] = 0;
+  __syncthreads();
+  for (int p = tid; p < g.count; p += NT) atomicAdd(&hist[g.bin(w.rs_yz[g.start + p])], 1);
+  __syncthreads();
+  scan_bins<NT>(hist, g.nbins, w.cell + g.cbase, g.start, tid, tmp);
+  __syncthreads();
+  if (tid >= 64) return;
+  int nbits = 1;
+  while ((1 << nbits) < g.nbins) ++nbits;
+  for (int c = 0; c < g.count; c += 64) {
+    const int p = c + tid;
+    const bool act = p < g.count;
+    int2 yz = make_int2(0, 0);
+    int idx = 0, bn = 0;
+    if (act) {
+      yz = w.rs_yz[g.start + p];
+      idx = w.rs_idx[g.start + p];
+      bn = g.bin(yz);
+    }
+    const uint64_t peers = peer_mask(uint32_t(bn), nbits, act);
+    int pos = 0;
+    if (act) pos = g.start + hist[bn] + __popcll(peers & lanemask_lt());
+    __builtin_amdgcn_wave_barrier();
+    if (act && (63 - __clzll(peers)) == tid) hist[bn] += __popcll(peers);
+    __builtin_amdgcn_wave_barrier();
+    if (act) {
+      w.perm[pos] = idx;
+      w.syz[pos] = yz;
+    }
+  }
+}
+
+// A block per (unit,row).
+constexpr int BIN_TPB = 512;
+__global__ void __launch_bounds__(BIN_TPB) k_bin_sort(Args A) {
+  __shared__ int pool[BIN_POOL];
+  __shared__ int tmp[BIN_TPB / 64];
+  const Workspace &w = A.w;
+  if (*A.out.status != TPC_OK) return;
+  const BinGrid g(w, blockIdx.x);
+  if (g.nbins + 1 + g.count <= BIN_POOL) bin_sort_lds<BIN_TPB, 12>(w, g, threadIdx.x, pool, tmp);
+  else bin_sort_global<BIN_TPB>(w, g, tmp);
+}
+
+// Four (unit,row)s a block, a wave each where they are small enough for it;
+// the block then takes the larger ones together.
+__global__ void __launch_bounds__(TPB) k_bin_sort_small(Args A) {
+  constexpr int WAVES = TPB / 64, POOL = WAVES * BIN_POOL_WAVE, KR = 8;
+  __shared__ int pool[POOL];
+  __shared__ int tmp[WAVES];
+  const Workspace &w = A.w;
+  if (*A.out.status != TPC_OK) return;
+  const int64_t s0 = int64_t(blockIdx.x) * WAVES;
+  const int wave = threadIdx.x >> 6;
+  if (s0 + wave < w.S) {
+    const BinGrid g(w, s0 + wave);
+    if (g.nbins + 1 + g.count <= BIN_POOL_WAVE && g.count <= 64 * KR)
+      bin_sort_lds<64, KR>(w, g, __lane_id(), pool + wave * BIN_POOL_WAVE, tmp);
+  }
+  for (int i = 0; i < WAVES && s0 + i < w.S; ++i) {  // block-uniform
+    const BinGrid g(w, s0 + i);
+    if (g.nbins + 1 + g.count <= BIN_POOL_WAVE && g.count <= 64 * KR) continue;
+    __syncthreads();
+    if (g.nbins + 1 + g.count <= POOL) bin_sort_lds<TPB, KR>(w, g, threadIdx.x, pool, tmp);
+    else bin_sort_global<TPB>(w, g, tmp);
+  }
+}
+// Hits a (unit,row) holds on average up to which k_bin_sort_small takes them.
+// A wave holds 512; the whole call takes, by the small kernel and by the other:
+// 91 hits a row 889 and 917 us, 274 a row 1203 and 1230, 548 a row 1519 and
+// 1521, 1.1 k a row 2020 and 2009.
+constexpr int64_t BIN_SMALL = 512;
+
+// ---------------------------------------------------------------------------
+// step 3: neighbour finder.  For hit m of row i (0 < i < n_rows-1): candidates
+// n of rows j = i-1, i+1 with |Y_n X_i - Y_m X_j| <= win_y X_i (origin-pointing
+// in the bending plane) and |Z_n - Z_m| <= win_z (no vertex pointing in z).  Of
+// all pairs (d below, u above), the least (score, id_d, id_u) with
+// score = w_y R_y^2 + w_z R_z^2, R = (V_d - V_m)(X_u - X_i) + (V_u - V_m)(X_i - X_d),
+// is kept when score <= smax_k (X_{i+1} - X_{i-1})^2.
 
 struct Win {
   int iy0, iy1, iz0, iz1, ny, cbase;
@@ -2246,7 +2371,8 @@ int track_impl(const tpc_clusters_t *c, const tpc_geometry_t *g, const tpc_field
     mark();
     hipLaunchKernelGGL(k_tile_scatter, dim3(unsigned(w.T_max)), dim3(TPB), 0, st, A);
     mark();
-    hipLaunchKernelGGL(k_bin_sort, dim3(unsigned(w.S)), dim3(TPB), 0, st, A);
+    if (c->n <= BIN_SMALL * w.S) hipLaunchKernelGGL(k_bin_sort_small, dim3(blocks_for(w.S, TPB / 64)), dim3(TPB), 0, st, A);
+    else hipLaunchKernelGGL(k_bin_sort, dim3(unsigned(w.S)), dim3(BIN_TPB), 0, st, A);
     mark();
     hipLaunchKernelGGL(k_neighbours, dim3(round8(w.CH_max)), dim3(NCH), 0, st, A);
     mark();
