@@ -41,11 +41,12 @@ constexpr float KAPPA = 0.00299792458f;
 enum { S_START = 0, S_COUNT, S_ZMIN, S_ZMAX, S_H, S_BY, S_NY, S_BZ, S_NZ, S_CBASE, S_CHUNK };
 // internal counters
 enum { C_K = 0, C_CELLS = 1, C_TRACKS = 2, C_HITS = 3, C_TILES = 4, C_NCHUNK = 5, C_SEEDS = 6, C_NWIDE = 7,
-       C_TICKET = 8, C_N = 9 };
+       C_TICKET = 8, C_PLANNED = 9, C_N = 10 };
 
 struct Workspace {
   int64_t *ctr;
-  int32_t *seg, *seg_cnt, *seg_zmin, *seg_zmax, *seg_nbins;
+  int32_t *seg, *seg_cnt, *seg_zmin, *seg_zmax;
+  int32_t *unit_base;  // per unit: its first cell and chunk
   float2 *seg_inv;  // per (unit,row): 1/by, 1/bz
   int32_t *unit_tiles, *tile_hist;
   int32_t *rs_idx;
@@ -119,7 +120,7 @@ bool layout(int64_t n, int32_t n_units, int32_t n_rows, const tpc_params_t *p, c
   L.seg_cnt = (int32_t *)take(4 * S);
   L.seg_zmin = (int32_t *)take(4 * S);
   L.seg_zmax = (int32_t *)take(4 * S);
-  L.seg_nbins = (int32_t *)take(4 * S);
+  L.unit_base = (int32_t *)take(8 * size_t(n_units));
   L.seg_inv = (float2 *)take(8 * S);
   L.unit_tiles = (int32_t *)take(4 * (size_t(n_units) + 1));
   L.tile_hist = (int32_t *)take(4 * size_t(n_rows) * size_t(L.T_max));
@@ -291,7 +292,11 @@ __device__ __forceinline__ int32_t *seed_column(const Workspace &w, int64_t i, i
   return w.trk_hits + ((i >> 6) * nr) * 64 + (i & 63);
 }
 
-__global__ void k_init(Args A) {
+// The counters and per-hit outputs cleared; the first block also checks the
+// rows and units, counts each unit's tiles and sets the status (its own
+// launch cost 4.6 us, all of it launch).
+__global__ void __launch_bounds__(TPB) k_init(Args A) {
+  __shared__ int tmp[TPB / 64];
   const Workspace &w = A.w;
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < w.S) {
@@ -303,18 +308,13 @@ __global__ void k_init(Args A) {
     w.owner[i] = 0u;
     A.out.cluster_track[i] = -1;
   }
-  if (i < C_N) w.ctr[i] = 0;
+  if (i < C_N && i != C_TILES) w.ctr[i] = 0;
   if (i < w.SB) w.lookback[i] = 0;
   if (i < w.KB) w.blk_keep[i] = 0;
   if (i < 5) A.out.counts[i] = 0;
-  if (i == 0) *A.out.status = TPC_OK;
-}
-
-__global__ void __launch_bounds__(1024) k_units(Args A) {
-  __shared__ int tmp[16];
-  const Workspace &w = A.w;
+  if (blockIdx.x != 0) return;
   bool bad = false;
-  for (int r = threadIdx.x; r < A.n_rows; r += blockDim.x) {
+  for (int r = threadIdx.x; r < A.n_rows; r += TPB) {
     const float x = A.row_x[r];
     if (!(x >= 1.f && x < 8192.f)) bad = true;  // 1 cm .. 8192 cm: X is at least 256 quanta
     if (r > 0 && !(x > A.row_x[r - 1])) bad = true;
@@ -325,7 +325,7 @@ __global__ void __launch_bounds__(1024) k_units(Args A) {
   }
   if (threadIdx.x == 0 && (A.off[0] != 0 || A.off[A.n_units] != A.n)) bad = true;
   int carry = 0;
-  for (int base = 0; base < A.n_units; base += blockDim.x) {
+  for (int base = 0; base < A.n_units; base += TPB) {
     const int u = base + threadIdx.x;
     int tiles = 0;
     if (u < A.n_units) {
@@ -334,15 +334,16 @@ __global__ void __launch_bounds__(1024) k_units(Args A) {
       else tiles = int((b - a + TILE - 1) / TILE);
     }
     int tot;
-    const int ex = block_exclusive_scan<1024>(tiles, tmp, &tot);
+    const int ex = block_exclusive_scan<TPB>(tiles, tmp, &tot);
     if (u < A.n_units) w.unit_tiles[u] = carry + ex;
     carry += tot;
   }
+  const bool any = __syncthreads_or(bad);
   if (threadIdx.x == 0) {
     w.unit_tiles[A.n_units] = carry;
     w.ctr[C_TILES] = carry;
+    *A.out.status = any ? TPC_E_INVALID : TPC_OK;
   }
-  if (bad) set_status(A.out.status, TPC_E_INVALID);
 }
 
 // ---------------------------------------------------------------------------
@@ -396,6 +397,7 @@ __global__ void __launch_bounds__(TPB) k_tile_hist(Args A) {
 // give about bin_occ hits per bin, none shorter than bin_zmin.
 __global__ void __launch_bounds__(256) k_seg_plan(Args A) {
   __shared__ int tmp[4];
+  __shared__ bool last;
   const Workspace &w = A.w;
   if (*A.out.status != TPC_OK) return;
   const int u = blockIdx.x, r = threadIdx.x;
@@ -403,9 +405,9 @@ __global__ void __launch_bounds__(256) k_seg_plan(Args A) {
   const int cnt = r < A.n_rows ? w.seg_cnt[s] : 0;
   int tot;
   const int pre = block_exclusive_scan<256>(cnt, tmp, &tot);
-  if (r >= A.n_rows) return;
+  const bool in = r < A.n_rows;
   const tpc_params_t &P = A.p;
-  const int64_t X = __float2ll_rn(A.row_x[r] * 256.0f);
+  const int64_t X = __float2ll_rn(A.row_x[in ? r : 0] * 256.0f);
   const int64_t H = (X * P.tan_half_q16) >> 16;
   int64_t by = P.bin_y_q;
   if (by < 2 * H / 63 + 1) by = 2 * H / 63 + 1;
@@ -419,47 +421,59 @@ __global__ void __launch_bounds__(256) k_seg_plan(Args A) {
   int64_t nz = nz_occ < nz_span ? nz_occ : nz_span;
   if (nz < 1) nz = 1;
   const int64_t bz = span / nz + 1;
-  int32_t *rec = w.seg + s * SEGW;
-  rec[S_START] = int32_t(A.off[u] + pre);
-  rec[S_COUNT] = cnt;
-  rec[S_ZMIN] = int32_t(zmin);
-  rec[S_ZMAX] = int32_t(zmax);
-  rec[S_H] = int32_t(H);
-  rec[S_BY] = int32_t(by);
-  rec[S_NY] = int32_t(ny);
-  rec[S_BZ] = int32_t(bz);
-  rec[S_NZ] = int32_t(nz);
-  rec[10] = 0;
-  rec[11] = 0;
-  w.seg_nbins[s] = int32_t(ny * nz);
-  w.seg_inv[s] = make_float2(1.f / float(by), 1.f / float(bz));
-}
-
-// step 2c: first cell of every (unit,row), and the end sentinel
-__global__ void __launch_bounds__(1024) k_cell_base(Args A) {
-  __shared__ int tmp[16];
-  const Workspace &w = A.w;
-  if (*A.out.status != TPC_OK) return;
-  int carry = 0, ccarry = 0;
-  for (int64_t base = 0; base < w.S; base += 1024) {
-    const int64_t s = base + threadIdx.x;
-    const int v = s < w.S ? w.seg_nbins[s] : 0;
-    const int nch = s < w.S ? (w.seg[s * SEGW + S_COUNT] + NCH - 1) / NCH : 0;
-    int tot, ctot;
-    const int ex = block_exclusive_scan<1024>(v, tmp, &tot);
-    const int cex = block_exclusive_scan<1024>(nch, tmp, &ctot);
-    if (s < w.S) {
-      w.seg[s * SEGW + S_CBASE] = carry + ex;
-      w.seg[s * SEGW + S_CHUNK] = ccarry + cex;
-    }
-    carry += tot;
-    ccarry += ctot;
+  int n_cells, n_chunks;
+  const int cells = block_exclusive_scan<256>(in ? int(ny * nz) : 0, tmp, &n_cells);
+  const int chunks = block_exclusive_scan<256>((cnt + NCH - 1) / NCH, tmp, &n_chunks);
+  if (in) {
+    int32_t *rec = w.seg + s * SEGW;
+    rec[S_START] = int32_t(A.off[u] + pre);
+    rec[S_COUNT] = cnt;
+    rec[S_ZMIN] = int32_t(zmin);
+    rec[S_ZMAX] = int32_t(zmax);
+    rec[S_H] = int32_t(H);
+    rec[S_BY] = int32_t(by);
+    rec[S_NY] = int32_t(ny);
+    rec[S_BZ] = int32_t(bz);
+    rec[S_NZ] = int32_t(nz);
+    rec[11] = 0;
+    rec[S_CBASE] = cells;  // within the unit; k_tile_offsets adds the unit's
+    rec[S_CHUNK] = chunks;
+    w.seg_inv[s] = make_float2(1.f / float(by), 1.f / float(bz));
   }
-  if (threadIdx.x == 0) {
-    w.ctr[C_CELLS] = carry;
-    w.ctr[C_NCHUNK] = ccarry;
-    A.out.counts[3] = carry;
-    w.cell[carry] = int32_t(A.n);
+  // The unit's cells and chunks, and from the block that ends last all units'
+  // first ones.  They travel between the XCDs as device-scope atomics.  (One
+  // block that scanned all (unit,row)s, 1024 at a time, took 159 us of the
+  // 3.5 ms of a call of 512 units, and 4.6 us, its launch, of the smallest.)
+  int32_t *base = w.unit_base;
+  if (r == 0) {
+    __hip_atomic_store(&base[2 * u], n_cells, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&base[2 * u + 1], n_chunks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = __hip_atomic_fetch_add(&w.ctr[C_PLANNED], int64_t(1), __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
+           A.n_units - 1;
+  }
+  __syncthreads();
+  if (!last) return;
+  int c0 = 0, k0 = 0;
+  for (int b = 0; b < A.n_units; b += 256) {
+    const int v = b + r;
+    int c = 0, k = 0, ct, kt;
+    if (v < A.n_units) {
+      c = __hip_atomic_load(&base[2 * v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      k = __hip_atomic_load(&base[2 * v + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    const int ce = block_exclusive_scan<256>(c, tmp, &ct), ke = block_exclusive_scan<256>(k, tmp, &kt);
+    if (v < A.n_units) {
+      base[2 * v] = c0 + ce;
+      base[2 * v + 1] = k0 + ke;
+    }
+    c0 += ct;
+    k0 += kt;
+  }
+  if (r == 0) {
+    w.ctr[C_CELLS] = c0;
+    w.ctr[C_NCHUNK] = k0;
+    A.out.counts[3] = c0;
+    w.cell[c0] = int32_t(A.n);
   }
 }
 
@@ -475,8 +489,14 @@ __global__ void __launch_bounds__(64) k_tile_offsets(Args A) {
   int32_t *h = w.tile_hist + int64_t(r) * w.T_max;
   const int lane = __lane_id();
   // neighbour-finder chunks of this (unit,row) point back to it
-  const int c0 = w.seg[s * SEGW + S_CHUNK], nch = (w.seg[s * SEGW + S_COUNT] + NCH - 1) / NCH;
+  const int c0 = w.seg[s * SEGW + S_CHUNK] + w.unit_base[2 * u + 1], nch = (w.seg[s * SEGW + S_COUNT] + NCH - 1) / NCH;
   for (int j = lane; j < nch; j += 64) w.chunk_seg[c0 + j] = int32_t(s);
+  const int cbase = w.seg[s * SEGW + S_CBASE] + w.unit_base[2 * u];
+  __builtin_amdgcn_wave_barrier();
+  if (lane == 0) {
+    w.seg[s * SEGW + S_CBASE] = cbase;
+    w.seg[s * SEGW + S_CHUNK] = c0;
+  }
   for (int t = t0; t < t1; t += 64) {
     const int i = t + lane;
     const int v = i < t1 ? h[i] : 0;
@@ -2278,7 +2298,7 @@ extern "C" const char *tpc_status_string(int status) {
 namespace {
 
 const char *const kKernelNames[] = {
-    "k_init",        "k_units",      "k_tile_hist",  "k_seg_plan",      "k_cell_base",
+    "k_init",        "k_tile_hist",  "k_seg_plan",
     "k_tile_offsets", "k_tile_scatter", "k_bin_sort",  "k_neighbours",    "k_neighbours_wide", "k_clean",
     "k_scan_blocks", "k_compact_starts", "k_chains", "k_scan_blocks", "k_compact_seeds",
     "k_fit",         "k_select_emit"};
@@ -2357,15 +2377,11 @@ int track_impl(const tpc_clusters_t *c, const tpc_geometry_t *g, const tpc_field
   if (init_n < w.KB) init_n = w.KB;
   mark();
   hipLaunchKernelGGL(k_init, dim3(blocks_for(init_n, TPB)), dim3(TPB), 0, st, A);
-  mark();
-  hipLaunchKernelGGL(k_units, dim3(1), dim3(1024), 0, st, A);
   if (c->n > 0) {
     mark();
     hipLaunchKernelGGL(k_tile_hist, dim3(unsigned(w.T_max)), dim3(TPB), 0, st, A);
     mark();
     hipLaunchKernelGGL(k_seg_plan, dim3(unsigned(c->n_units)), dim3(256), 0, st, A);
-    mark();
-    hipLaunchKernelGGL(k_cell_base, dim3(1), dim3(1024), 0, st, A);
     mark();
     hipLaunchKernelGGL(k_tile_offsets, dim3(unsigned(w.S)), dim3(64), 0, st, A);
     mark();
