@@ -41,7 +41,7 @@ constexpr float KAPPA = 0.00299792458f;
 enum { S_START = 0, S_COUNT, S_ZMIN, S_ZMAX, S_H, S_BY, S_NY, S_BZ, S_NZ, S_CBASE, S_CHUNK };
 // internal counters
 enum { C_K = 0, C_CELLS = 1, C_TRACKS = 2, C_HITS = 3, C_TILES = 4, C_NCHUNK = 5, C_SEEDS = 6, C_NWIDE = 7,
-       C_TICKET = 8, C_PLANNED = 9, C_N = 10 };
+       C_SELECT = 8, C_PLANNED = 9, C_N = 10 };
 
 struct Workspace {
   int64_t *ctr;
@@ -59,7 +59,7 @@ struct Workspace {
   int32_t *cell, *cursor;
   int32_t *chunk_seg, *wide;  // neighbour-finder chunk -> (unit,row); chunks too wide for LDS
   int32_t *blk, *blk_keep;
-  uint64_t *lookback;  // per seed block: decoupled look-back word of the selector
+  uint64_t *sel_sum;  // per 256 seeds: the selector's kept tracks and their hits
   // per tracklet (chain start), capacity T_cap = n/2 + 64: a start hit has an
   // upward partner that starts nothing, so there are at most n/2
   int32_t *trk_start, *trk_unit, *trk_len;
@@ -137,7 +137,7 @@ bool layout(int64_t n, int32_t n_units, int32_t n_rows, const tpc_params_t *p, c
   L.wide = (int32_t *)take(4 * size_t(L.CH_max));
   L.blk = (int32_t *)take(4 * size_t(L.NB));
   L.blk_keep = (int32_t *)take(4 * size_t(L.KB));
-  L.lookback = (uint64_t *)take(8 * size_t(L.SB));
+  L.sel_sum = (uint64_t *)take(8 * size_t(L.SB));
   L.trk_start = (int32_t *)take(4 * T);
   L.trk_unit = (int32_t *)take(4 * T);
   L.trk_len = (int32_t *)take(4 * T);
@@ -309,7 +309,7 @@ __global__ void __launch_bounds__(TPB) k_init(Args A) {
     A.out.cluster_track[i] = -1;
   }
   if (i < C_N && i != C_TILES) w.ctr[i] = 0;
-  if (i < w.SB) w.lookback[i] = 0;
+  if (i < w.SB) w.sel_sum[i] = 0;
   if (i < w.KB) w.blk_keep[i] = 0;
   if (i < 5) A.out.counts[i] = 0;
   if (blockIdx.x != 0) return;
@@ -2095,175 +2095,196 @@ __global__ void __launch_bounds__(64) k_fit_group(Args A) {
 // step 6: selector and output.  Keep a tracklet that owns >= n_min of its
 // hits and at least f_min of them; tracks keep the tracklet order; no refit.
 //
-// One pass over the seed list (tracklets that are not seeds own nothing and
-// are never kept; k_chains set their owned = keep = 0).  Seeds are in
+// Both passes are over the seed list (tracklets that are not seeds own nothing
+// and are never kept; k_chains set their owned = keep = 0).  Seeds are in
 // tracklet order, so an exclusive scan over seed order numbers the tracks in
-// tracklet order.  The scan is a single-pass decoupled look-back: a block
-// takes the next 256 seeds by ticket (so every seed block it waits on has
-// already started), counts and marks its tracklets' owned hits, publishes its
-// (tracks, hits) aggregate, adds up its predecessors' aggregates until it
-// meets an inclusive prefix, publishes its own inclusive prefix, and writes
-// its tracks.  The grid is a fixed number of blocks that loop over tickets,
-// so the launch does not depend on the tracklet capacity.
+// tracklet order.  A block takes 64 seeds, a column of the hit table each, and
+// its waves a share of the rows each (a batch of few seeds has few
+// blocks, and the rows are then what there is to share out).
+//   k_select  counts and marks each tracklet's owned hits, and adds the tracks
+//             and hits of 256 seeds to their word of sel_sum;
+//   k_emit    adds up the words before its seeds, stages its hits in LDS and
+//             writes the tracks and their hits in whole lines.
+// What bounds them: gathers and scatters by hit (owner, id, the hit's track).
+// Neighbouring seeds share the cache lines of these, so each XCD takes one
+// contiguous range of seeds.  One kernel that numbered its blocks by ticket,
+// 256 seeds at a time, and so dealt neighbours to all XCDs, took 225 us for 512
+// chunks (these two 46 and 110), 43 for one (7 and 10) and 1340 for 50
+// collisions (475 and 890: there the tracks of the hits, whose ids are in no
+// order, leave the L2 in parts of lines).
 
-// look-back word: flag (bits 62-63: 1 aggregate, 2 inclusive prefix),
-// tracks (bits 31-61), hits (bits 0-30).  The counts travel in the same
-// 64-bit word as their flag, so relaxed device-scope atomics suffice: no
-// other memory is published with it (release/acquire would write back and
-// invalidate the caches at every step).
-constexpr uint64_t LB_AGG = uint64_t(1) << 62, LB_INC = uint64_t(2) << 62;
-__device__ __forceinline__ uint64_t lb_word(uint64_t flag, int tracks, int hits) {
-  return flag | (uint64_t(uint32_t(tracks)) << 31) | uint64_t(uint32_t(hits));
+// a word of sel_sum: kept tracks (bits 31-62), their hits (bits 0-30)
+__device__ __forceinline__ uint64_t sel_word(int tracks, int hits) {
+  return (uint64_t(uint32_t(tracks)) << 31) | uint64_t(uint32_t(hits));
 }
 constexpr int SELECT_BLOCKS = 2048;
-constexpr int LB_SPIN_MAX = 1 << 26;
+constexpr int SEL_RB = 20;    // rows of a round trip
 
-__global__ void __launch_bounds__(TPB) k_select_emit(Args A) {
-  __shared__ int tmp[4];
-  __shared__ int64_t s_vb;
-  __shared__ int s_bt, s_bh;  // tracks and hits of the blocks before this one
+template <int WAVES>
+__global__ void __launch_bounds__(WAVES * 64) k_select(Args A) {
+  __shared__ int cnt[WAVES][64];
   const Workspace &w = A.w;
   if (*A.out.status != TPC_OK) return;
-  const int64_t n_seeds = w.ctr[C_SEEDS];
-  const int64_t nvb = (n_seeds + TPB - 1) / TPB;
-  const int nr = A.n_rows;
-  const tpc_tracks_t &O = A.out;
-  for (;;) {
-    if (threadIdx.x == 0)
-      s_vb = int64_t(atomicAdd(reinterpret_cast<unsigned long long *>(&w.ctr[C_TICKET]), 1ull));
-    __syncthreads();
-    const int64_t vb = s_vb;
-    if (vb >= nvb) return;
-    const int64_t i = vb * TPB + threadIdx.x;
+  if (blockIdx.x == 0 && threadIdx.x == 0) w.ctr[C_SELECT] = 1;  // k_emit writes the status while others start
+  const int64_t n_seeds = w.ctr[C_SEEDS], n_tiles = (n_seeds + 63) / 64;
+  const int nr = A.n_rows, wave = threadIdx.x >> 6, lane = __lane_id();
+  const int part = (nr + WAVES - 1) / WAVES;
+  const int ra = wave * part, rz = min(nr, ra + part);  // the wave's rows
+  for (int64_t b = blockIdx.x; b < ((n_tiles + 7) & ~int64_t(7)); b += gridDim.x) {
+    const int64_t tile = xcd_chunk(b, n_tiles);
+    if (tile >= n_tiles) continue;  // block-uniform
+    const int64_t i = tile * 64 + lane;
     const bool valid = i < n_seeds;
-    const int64_t t = valid ? w.seed_list[i] : 0;
     const int nfit = valid ? w.sd_nfit[i] : 0;
     const bool has = nfit > 0;
     const uint32_t key = has ? w.sd_key[i] : 0u;
-    const int rlo = has ? w.sd_rlo[i] : 0, rhi = has ? w.sd_rhi[i] : -1;
+    const int rlo = has ? max(ra, w.sd_rlo[i]) : 0, rhi = has ? min(rz - 1, w.sd_rhi[i]) : -1;
     int32_t *col = seed_column(w, i, nr);
     // owned hits: those whose owner key is this tracklet's, marked for the output
     int owned = 0;
-    {
-      const int rb = wave_max(has ? rhi : -1);
-      for (int r0 = wave_min(has ? rlo : nr); r0 <= rb; r0 += RB) {  // RB rows per round trip
-        int h[RB];
-        uint32_t o[RB];
+    const int rb = wave_max(has ? rhi : -1);
+    for (int r0 = wave_min(has ? rlo : nr); r0 <= rb; r0 += SEL_RB) {
+      int h[SEL_RB];
+      uint32_t o[SEL_RB];
 #pragma unroll
-        for (int k = 0; k < RB; ++k) h[k] = (r0 + k >= rlo && r0 + k <= rhi) ? col[(r0 + k) * 64] : -1;
+      for (int k = 0; k < SEL_RB; ++k) h[k] = (r0 + k >= rlo && r0 + k <= rhi) ? col[(r0 + k) * 64] : -1;
 #pragma unroll
-        for (int k = 0; k < RB; ++k) o[k] = h[k] >= 0 ? w.owner[h[k]] : 0u;
+      for (int k = 0; k < SEL_RB; ++k) o[k] = h[k] >= 0 ? w.owner[h[k]] : 0u;
 #pragma unroll
-        for (int k = 0; k < RB; ++k)
-          if (h[k] >= 0 && o[k] == key) {
-            ++owned;
-            col[(r0 + k) * 64] = h[k] | OWNED;
-          }
-      }
-    }
-    const int keep = has && owned >= A.p.n_min && int64_t(owned) * 256 >= int64_t(A.p.f_min_q8) * nfit;
-    if (valid) {
-      w.sd_owned[i] = owned;
-      w.sd_keep[i] = keep;
-    }
-    int tk, to;
-    const int ek = block_exclusive_scan<TPB>(keep, tmp, &tk);
-    const int eo = block_exclusive_scan<TPB>(keep ? owned : 0, tmp, &to);
-    if (threadIdx.x < 64) {  // wave 0: publish, then look back 64 predecessors at a time
-      uint64_t *lb = w.lookback;
-      const int lane = threadIdx.x;
-      int bt = 0, bh = 0;
-      if (vb == 0) {
-        if (lane == 0)
-          __hip_atomic_store(&lb[0], lb_word(LB_INC, tk, to), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      } else {
-        if (lane == 0)
-          __hip_atomic_store(&lb[vb], lb_word(LB_AGG, tk, to), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        int64_t top = vb - 1;  // lane k reads block top - k
-        int spins = 0;
-        for (;;) {
-          const int64_t j = top - lane;
-          // before block 0 counts as an inclusive prefix of nothing
-          const uint64_t v =
-              j >= 0 ? __hip_atomic_load(&lb[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : LB_INC;
-          const uint64_t inc = __ballot((v >> 62) == 2), empty = __ballot((v >> 62) == 0);
-          const int first = inc ? __ffsll(static_cast<unsigned long long>(inc)) - 1 : 64;  // nearest prefix
-          const uint64_t before = first < 64 ? ((uint64_t(1) << first) << 1) - 1 : ~uint64_t(0);
-          if (empty & before) {  // a block between us and that prefix has not published yet
-            // the blocks looked at hold earlier tickets, so they are running or done
-            if (++spins > LB_SPIN_MAX) {
-              if (lane == 0) set_status(A.out.status, TPC_E_HIP);
-              break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-            continue;
-          }
-          int vt = lane <= first ? int((v >> 31) & 0x7FFFFFFF) : 0;
-          int vh = lane <= first ? int(v & 0x7FFFFFFF) : 0;
-#pragma unroll
-          for (int o = 32; o > 0; o >>= 1) {
-            vt += __shfl_xor(vt, o, 64);
-            vh += __shfl_xor(vh, o, 64);
-          }
-          bt += vt;
-          bh += vh;
-          if (first < 64) break;
-          top -= 64;
+      for (int k = 0; k < SEL_RB; ++k)
+        if (h[k] >= 0 && o[k] == key) {
+          ++owned;
+          col[(r0 + k) * 64] = h[k] | OWNED;
         }
-        if (lane == 0)
-          __hip_atomic_store(&lb[vb], lb_word(LB_INC, bt + tk, bh + to), __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
+    }
+    cnt[wave][lane] = owned;
+    __syncthreads();
+    if (wave == 0) {
+      owned = 0;
+#pragma unroll
+      for (int v = 0; v < WAVES; ++v) owned += cnt[v][lane];
+      const int keep = has && owned >= A.p.n_min && int64_t(owned) * 256 >= int64_t(A.p.f_min_q8) * nfit;
+      if (valid) {
+        w.sd_owned[i] = owned;
+        w.sd_keep[i] = keep;
       }
-      if (lane == 0) {
-        s_bt = bt;
-        s_bh = bh;
-        if (vb == nvb - 1) {  // the last block knows the totals
-          const int64_t nt = int64_t(bt) + tk, nh = int64_t(bh) + to;
-          w.ctr[C_TRACKS] = nt;
-          w.ctr[C_HITS] = nh;
-          O.counts[0] = nt;
-          O.counts[1] = nh;
-          if (nt > O.cap_tracks || nh > O.cap_hits) set_status(A.out.status, TPC_E_CAPACITY);
-        }
-      }
+      int hits = keep ? owned : 0;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) hits += __shfl_xor(hits, o, 64);
+      const uint64_t kept = __ballot(keep);
+      if (lane == 0 && kept)
+        atomicAdd(reinterpret_cast<unsigned long long *>(&w.sel_sum[tile >> 2]),
+                  (unsigned long long)sel_word(__popcll(kept), hits));
     }
     __syncthreads();
-    const int tr = s_bt + ek;
-    int64_t off = int64_t(s_bh) + eo;
-    const bool fits = keep && tr < O.cap_tracks && off + owned <= O.cap_hits;
-    int elo = 0, ehi = -1;
-    if (fits) {
-#pragma unroll
-      for (int j = 0; j < 5; ++j) O.params[int64_t(tr) * 5 + j] = w.sd_par[i * 5 + j];
-#pragma unroll
-      for (int j = 0; j < 15; ++j) O.cov[int64_t(tr) * 15 + j] = w.sd_cov[i * 15 + j];
-      O.x_ref[tr] = w.sd_x[i];
-      O.chi2[tr] = w.sd_chi2[i];
-      O.unit[tr] = w.trk_unit[t];
-      O.n_hits[tr] = owned;
-      O.n_fit[tr] = nfit;
-      O.first_hit[tr] = int32_t(off);
-      elo = rlo;
-      ehi = rhi;
+  }
+}
+
+template <int WAVES>
+__global__ void __launch_bounds__(WAVES * 64) k_emit(Args A) {
+  extern __shared__ int32_t ids[];  // the tile's hits, in output order: 64 * n_rows
+  __shared__ int cnt[WAVES][64], dest[64];
+  __shared__ unsigned long long sums[WAVES];
+  const Workspace &w = A.w;
+  if (!w.ctr[C_SELECT]) return;
+  const int64_t n_seeds = w.ctr[C_SEEDS], n_tiles = (n_seeds + 63) / 64;
+  const int nr = A.n_rows, wave = threadIdx.x >> 6, lane = __lane_id();
+  const int part = (nr + WAVES - 1) / WAVES;
+  const int ra = wave * part, rz = min(nr, ra + part);
+  const tpc_tracks_t &O = A.out;
+  for (int64_t b = blockIdx.x; b < ((n_tiles + 7) & ~int64_t(7)); b += gridDim.x) {
+    const int64_t tile = xcd_chunk(b, n_tiles);
+    if (tile >= n_tiles) continue;  // block-uniform
+    // the tracks and hits before the tile: whole words, then the tiles of its own
+    uint64_t sum = 0;
+    for (int64_t j = threadIdx.x; j < (tile >> 2); j += WAVES * 64) sum += w.sel_sum[j];
+    if (int(threadIdx.x) < int(tile & 3) * 64) {
+      const int64_t s = (tile >> 2) * 256 + threadIdx.x;
+      if (w.sd_keep[s]) sum += sel_word(1, w.sd_owned[s]);
     }
-    {
-      const int rb = wave_max(fits ? ehi : -1);
-      for (int r0 = wave_min(fits ? elo : nr); r0 <= rb; r0 += RB) {  // RB rows per round trip
-        int h[RB], id[RB];
+    const int64_t i = tile * 64 + lane;
+    const bool valid = i < n_seeds;
+    const bool keep = valid && w.sd_keep[i];
+    const int owned = keep ? w.sd_owned[i] : 0;
+    const int rlo = keep ? max(ra, w.sd_rlo[i]) : 0, rhi = keep ? min(rz - 1, w.sd_rhi[i]) : -1;
+    const int32_t *col = seed_column(w, i, nr);
+    const int rb = wave_max(rhi);
+    const int row_a = wave_min(keep ? rlo : nr);
+    int mine = 0;
+    for (int r0 = row_a; r0 <= rb; r0 += SEL_RB) {
+      int h[SEL_RB];
 #pragma unroll
-        for (int k = 0; k < RB; ++k) h[k] = (r0 + k >= elo && r0 + k <= ehi) ? col[(r0 + k) * 64] : -1;
+      for (int k = 0; k < SEL_RB; ++k) h[k] = (r0 + k >= rlo && r0 + k <= rhi) ? col[(r0 + k) * 64] : -1;
 #pragma unroll
-        for (int k = 0; k < RB; ++k) id[k] = (h[k] >= 0 && (h[k] & OWNED)) ? w.perm[h[k] & (OWNED - 1)] : -1;
+      for (int k = 0; k < SEL_RB; ++k) mine += h[k] >= 0 && (h[k] & OWNED);
+    }
 #pragma unroll
-        for (int k = 0; k < RB; ++k) {
-          if (id[k] >= 0) {
-            O.hits[off++] = id[k];
-            O.cluster_track[id[k]] = tr;
-          }
-        }
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor((unsigned long long)sum, o, 64);
+    if (lane == 0) sums[wave] = sum;
+    cnt[wave][lane] = mine;
+    __syncthreads();
+    sum = 0;
+    int at = 0;
+#pragma unroll
+    for (int v = 0; v < WAVES; ++v) {
+      sum += sums[v];
+      at += v < wave ? cnt[v][lane] : 0;
+    }
+    const int64_t t0 = int64_t(sum >> 31), h0 = int64_t(sum & 0x7FFFFFFF);
+    const uint64_t kept = __ballot(keep);
+    int eo = owned;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(eo, o, 64);
+      if (lane >= o) eo += y;
+    }
+    const int total = __shfl(eo, 63, 64);
+    eo -= owned;
+    const int64_t tr = t0 + __popcll(kept & lanemask_lt()), off = h0 + eo;
+    // the tracks that fit come first: both counts only grow
+    const bool fits = keep && tr < O.cap_tracks && off + owned <= O.cap_hits;
+    const int n_out = wave_max(fits ? eo + owned : 0);
+    if (tile == n_tiles - 1 && threadIdx.x == 0) {  // the last tile knows the totals
+      const int64_t nt = t0 + __popcll(kept), nh = h0 + total;
+      w.ctr[C_TRACKS] = nt;
+      w.ctr[C_HITS] = nh;
+      O.counts[0] = nt;
+      O.counts[1] = nh;
+      if (nt > O.cap_tracks || nh > O.cap_hits) set_status(A.out.status, TPC_E_CAPACITY);
+    }
+    if (wave == 0) {
+      dest[lane] = fits ? int(tr) : -1;
+      if (fits) {
+        O.x_ref[tr] = w.sd_x[i];
+        O.chi2[tr] = w.sd_chi2[i];
+        O.unit[tr] = w.trk_unit[w.seed_list[i]];
+        O.n_hits[tr] = owned;
+        O.n_fit[tr] = w.sd_nfit[i];
+        O.first_hit[tr] = int32_t(off);
       }
     }
-    __syncthreads();  // s_vb, s_bt, s_bh are rewritten by the next ticket
+    at += eo;
+    for (int r0 = row_a; r0 <= rb; r0 += SEL_RB) {
+      int h[SEL_RB], id[SEL_RB];
+#pragma unroll
+      for (int k = 0; k < SEL_RB; ++k) h[k] = (r0 + k >= rlo && r0 + k <= rhi) ? __builtin_nontemporal_load(&col[(r0 + k) * 64]) : -1;
+#pragma unroll
+      for (int k = 0; k < SEL_RB; ++k)
+        id[k] = fits && h[k] >= 0 && (h[k] & OWNED) ? w.perm[h[k] & (OWNED - 1)] : -1;
+#pragma unroll
+      for (int k = 0; k < SEL_RB; ++k)
+        if (id[k] >= 0) {
+          ids[at++] = id[k];
+          O.cluster_track[id[k]] = int32_t(tr);
+        }
+    }
+    __syncthreads();
+    for (int j = threadIdx.x; j < n_out; j += WAVES * 64) __builtin_nontemporal_store(ids[j], &O.hits[h0 + j]);
+    for (int j = threadIdx.x; j < 64 * 5; j += WAVES * 64)
+      if (dest[j / 5] >= 0) __builtin_nontemporal_store(__builtin_nontemporal_load(&w.sd_par[tile * 320 + j]), &O.params[int64_t(dest[j / 5]) * 5 + j % 5]);
+    for (int j = threadIdx.x; j < 64 * 15; j += WAVES * 64)
+      if (dest[j / 15] >= 0) __builtin_nontemporal_store(__builtin_nontemporal_load(&w.sd_cov[tile * 960 + j]), &O.cov[int64_t(dest[j / 15]) * 15 + j % 15]);
+    __syncthreads();  // ids, cnt, dest and sums are the next tile's
   }
 }
 
@@ -2301,7 +2322,7 @@ const char *const kKernelNames[] = {
     "k_init",        "k_tile_hist",  "k_seg_plan",
     "k_tile_offsets", "k_tile_scatter", "k_bin_sort",  "k_neighbours",    "k_neighbours_wide", "k_clean",
     "k_scan_blocks", "k_compact_starts", "k_chains", "k_scan_blocks", "k_compact_seeds",
-    "k_fit",         "k_select_emit"};
+    "k_fit",         "k_select",    "k_emit"};
 constexpr int kNumKernels = int(sizeof(kKernelNames) / sizeof(kKernelNames[0]));
 
 template <int G, int PER>
@@ -2330,6 +2351,20 @@ void launch_fit(const Args &A, hipStream_t st) {
   else if (A.n <= 1800 * 1024) launch_fit_group<4, 16>(A, st);
   else if (A.n <= 3000 * 1024) launch_fit_group<2, 32>(A, st);
   else hipLaunchKernelGGL(k_fit, dim3(round8(blocks_for(A.w.S_cap, CTB))), dim3(CTB), 0, st, A);
+}
+
+// Waves to 64 seeds.  Eight shorten a small batch's walk over the rows; where
+// there are blocks enough, four leave the caches to fewer of them.
+// Whole calls with eight and with four, by clusters: 18 k 638 and 642 us, 0.5 M
+// 840 and 841, 3 M 1467 and 1480, 7 M 3016 and 3021, 12 M 4259 and 4262, 20 M
+// 6990 and 6942, 25 M 8655 and 8567.
+constexpr int64_t SELECT_WIDE = 8 << 20;
+template <int WAVES, class Mark>
+void launch_select(const Args &A, hipStream_t st, Mark mark) {
+  const unsigned blocks = round8(A.w.KW < SELECT_BLOCKS ? A.w.KW : SELECT_BLOCKS);
+  hipLaunchKernelGGL(k_select<WAVES>, dim3(blocks), dim3(WAVES * 64), 0, st, A);
+  mark();
+  hipLaunchKernelGGL(k_emit<WAVES>, dim3(blocks), dim3(WAVES * 64), unsigned(64 * 4 * A.n_rows), st, A);
 }
 
 int track_impl(const tpc_clusters_t *c, const tpc_geometry_t *g, const tpc_field_t *f,
@@ -2413,8 +2448,8 @@ int track_impl(const tpc_clusters_t *c, const tpc_geometry_t *g, const tpc_field
     mark();
     launch_fit(A, st);
     mark();
-    hipLaunchKernelGGL(k_select_emit, dim3(unsigned(w.SB < SELECT_BLOCKS ? w.SB : SELECT_BLOCKS)), dim3(TPB), 0,
-                       st, A);
+    if (c->n <= SELECT_WIDE) launch_select<8>(A, st, mark);
+    else launch_select<4>(A, st, mark);
   }
   while (ki <= kNumKernels) mark();  // empty batch: the remaining events mark the same point
   if (hipGetLastError() != hipSuccess) return TPC_E_HIP;
