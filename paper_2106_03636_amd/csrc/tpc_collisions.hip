@@ -18,7 +18,8 @@
 // one z'), so the per-bin atomics are spread over NCOPY private copies of
 // every counter, copy = block index mod NCOPY; consecutive blocks go to the
 // eight XCDs in turn, so each copy is updated from one XCD only.  Lanes of a
-// wave that hit the same bin are first combined into one atomic.
+// wave that hit the same bin are first combined into one atomic, and a block's
+// tracks of one candidate in LDS.
 
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -34,6 +35,8 @@ constexpr int MAX_BINS_PER_SIDE = 1 << 16;
 constexpr int MAX_REACH = 64;
 constexpr float MAX_Z_RANGE = 1048576.0f;  // keeps the fixed-point sums of z' far from overflow
 constexpr int MAX_TRACK_BLOCKS = 2048;
+constexpr int MAX_ASSIGN_BLOCKS = 1024;
+constexpr int CAND_LDS = 1024;  // candidates up to which a block sums in LDS
 constexpr double FIX_SCALE = 65536.0;  // z' sums in units of 2^-16 cm
 constexpr float KAPPA = 0.00299792458f;
 
@@ -104,36 +107,55 @@ __device__ __forceinline__ int32_t bin_of(double z, const ColArgs &A) {
   return b < A.nb ? b : A.nb - 1;
 }
 
-// Adds v to a[key] once per distinct key among the lanes with `on` (v is the
-// same on every lane): each round takes the key of the lowest pending lane
-// (v_readlane with a wave-uniform lane, no LDS traffic) and one lane adds v
-// times the number of lanes holding it.  Every lane of the wave must call it.
-__device__ __forceinline__ void wave_add_i32(int32_t *a, int32_t key, bool on, int32_t v) {
+// Lanes with the same bin add to it once: a round takes the bin of the lowest
+// pending lane and one lane adds for all that hold it.  After ROUNDS of them
+// the lanes left add by themselves (50 collisions, 458 k tracks, the whole
+// call with 1, 2, 4 and 8 rounds: 76, 72, 67 and 65 us; without a bound 70: an
+// atomic costs more than a round until few lanes share a bin).  Every lane of
+// the wave must call it.
+constexpr int ROUNDS = 8;
+
+// hist[key] counts the lanes with `on`
+__device__ __forceinline__ void wave_count(int32_t *hist, int32_t key, bool on) {
   uint64_t todo = __ballot(on);
-  while (todo) {
+#pragma unroll
+  for (int round = 0; round < ROUNDS; ++round) {
+    if (!todo) return;
     const int leader = __ffsll((unsigned long long)todo) - 1;
     const int32_t lk = __builtin_amdgcn_readlane(key, leader);
     const uint64_t same = __ballot(on && key == lk) & todo;
-    if (__lane_id() == leader) atomicAdd(&a[lk], v * __popcll(same));
+    if (int(__lane_id()) == leader) atomicAdd(&hist[lk], __popcll(same));
     todo &= ~same;
   }
+  if ((todo >> __lane_id()) & 1) atomicAdd(&hist[key], 1);
 }
 
-// As wave_add_i32 with per-lane values: the lanes holding the round's key
-// are summed across the wave first (two's complement: signed values add as
-// unsigned).
-__device__ __forceinline__ void wave_add_u64(unsigned long long *a, int32_t key, bool on, unsigned long long v) {
+// cf[key] counts the lanes with `on` (high half) and those also with `form`
+// (low half), and sum[key] adds up the latter's v (two's complement: signed
+// values add as unsigned)
+__device__ __forceinline__ void wave_sums(unsigned long long *cf, unsigned long long *sum, int32_t key, bool on, bool form,
+                                          unsigned long long v) {
   uint64_t todo = __ballot(on);
-  while (todo) {
+  const uint64_t forms = __ballot(on && form);
+#pragma unroll
+  for (int round = 0; round < ROUNDS; ++round) {
+    if (!todo) return;
     const int leader = __ffsll((unsigned long long)todo) - 1;
     const int32_t lk = __builtin_amdgcn_readlane(key, leader);
     const bool mine = on && key == lk;
     const uint64_t same = __ballot(mine) & todo;
-    unsigned long long x = mine ? v : 0ull;
-    if (__popcll(same) > 1)
+    unsigned long long x = mine && form ? v : 0ull;
+    if (same & forms)
       for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-    if (__lane_id() == leader) atomicAdd(&a[lk], x);
+    if (int(__lane_id()) == leader) {
+      atomicAdd(&cf[lk], (unsigned long long)__popcll(same) << 32 | (unsigned long long)__popcll(same & forms));
+      if (same & forms) atomicAdd(&sum[lk], x);
+    }
     todo &= ~same;
+  }
+  if ((todo >> __lane_id()) & 1) {
+    atomicAdd(&cf[key], (1ull << 32) | (form ? 1ull : 0ull));
+    if (form) atomicAdd(&sum[key], v);
   }
 }
 
@@ -170,7 +192,7 @@ __global__ void __launch_bounds__(TPB) k_col_zdca(ColArgs A) {
         key = (side > 0 ? 0 : A.nb) + b;
       }
     }
-    wave_add_i32(hist, key, form, 1);
+    wave_count(hist, key, form);
   }
 }
 
@@ -269,8 +291,20 @@ __global__ void __launch_bounds__(TPB) k_col_number(ColArgs A) {
   }
 }
 
+// What bounds it: the sums.  Few candidates hold all tracks, so each block
+// sums up to CAND_LDS of them in LDS and adds what it has at its end; with the
+// waves' sums (above) for every track the call took 65 us, so 50 (with 256 or
+// 512 blocks instead of 1024: 53; latency of the tracks' loads).
 __global__ void __launch_bounds__(TPB) k_col_assign(ColArgs A) {
+  __shared__ unsigned long long s_cf[CAND_LDS], s_sum[CAND_LDS];
+  __shared__ int32_t s_bin[CAND_LDS];
   if (bad(A)) return;
+  const int64_t nc = *A.n_col;
+  const bool in_lds = nc <= CAND_LDS;
+  if (in_lds) {
+    for (int j = threadIdx.x; j < nc; j += TPB) s_cf[j] = s_sum[j] = 0ull;
+    __syncthreads();
+  }
   const int64_t T = A.trk_counts[0];
   const int64_t copy = int64_t(blockIdx.x % NCOPY) * A.n2;
   const int64_t stride = int64_t(gridDim.x) * TPB;
@@ -299,9 +333,21 @@ __global__ void __launch_bounds__(TPB) k_col_assign(ColArgs A) {
       }
       A.col[t] = c;
     }
-    wave_add_u64(A.cf + copy, peak_bin, c >= 0, (1ull << 32) | (form ? 1ull : 0ull));
-    wave_add_u64(A.sum + copy, peak_bin, form, fz);
+    if (!in_lds) {
+      wave_sums(A.cf + copy, A.sum + copy, peak_bin, c >= 0, form, fz);
+    } else if (c >= 0) {
+      atomicAdd(&s_cf[c], (1ull << 32) | (form ? 1ull : 0ull));
+      if (form) atomicAdd(&s_sum[c], fz);
+      s_bin[c] = peak_bin;  // the same from every lane
+    }
   }
+  if (!in_lds) return;
+  __syncthreads();
+  for (int j = threadIdx.x; j < nc; j += TPB)
+    if (s_cf[j]) {
+      atomicAdd(&A.cf[copy + s_bin[j]], s_cf[j]);
+      if (s_sum[j]) atomicAdd(&A.sum[copy + s_bin[j]], s_sum[j]);
+    }
 }
 
 __global__ void __launch_bounds__(TPB) k_col_finish(ColArgs A) {
@@ -420,7 +466,7 @@ extern "C" int tpc_assign_collisions(const tpc_tracks_t *tracks, const int32_t *
   hipLaunchKernelGGL(k_col_zdca, dim3(track_blocks), dim3(TPB), 0, st, A);
   hipLaunchKernelGGL(k_col_flags, dim3(bin_blocks), dim3(TPB), 0, st, A);
   hipLaunchKernelGGL(k_col_number, dim3(bin_blocks), dim3(TPB), 0, st, A);
-  hipLaunchKernelGGL(k_col_assign, dim3(track_blocks), dim3(TPB), 0, st, A);
+  hipLaunchKernelGGL(k_col_assign, dim3(track_blocks < MAX_ASSIGN_BLOCKS ? track_blocks : MAX_ASSIGN_BLOCKS), dim3(TPB), 0, st, A);
   hipLaunchKernelGGL(k_col_finish, dim3(cand_blocks), dim3(TPB), 0, st, A);
   return hipGetLastError() == hipSuccess ? TPC_OK : TPC_E_HIP;
 }
