@@ -73,11 +73,11 @@ COL_KERNEL_BYTES = {"k_col_clear": None, "k_col_zdca": 36, "k_col_flags": None, 
 SQ_COUNTERS = ("SQ_WAVES", "SQ_INSTS_VALU", "SQ_INSTS_SALU", "SQ_INSTS_LDS", "SQ_INSTS_VMEM",
                "SQ_WAVE_CYCLES", "SQ_BUSY_CYCLES", "SQ_WAIT_INST_ANY")
 KERNEL_FAMILY = {
-    "k_init": None, "k_units": None, "k_tile_hist": "grid", "k_seg_plan": "grid",
-    "k_cell_base": "grid", "k_tile_offsets": "grid", "k_tile_scatter": "grid", "k_bin_sort": "grid",
+    "k_init": None, "k_tile_hist": "grid", "k_seg_plan": "grid",
+    "k_tile_offsets": "grid", "k_tile_scatter": "grid", "k_bin_sort": "grid", "k_bin_sort_small": "grid",
     "k_neighbours": "neighbours", "k_neighbours_wide": "neighbours", "k_clean": "cleaner", "k_scan_blocks": "cleaner",
     "k_compact_starts": "cleaner", "k_chains": "constructor", "k_compact_seeds": "constructor",
-    "k_fit": "constructor", "k_select_emit": "selector",
+    "k_fit": "constructor", "k_fit_group": "constructor", "k_select": "selector", "k_emit": "selector",
 }
 
 
@@ -138,7 +138,7 @@ def _short(name):
     n = name.replace("(anonymous namespace)::", "")
     if "neg_kernel" in n:
         return "copy_calib"
-    return n.split("(")[0].strip()
+    return n.split("(")[0].split("<")[0].split()[-1]  # "void k_fit_group<16, 1>": k_fit_group
 
 
 def _csv(pattern_dir, suffix):
@@ -177,7 +177,9 @@ def summarize_profiles(prof_dir, workload):
     Writes profiles/<workload>_kernels.txt and profiles/traffic.json."""
     out_dir = os.path.join(ROOT, "profiles")
     os.makedirs(out_dir, exist_ok=True)
-    stats = {_short(r["name"]): r for r in _csv(os.path.join(prof_dir, "trace"), "kernel_stats.csv")}
+    rows = _csv(os.path.join(prof_dir, "trace"), "kernel_stats.csv")
+    # of a template's instances the one that took most time
+    stats = {_short(r["name"]): r for r in sorted(rows, key=lambda r: float(r["totaldurationns"]))}
     fetch = _counter_means(os.path.join(prof_dir, "fetch"), "FETCH_SIZE")
     write = _counter_means(os.path.join(prof_dir, "write"), "WRITE_SIZE")
     gib_kib = float(1 << 20)
@@ -867,7 +869,7 @@ def merge_bench(dev, tr, batch, ev, reps, workload):
     a = np.nonzero(r["next"] >= 0)[0]
     b = r["next"][a]
     unit = res["unit"].cpu().numpy()
-    out = dict(workload=workload, tracks=n_tracks, ms_per_call=ms, tracks_per_s=n_tracks / (ms * 1e-3), launches=10,
+    out = dict(workload=workload, tracks=n_tracks, ms_per_call=ms, tracks_per_s=n_tracks / (ms * 1e-3), launches=9,
                pairs=r["n_pairs"], candidates=r["n_candidates"], links=r["n_links"],
                links_across_sectors=int((unit[a] != unit[b]).sum()),
                link_purity=float(((maj[a] == maj[b]) & (maj[a] >= 0)).mean()) if len(a) else None,
@@ -906,7 +908,7 @@ def merge_bench(dev, tr, batch, ev, reps, workload):
     g = p >= 0
     true_qpt = ev.tracks.q[p[g]] / ev.tracks.pt[p[g]]
     seg = rf.result(n_tracks, sync=False)["params"].cpu().numpy()
-    out["chain_fit"] = dict(ms_per_call=cms, chains=int(len(heads)), launches=8,
+    out["chain_fit"] = dict(ms_per_call=cms, chains=int(len(heads)), launches=7,
                             fitted_fraction=float(ok.mean()) if len(heads) else None,
                             hits=int(c["n_hits"][heads].sum()), chi2_per_ndf_median=float(np.median(chi2_ndf)) if len(h) else None,
                             qpt_rel_error_median=dict(chain=float(np.median(np.abs(c["params"][h][g, 4] / true_qpt - 1))),
@@ -970,7 +972,7 @@ def clusterizer_bench(dev, ev, reps, workload, cpu_units=2):
     oracle.clusterize(synth.PAD_HALF, sub_off, d.time[:n_sub], d.q[:n_sub], nu, 10, pw, tb, zoff)
     cpu_s = time.time() - t
     out = dict(workload=workload, digits=int(d.n), clusters=int(n_clusters), pads=int(n_pads),
-               ms_per_call=ms, digits_per_s=d.n / (ms * 1e-3), launches=4,
+               ms_per_call=ms, digits_per_s=d.n / (ms * 1e-3), launches=2,
                roofline=dict(bound="hbm", achieved=achieved, peak=HBM_PEAK_GBS, unit="GB/s",
                              frac=achieved / HBM_PEAK_GBS, algorithmic_bytes_per_launch=int(alg), traffic=None),
                cpu_oracle=dict(value=n_sub / cpu_s, unit="digits/s", cores=1,
