@@ -310,7 +310,6 @@ __global__ void __launch_bounds__(TPB) k_init(Args A) {
   }
   if (i < C_N && i != C_TILES) w.ctr[i] = 0;
   if (i < w.SB) w.sel_sum[i] = 0;
-  if (i < w.KB) w.blk_keep[i] = 0;
   if (i < 5) A.out.counts[i] = 0;
   if (blockIdx.x != 0) return;
   bool bad = false;
@@ -1296,43 +1295,38 @@ __global__ void __launch_bounds__(TPB) k_clean(Args A) {
   if (threadIdx.x == 0) w.blk[blockIdx.x] = tot;
 }
 
-// one-block exclusive scan of per-block counts; total into counters, capacity check
-__global__ void __launch_bounds__(1024) k_scan_blocks(int32_t *blk, int64_t nb, int64_t *ctr_total,
-                                                      int64_t *out_total, int64_t cap,
-                                                      int32_t *status, int32_t *blk2,
-                                                      int64_t *ctr_total2, int64_t *out_total2,
-                                                      int64_t cap2) {
+// One-block exclusive scan of nb per-block counts, or of the blocks of TPB
+// that *used elements fill; total into counters, capacity check.  (The seeds'
+// scan over all blocks the tracklets' capacity has, 45 k for 23 M clusters of
+// which 5 k are used, took 50 us, so 11.)
+__global__ void __launch_bounds__(1024) k_scan_blocks(int32_t *blk, int64_t nb, const int64_t *used, int64_t *ctr_total,
+                                                      int64_t *out_total, int64_t cap, int32_t *status) {
   __shared__ int tmp[16];
   if (*status != TPC_OK) return;
-  for (int which = 0; which < (blk2 ? 2 : 1); ++which) {
-    int32_t *b = which ? blk2 : blk;
-    int carry = 0;
-    constexpr int PER = 8;  // consecutive entries per thread, one block scan per 8192
-    for (int64_t base = 0; base < nb; base += 1024 * PER) {
-      const int64_t i0 = base + int64_t(threadIdx.x) * PER;
-      int v[PER], sum = 0;
+  if (used) nb = min(nb, (*used + TPB - 1) / TPB);
+  int carry = 0;
+  constexpr int PER = 8;  // consecutive entries per thread, one block scan per 8192
+  for (int64_t base = 0; base < nb; base += 1024 * PER) {
+    const int64_t i0 = base + int64_t(threadIdx.x) * PER;
+    int v[PER], sum = 0;
 #pragma unroll
-      for (int e = 0; e < PER; ++e) {
-        v[e] = i0 + e < nb ? b[i0 + e] : 0;
-        sum += v[e];
-      }
-      int tot;
-      int ex = carry + block_exclusive_scan<1024>(sum, tmp, &tot);
+    for (int e = 0; e < PER; ++e) {
+      v[e] = i0 + e < nb ? blk[i0 + e] : 0;
+      sum += v[e];
+    }
+    int tot;
+    int ex = carry + block_exclusive_scan<1024>(sum, tmp, &tot);
 #pragma unroll
-      for (int e = 0; e < PER; ++e) {
-        if (i0 + e < nb) b[i0 + e] = ex;
-        ex += v[e];
-      }
-      carry += tot;
+    for (int e = 0; e < PER; ++e) {
+      if (i0 + e < nb) blk[i0 + e] = ex;
+      ex += v[e];
     }
-    if (threadIdx.x == 0) {
-      int64_t *ct = which ? ctr_total2 : ctr_total;
-      int64_t *ot = which ? out_total2 : out_total;
-      const int64_t c = which ? cap2 : cap;
-      *ct = carry;
-      if (ot) *ot = carry;
-      if (carry > c) set_status(status, TPC_E_CAPACITY);
-    }
+    carry += tot;
+  }
+  if (threadIdx.x == 0) {
+    *ctr_total = carry;
+    *out_total = carry;
+    if (carry > cap) set_status(status, TPC_E_CAPACITY);
   }
 }
 
@@ -1503,7 +1497,7 @@ __global__ void __launch_bounds__(TPB) k_chains(Args A) {
     }
     int tot;
     block_exclusive_scan<TPB>(seed, tmp, &tot);
-    if (threadIdx.x == 0) w.blk_keep[b] = tot;  // chunks past the tracklets keep k_init's 0
+    if (threadIdx.x == 0) w.blk_keep[b] = tot;
   }
 }
 
@@ -2409,7 +2403,6 @@ int track_impl(const tpc_clusters_t *c, const tpc_geometry_t *g, const tpc_field
   };
   int64_t init_n = w.S > c->n ? w.S : (c->n > C_N ? c->n : int64_t(C_N));
   if (init_n < w.SB) init_n = w.SB;
-  if (init_n < w.KB) init_n = w.KB;
   mark();
   hipLaunchKernelGGL(k_init, dim3(blocks_for(init_n, TPB)), dim3(TPB), 0, st, A);
   if (c->n > 0) {
@@ -2431,17 +2424,15 @@ int track_impl(const tpc_clusters_t *c, const tpc_geometry_t *g, const tpc_field
     mark();
     hipLaunchKernelGGL(k_clean, dim3(unsigned(w.NB)), dim3(TPB), 0, st, A);
     mark();
-    hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(1024), 0, st, w.blk, w.NB, w.ctr + C_K,
-                       out->counts + 2, w.T_cap, out->status, (int32_t *)nullptr, (int64_t *)nullptr,
-                       (int64_t *)nullptr, int64_t(0));
+    hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(1024), 0, st, w.blk, w.NB, (const int64_t *)nullptr,
+                       w.ctr + C_K, out->counts + 2, w.T_cap, out->status);
     mark();
     hipLaunchKernelGGL(k_compact_starts, dim3(unsigned(w.NB)), dim3(TPB), 0, st, A);
     mark();
     hipLaunchKernelGGL(k_chains, dim3(unsigned(w.KB < CHAIN_BLOCKS ? w.KB : CHAIN_BLOCKS)), dim3(TPB), 0, st, A);
     mark();
-    hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(1024), 0, st, w.blk_keep, w.KB, w.ctr + C_SEEDS,
-                       out->counts + 4, w.S_cap, out->status, (int32_t *)nullptr, (int64_t *)nullptr,
-                       (int64_t *)nullptr, int64_t(0));
+    hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(1024), 0, st, w.blk_keep, w.KB, w.ctr + C_K,
+                       w.ctr + C_SEEDS, out->counts + 4, w.S_cap, out->status);
     mark();
     hipLaunchKernelGGL(k_compact_seeds, dim3(unsigned(w.KB < CHAIN_BLOCKS ? w.KB : CHAIN_BLOCKS)), dim3(TPB), 0,
                        st, A);
