@@ -357,35 +357,49 @@ __global__ void __launch_bounds__(TPB) k_tile_hist(Args A) {
   const int u = unit_of_tile(w.unit_tiles, A.n_units, b);
   const int64_t beg = A.off[u] + int64_t(b - w.unit_tiles[u]) * TILE;
   const int64_t end = min(beg + TILE, A.off[u + 1]);
-  for (int r = threadIdx.x; r < 256; r += TPB) {
-    cnt[r] = 0;
-    zmn[r] = INT32_MAX;
-    zmx[r] = INT32_MIN;
+  for (int q = threadIdx.x; q < 256; q += TPB) {
+    cnt[q] = 0;
+    zmn[q] = INT32_MAX;
+    zmx[q] = INT32_MIN;
   }
   __syncthreads();
   bool bad = false;
-  for (int64_t i = beg + threadIdx.x; i < end; i += TPB) {
-    const int r = A.row[i];
-    const float yf = A.y[i], zf = A.z[i];
-    if (r >= A.n_rows || !(fabsf(yf) <= 8192.f) || !(fabsf(zf) <= 8192.f)) {
+  // the thread's hits all on their way before the first is counted (one after
+  // the other 117 us for 25 M clusters, so 99)
+  constexpr int PER = TILE / TPB;
+  int r[PER];
+  float y[PER], z[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int64_t i = beg + threadIdx.x + k * TPB;
+    if (i < end) {
+      r[k] = A.row[i];
+      y[k] = A.y[i];
+      z[k] = A.z[i];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    if (beg + threadIdx.x + k * TPB >= end) break;
+    if (r[k] >= A.n_rows || !(fabsf(y[k]) <= 8192.f) || !(fabsf(z[k]) <= 8192.f)) {
       bad = true;
       continue;
     }
-    const int Z = quant(zf);
-    atomicAdd(&cnt[r], 1);
-    atomicMin(&zmn[r], Z);
-    atomicMax(&zmx[r], Z);
+    const int Z = quant(z[k]);
+    atomicAdd(&cnt[r[k]], 1);
+    atomicMin(&zmn[r[k]], Z);
+    atomicMax(&zmx[r[k]], Z);
   }
   if (bad) set_status(A.out.status, TPC_E_INVALID);
   __syncthreads();
-  for (int r = threadIdx.x; r < A.n_rows; r += TPB) {
-    const int c = cnt[r];
-    w.tile_hist[int64_t(r) * w.T_max + b] = c;
+  for (int q = threadIdx.x; q < A.n_rows; q += TPB) {
+    const int c = cnt[q];
+    w.tile_hist[int64_t(q) * w.T_max + b] = c;
     if (c) {
-      const int64_t s = int64_t(u) * A.n_rows + r;
+      const int64_t s = int64_t(u) * A.n_rows + q;
       atomicAdd(&w.seg_cnt[s], c);
-      atomicMin(&w.seg_zmin[s], zmn[r]);
-      atomicMax(&w.seg_zmax[s], zmx[r]);
+      atomicMin(&w.seg_zmin[s], zmn[q]);
+      atomicMax(&w.seg_zmax[s], zmx[q]);
     }
   }
 }
