@@ -1481,7 +1481,12 @@ __global__ void __launch_bounds__(TPB) k_chains(Args A) {
   if (*A.out.status != TPC_OK) return;
   const int64_t n_trk = w.ctr[C_K];
   const int64_t n_chunks = (n_trk + TPB - 1) / TPB;
-  for (int64_t b = blockIdx.x; b < n_chunks; b += gridDim.x) {
+  // Neighbouring tracklets share the cache lines of their links, so each XCD
+  // takes one contiguous range of them (50 collisions: 172 us; dealt to the
+  // XCDs in turn 310).
+  for (int64_t k = blockIdx.x; k < ((n_chunks + 7) & ~int64_t(7)); k += gridDim.x) {
+    const int64_t b = xcd_chunk(k, n_chunks);
+    if (b >= n_chunks) continue;  // block-uniform
     const int64_t t = b * TPB + threadIdx.x;
     int seed = 0;
     if (t < n_trk) {
@@ -2443,7 +2448,7 @@ int track_impl(const tpc_clusters_t *c, const tpc_geometry_t *g, const tpc_field
     mark();
     hipLaunchKernelGGL(k_compact_starts, dim3(unsigned(w.NB)), dim3(TPB), 0, st, A);
     mark();
-    hipLaunchKernelGGL(k_chains, dim3(unsigned(w.KB < CHAIN_BLOCKS ? w.KB : CHAIN_BLOCKS)), dim3(TPB), 0, st, A);
+    hipLaunchKernelGGL(k_chains, dim3(round8(w.KB < CHAIN_BLOCKS ? w.KB : CHAIN_BLOCKS)), dim3(TPB), 0, st, A);
     mark();
     hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(1024), 0, st, w.blk_keep, w.KB, w.ctr + C_K,
                        w.ctr + C_SEEDS, out->counts + 4, w.S_cap, out->status);
