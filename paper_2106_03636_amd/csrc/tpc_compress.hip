@@ -18,12 +18,12 @@
 // half of what it can take, when each of a state's six floats was loaded by
 // itself and the rest of its line had left the L1 in between).  The parameters
 // are therefore one 16-byte and one 4-byte load, and four clusters' states are
-// on their way together; 24 M clusters take 363 us instead of 540 (one cluster
-// a thread with the wide load: 392; four with the narrow ones: 516 - 784).
+// on their way together: 24 M clusters 363 us instead of 540 (one cluster a
+// thread with the wide load: 392; four with the narrow ones: 516 - 784), and
+// with each XCD on a contiguous range 343.
 // Each block adds its residuals to the same few hundred histogram bins, one
-// after the other: 512 blocks.  1024 cost more (374; with 1 M clusters 50 us
-// against 42), 256 leave too few loads in flight (361 with 512 threads each,
-// 23 against 22 us for 0.2 M).
+// after the other: 512 blocks.  1024 cost more (374 against 363; with 1 M
+// clusters 50 us against 42), 256 leave too few loads in flight.
 
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -190,8 +190,13 @@ __global__ void __launch_bounds__(TPB) k_cmp_codes(CmpArgs A) {
   const int64_t T = A.trk_counts[0];
   int32_t n[6] = {0, 0, 0, 0, 0, 0};
   const int64_t quads = A.n / PER;
-  for (int64_t i = int64_t(blockIdx.x) * TPB + threadIdx.x; i < quads; i += int64_t(gridDim.x) * TPB)
-    codes<PER>(A, i * PER, T, row_x, hy, hz, n);
+  // a unit's clusters share its tracks' states, so each XCD (blocks go to the
+  // eight in turn) takes one contiguous range
+  const int64_t turns = (quads + TPB - 1) / TPB, n8 = (turns + 7) & ~int64_t(7);
+  for (int64_t k = blockIdx.x; k < n8; k += gridDim.x) {
+    const int64_t i = ((k & 7) * (n8 >> 3) + (k >> 3)) * TPB + threadIdx.x;
+    if (i < quads) codes<PER>(A, i * PER, T, row_x, hy, hz, n);
+  }
   if (PER > 1 && blockIdx.x == 0 && quads * PER + threadIdx.x < A.n)
     codes<1>(A, quads * PER + threadIdx.x, T, row_x, hy, hz, n);
 #pragma unroll
@@ -254,7 +259,7 @@ extern "C" int tpc_compress(const tpc_clusters_t *clusters, const tpc_geometry_t
   const bool aligned = (quad & 15) == 0 && (reinterpret_cast<uintptr_t>(A.row) & 7) == 0 &&
                        (reinterpret_cast<uintptr_t>(A.cls) & 3) == 0;
   const int64_t per = aligned ? 4 : 1, cb = (A.n / per + TPB - 1) / TPB;
-  const unsigned blocks = unsigned(cb < 1 ? 1 : (cb > CMP_BLOCKS ? CMP_BLOCKS : cb));
+  const unsigned blocks = (unsigned(cb < 1 ? 1 : (cb > CMP_BLOCKS ? CMP_BLOCKS : cb)) + 7u) & ~7u;
   const unsigned lds = unsigned(sizeof(int32_t)) * (4 * unsigned(A.hh) + unsigned(A.n_rows));
   hipLaunchKernelGGL(k_cmp_init, dim3(unsigned(ib)), dim3(TPB), 0, st, A);
   if (aligned)
