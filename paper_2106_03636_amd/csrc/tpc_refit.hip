@@ -677,7 +677,8 @@ __global__ void __launch_bounds__(TPB) k_ch_len(ChArgs A) {
         to += A.n_hits[q];
         const int u = A.unit[q];
         float c = SAME_FRAME, sn = 0.f;
-        if (before >= 0 && u != from && u >= 0 && u < A.n_units) {
+        // the segments' units may be out of range (their own threads report it): neither is then looked up
+        if (before >= 0 && u != from && min(u, from) >= 0 && max(u, from) < A.n_units) {
           const float d = frame_turn(A, from, u);  // back again it is -d: remainder, sine and cosine are odd or even
           c = cosf(d);
           sn = sinf(d);
