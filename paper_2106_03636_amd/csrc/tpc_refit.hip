@@ -732,7 +732,7 @@ __device__ uint64_t walk_to(const ChArgs &A, int32_t head, int j) {
 // The records of every track's hits, a wave per track (each XCD a contiguous
 // range of the tracks, as in k_rf_gather): checked, and those of chain
 // segments written at their places.  Hits that belong to no track are checked
-// too, where the lists leave any.
+// too, where the lists leave any: with no track at all, every hit.
 __global__ void __launch_bounds__(TPB) k_ch_gather(ChArgs A) {
   constexpr int WAVES = TPB / 64;
   if (*A.status != TPC_OK) return;
@@ -740,7 +740,7 @@ __global__ void __launch_bounds__(TPB) k_ch_gather(ChArgs A) {
   const int64_t H = A.trk_counts[1] < A.cap_hits ? A.trk_counts[1] : A.cap_hits;
   const int lane = __lane_id();
   const bool room = !crowded(A);
-  if (A.bad[2])
+  if (A.bad[2] || T == 0)
     for (int64_t i = int64_t(blockIdx.x) * TPB + threadIdx.x; i < H; i += int64_t(gridDim.x) * TPB) record_of(A, A.hits[i]);
   xcd_chunks((T + WAVES - 1) / WAVES, [&](int64_t c) {
     const int64_t t = c * WAVES + (threadIdx.x >> 6);

@@ -24,3 +24,15 @@ def test_chain_segments_of_units_out_of_range(unit):
     ev, dt = _three(unit)
     print("case chain units", unit, flush=True)
     assert G._chain_status(ev, dt, [1, 2, -1], [-1, 0, 1], [0.0]) == T.TPC_E_INVALID
+
+
+@pytest.mark.parametrize("n_tracks", [0, 1, 3])
+def test_hits_of_no_track_are_checked(n_tracks):
+    """A hit naming no cluster is an error whether the call's tracks hold it or not, also when there are no tracks."""
+    import paper_2106_03636_amd as T
+    import test_gpu_merge as G
+    for hits, want in ((range(6), 0), ([0, 1, 2, 3, 4, 99], T.TPC_E_INVALID), ([0, 1, 2, 3, -1, 5], T.TPC_E_INVALID)):
+        ev, dt = _three(hits=hits)
+        dt.counts[0] = n_tracks
+        print("case chain hits", n_tracks, list(hits), flush=True)
+        assert G._chain_status(ev, dt, [-1, -1, -1], [-1, -1, -1], [0.0]) == want
