@@ -259,7 +259,7 @@ struct Runs {
     }
   }
   // loads records [CHUNK c, CHUNK c + CHUNK) of every run; the last piece of a
-  // run may read one record past it (the array is padded)
+  // run may read one record past it (see Layout)
   __device__ __forceinline__ void load(int c) const {
     uint64_t *to = buf + (c & 1) * (64 * CHUNK);
 #pragma unroll
@@ -369,19 +369,37 @@ __global__ void __launch_bounds__(FTB) k_rf_fit(RfArgs A) {
   }
 }
 
-constexpr size_t REC_PAD = 256;  // bytes past the hit records that their 16-byte loads may touch
-
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
+
+// The workspace of a refit, and behind it the arrays that only the chain fit
+// uses.  The 16-byte loads of the hit records may touch one record past the
+// last: the order follows them, which is never empty where there are records
+// to load.
+struct Layout {
+  size_t cl, rec, order, refit;                // refit: where a refit's arrays end
+  size_t dst, next_side, prev_side, chains;    // chains: where the chain fit's end
+};
+Layout layout(int64_t n_clusters, int64_t cap_tracks, int64_t cap_hits) {
+  const size_t tracks = size_t(cap_tracks);
+  Layout L;
+  L.cl = align256(NB * 4 + 256);  // after the length buckets and the flags
+  L.rec = L.cl + align256(size_t(n_clusters) * 8);
+  L.order = L.rec + align256(size_t(cap_hits) * 8);
+  L.refit = L.dst = L.order + align256(tracks * 4);
+  L.next_side = L.dst + align256(tracks * 4);
+  L.prev_side = L.next_side + align256(tracks * 16);
+  L.chains = L.prev_side + align256(tracks * 16);
+  return L;
+}
+bool layout_ok(int64_t n_clusters, int64_t cap_tracks, int64_t cap_hits) {
+  return n_clusters >= 0 && n_clusters < (int64_t(1) << 30) && cap_tracks >= 0 && cap_hits >= 0 &&
+         cap_tracks <= (int64_t(1) << 31) && cap_hits <= (int64_t(1) << 31);
+}
 
 }  // namespace
 
 extern "C" size_t tpc_refit_workspace_size(int64_t n_clusters, int64_t cap_tracks, int64_t cap_hits) {
-  if (n_clusters < 0 || n_clusters >= (int64_t(1) << 30) || cap_tracks < 0 || cap_hits < 0 ||
-      cap_tracks > (int64_t(1) << 31) || cap_hits > (int64_t(1) << 31))
-    return 0;
-  return align256(NB * 4 + 256) + align256(size_t(cap_tracks) * 4) + align256(size_t(n_clusters) * 8) +
-         align256(size_t(cap_hits) * 8 + REC_PAD) + align256(size_t(cap_tracks) * 4) +
-         2 * align256(size_t(cap_tracks) * 16);
+  return layout_ok(n_clusters, cap_tracks, cap_hits) ? layout(n_clusters, cap_tracks, cap_hits).chains : 0;
 }
 
 extern "C" int tpc_refit_tracks(const tpc_clusters_t *clusters, const tpc_geometry_t *geometry,
@@ -403,10 +421,10 @@ extern "C" int tpc_refit_tracks(const tpc_clusters_t *clusters, const tpc_geomet
   if (!out->params || !out->cov || !out->x_ref || !out->chi2 || !out->params_out || !out->cov_out ||
       !out->x_out || !out->ok || !out->status)
     return TPC_E_INVALID;
-  const size_t need = tpc_refit_workspace_size(clusters->n, tracks->cap_tracks, tracks->cap_hits);
-  if (need == 0) return TPC_E_INVALID;
+  if (!layout_ok(clusters->n, tracks->cap_tracks, tracks->cap_hits)) return TPC_E_INVALID;
+  const Layout L = layout(clusters->n, tracks->cap_tracks, tracks->cap_hits);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255)) return TPC_E_INVALID;
-  if (workspace_bytes < need) return TPC_E_NOMEM;
+  if (workspace_bytes < L.refit) return TPC_E_NOMEM;
   RfArgs A;
   A.y = clusters->y;
   A.z = clusters->z;
@@ -438,12 +456,9 @@ extern "C" int tpc_refit_tracks(const tpc_clusters_t *clusters, const tpc_geomet
   char *w = static_cast<char *>(workspace);
   A.bucket = reinterpret_cast<int32_t *>(w);
   A.bad = A.bucket + NB;
-  w += align256(NB * 4 + 256);
-  A.order = reinterpret_cast<int32_t *>(w);
-  w += align256(size_t(tracks->cap_tracks) * 4);
-  A.cl = reinterpret_cast<uint64_t *>(w);
-  w += align256(size_t(clusters->n) * 8);
-  A.rec = reinterpret_cast<uint64_t *>(w);
+  A.cl = reinterpret_cast<uint64_t *>(w + L.cl);
+  A.rec = reinterpret_cast<uint64_t *>(w + L.rec);
+  A.order = reinterpret_cast<int32_t *>(w + L.order);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t tb = (tracks->cap_tracks + TPB - 1) / TPB;
   const int64_t hb = (tracks->cap_hits + TPB * GATHER_PER - 1) / (TPB * GATHER_PER);
@@ -904,10 +919,10 @@ extern "C" int tpc_fit_chains(const tpc_clusters_t *clusters, const tpc_geometry
     if (!(params->cov0[q] > 0.f) || !isfinite(params->cov0[q])) return TPC_E_INVALID;
   if (!out->params || !out->cov || !out->x_ref || !out->chi2 || !out->n_hits || !out->ok || !out->status)
     return TPC_E_INVALID;
-  const size_t need = tpc_refit_workspace_size(clusters->n, tracks->cap_tracks, tracks->cap_hits);
-  if (need == 0) return TPC_E_INVALID;
+  if (!layout_ok(clusters->n, tracks->cap_tracks, tracks->cap_hits)) return TPC_E_INVALID;
+  const Layout L = layout(clusters->n, tracks->cap_tracks, tracks->cap_hits);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255)) return TPC_E_INVALID;
-  if (workspace_bytes < need) return TPC_E_NOMEM;
+  if (workspace_bytes < L.chains) return TPC_E_NOMEM;
   // the refit's workspace layout; its pack and gather fill the hit records
   char *w = static_cast<char *>(workspace);
   RfArgs R{};
@@ -927,12 +942,9 @@ extern "C" int tpc_fit_chains(const tpc_clusters_t *clusters, const tpc_geometry
   R.status = out->status;
   R.bucket = reinterpret_cast<int32_t *>(w);
   R.bad = R.bucket + NB;
-  w += align256(NB * 4 + 256);
-  R.order = reinterpret_cast<int32_t *>(w);
-  w += align256(size_t(tracks->cap_tracks) * 4);
-  R.cl = reinterpret_cast<uint64_t *>(w);
-  w += align256(size_t(clusters->n) * 8);
-  R.rec = reinterpret_cast<uint64_t *>(w);
+  R.cl = reinterpret_cast<uint64_t *>(w + L.cl);
+  R.rec = reinterpret_cast<uint64_t *>(w + L.rec);
+  R.order = reinterpret_cast<int32_t *>(w + L.order);
   ChArgs A;
   A.y = clusters->y;
   A.z = clusters->z;
@@ -967,12 +979,10 @@ extern "C" int tpc_fit_chains(const tpc_clusters_t *clusters, const tpc_geometry
   A.status = out->status;
   A.cl = R.cl;
   A.rec = R.rec;
-  w += align256(size_t(tracks->cap_hits) * 8 + REC_PAD);
-  A.dst = reinterpret_cast<int32_t *>(w);
-  w += align256(size_t(tracks->cap_tracks) * 4);
-  A.next_side = reinterpret_cast<Side *>(w);
-  w += align256(size_t(tracks->cap_tracks) * sizeof(Side));
-  A.prev_side = reinterpret_cast<Side *>(w);
+  static_assert(sizeof(Side) == 16, "as laid out");
+  A.dst = reinterpret_cast<int32_t *>(w + L.dst);
+  A.next_side = reinterpret_cast<Side *>(w + L.next_side);
+  A.prev_side = reinterpret_cast<Side *>(w + L.prev_side);
   A.order = R.order;
   A.bucket = R.bucket;
   A.bad = R.bad;
