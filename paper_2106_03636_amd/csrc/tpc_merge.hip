@@ -526,8 +526,8 @@ struct Reach {
   int32_t plain;  // the first look's bound holds (|sin(phi)| well below 1)
 
   // Whether the record cannot pass the z' and y windows: their test in FP32,
-  // with margins above its error.  x and y up to 8192 cm round by 5e-4 cm, z'
-  // differences by as much; for |C| < 0.05 / cm that puts sin(phi) off by less
+  // with margins above its error.  The state's x and y, up to 8192 cm, round by
+  // 5e-4 cm, z' differences by as much; for |C| < 0.05 / cm that puts sin(phi) off by less
   // than 3e-5 and, where it is below 0.96 at both ends (tan < 3.5), the
   // carried y by less than 3e-3 cm and 6e-4 dx.  Anything else, NaN too, is
   // left to the exact test.  (Most segments of low-pT particles end where
@@ -606,7 +606,7 @@ __device__ __forceinline__ void scan_unit(const MgArgs &A, WaveScan &L, int64_t 
       r.s = float(q[2]);
       r.C = float(A.k * q[4]);
       r.c = __builtin_amdgcn_sqrtf(fmaxf(0.f, 1.f - r.s * r.s));
-      r.plain = fabsf(r.s) < 0.96f && fabsf(r.C) < 0.05f;
+      r.plain = fabsf(r.s) < 0.96f && fabsf(r.C) < 0.05f && fabsf(r.x) <= 8192.f && fabsf(r.y) <= 8192.f;
     }
   }
   const float dz = float(A.dz_max) * 1.000001f + 2e-3f, dy = float(A.dy_max) * 1.000001f + 6e-3f, smx = float(A.smx) + 1e-4f;
