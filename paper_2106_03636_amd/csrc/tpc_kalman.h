@@ -54,15 +54,25 @@ __device__ __forceinline__ float div_by(float a, float b, float rb) {  // a / b,
 __device__ __forceinline__ bool is_mid(float x) { return fabsf(x) > 1e-25f && fabsf(x) < 1e25f; }
 
 __device__ __forceinline__ float asin_over(float u) {  // asin(u)/u
+#pragma clang fp contract(off)
   const float u2 = u * u;
-  if (u < 0.03f) return 1.f + u2 * (1.f / 6.f + u2 * (3.f / 40.f));
+  if (u < 0.03f) return fmaf(u2, fmaf(u2, 3.f / 40.f, 1.f / 6.f), 1.f);
   return asinf(u) / u;
 }
 __device__ __forceinline__ float asin_over_dd(float u) {  // (d/du asin(u)/u) / u
+#pragma clang fp contract(off)
   const float u2 = u * u;
-  if (u < 0.2f) return 1.f / 3.f + u2 * (0.3f + u2 * (15.f / 56.f + u2 * (35.f / 144.f)));
+  if (u < 0.2f) return fmaf(u2, fmaf(u2, fmaf(u2, 35.f / 144.f, 15.f / 56.f), 0.3f), 1.f / 3.f);
   return (u / sqrtf(1.f - u2) - asinf(u)) / (u2 * u);
 }
+
+// How the transport, the update and the seed round is written out: contraction
+// is off and each FMA is named.  Left to the compiler, which product of a sum
+// enters an FMA depends on what surrounds the inlined code, and the tracklet
+// fit alone compiles it into six bodies, chosen by the size of the batch: a
+// unit's fit may not depend on what else the batch holds.  The forms are those
+// the compiler had taken for all six (so at i == 1 below, where q0[1] * I01 is
+// also a product of K0[0]).
 
 // Transport of the state to a plane x2, parameter part; kept so that the
 // covariance part can follow once a hit is found in that row.
@@ -74,18 +84,19 @@ struct Step {
 // ROWS: the two planes are pad rows of one geometry (1 .. 8192 cm, apart).
 template <bool ROWS = false, class S>
 __device__ __forceinline__ bool step_prepare(const S &s, float x2, float k, float sinmax, Step &t) {
+#pragma clang fp contract(off)
   t.dx = x2 - s.x;
   t.C = k * s.p[4];
   t.s1 = s.p[2];
-  t.s2 = t.s1 + t.C * t.dx;
+  t.s2 = fmaf(t.C, t.dx, t.s1);
   if (!(fabsf(t.s1) < sinmax) || !(fabsf(t.s2) < sinmax)) return false;
-  t.c1 = sqrt_n(1.f - t.s1 * t.s1, t.r1);  // 1 - sinmax^2 or more
-  t.c2 = sqrt_n(1.f - t.s2 * t.s2, t.r2);
+  t.c1 = sqrt_n(fmaf(-t.s1, t.s1, 1.f), t.r1);  // 1 - sinmax^2 or more
+  t.c2 = sqrt_n(fmaf(-t.s2, t.s2, 1.f), t.r2);
   t.D = t.c1 + t.c2;
   t.N = t.s1 + t.s2;
   t.iD = rcp_n(t.D);
   t.dy = t.dx * t.N * t.iD;
-  const float LL = t.dx * t.dx + t.dy * t.dy;
+  const float LL = fmaf(t.dx, t.dx, t.dy * t.dy);
   if (ROWS || is_mid(LL)) {
     t.L = sqrt_n(LL, t.rL);
   } else {  // planes that (nearly) coincide
@@ -100,26 +111,37 @@ __device__ __forceinline__ bool step_prepare(const S &s, float x2, float k, floa
   return true;
 }
 
+// The position a prepared step leads to.
+template <class S>
+__device__ __forceinline__ float y_after(const S &s, const Step &t) {
+  return s.p[0] + t.dy;
+}
+template <class S>
+__device__ __forceinline__ float z_after(const S &s, const Step &t) {
+  return fmaf(s.p[3], t.sT, s.p[1]);
+}
+
 // Apply a prepared step: parameters, and the covariance through the analytic
 // Jacobian.
 template <class S>
 __device__ __forceinline__ void step_apply(S &s, const Step &t, float x2, float k) {
+#pragma clang fp contract(off)
   const float dx = t.dx, s1 = t.s1, s2 = t.s2, c1 = t.c1, c2 = t.c2, D = t.D, N = t.N, iD = t.iD;
   const float dy = t.dy, L = t.L, u = t.u, fu = t.fu, sT = t.sT, sg = t.sg, C = t.C;
   const float tgl = s.p[3];
   const float iD2 = iD * iD;
   const float i2 = refine_rcp(c2, t.r2);
-  const float a = dx * (2.f * D + N * (div_by(s1, c1, refine_rcp(c1, t.r1)) + div_by(s2, c2, i2))) * iD2;
+  const float a = dx * fmaf(2.f, D, N * (div_by(s1, c1, refine_rcp(c1, t.r1)) + div_by(s2, c2, i2))) * iD2;
   const float b = dx * k * dx * (D + div_by(N * s2, c2, i2)) * iD2;
   const float g = asin_over_dd(u);
-  const float dsdy = L > 0.f ? sg * div_by(dy, L, refine_rcp(L, t.rL)) * (fu + u * u * g) : 0.f;
+  const float dsdy = L > 0.f ? sg * div_by(dy, L, refine_rcp(L, t.rL)) * fmaf(u * u, g, fu) : 0.f;
   const float dsdC = sg * C * L * L * L * g * 0.25f;
   const float cc = tgl * dsdy * a;
   const float d = sT;
-  const float e = tgl * (dsdy * b + dsdC * k);
+  const float e = tgl * fmaf(dsdC, k, dsdy * b);
   const float f = k * dx;
   s.p[0] += dy;
-  s.p[1] += tgl * sT;
+  s.p[1] = fmaf(tgl, sT, s.p[1]);
   s.p[2] = s2;
   s.x = x2;
   // cov <- F cov F^T, F = I + {(0,2)=a, (0,4)=b, (1,2)=cc, (1,3)=d, (1,4)=e, (2,4)=f}
@@ -127,36 +149,41 @@ __device__ __forceinline__ void step_apply(S &s, const Step &t, float x2, float 
               P22 = cv(s, 5), P30 = cv(s, 6), P31 = cv(s, 7), P32 = cv(s, 8), P33 = cv(s, 9),
               P40 = cv(s, 10), P41 = cv(s, 11), P42 = cv(s, 12), P43 = cv(s, 13), P44 = cv(s, 14);
   // T = F P, rows 0..2
-  const float T00 = P00 + a * P20 + b * P40, T02 = P20 + a * P22 + b * P42,
-              T04 = P40 + a * P42 + b * P44;
-  const float T10 = P10 + cc * P20 + d * P30 + e * P40, T11 = P11 + cc * P21 + d * P31 + e * P41,
-              T12 = P21 + cc * P22 + d * P32 + e * P42, T13 = P31 + cc * P32 + d * P33 + e * P43,
-              T14 = P41 + cc * P42 + d * P43 + e * P44;
-  const float T20 = P20 + f * P40, T21 = P21 + f * P41, T22 = P22 + f * P42, T23 = P32 + f * P43,
-              T24 = P42 + f * P44;
-  cv(s, 0) = T00 + a * T02 + b * T04;
-  cv(s, 1) = T10 + a * T12 + b * T14;
-  cv(s, 2) = T11 + cc * T12 + d * T13 + e * T14;
-  cv(s, 3) = T20 + a * T22 + b * T24;
-  cv(s, 4) = T21 + cc * T22 + d * T23 + e * T24;
-  cv(s, 5) = T22 + f * T24;
-  cv(s, 6) = P30 + a * P32 + b * P43;
-  cv(s, 7) = P31 + cc * P32 + d * P33 + e * P43;
-  cv(s, 8) = P32 + f * P43;
-  cv(s, 10) = P40 + a * P42 + b * P44;
-  cv(s, 11) = P41 + cc * P42 + d * P43 + e * P44;
-  cv(s, 12) = P42 + f * P44;
+  const float T00 = fmaf(b, P40, fmaf(a, P20, P00));
+  const float T02 = fmaf(b, P42, fmaf(a, P22, P20));
+  const float T04 = fmaf(b, P44, fmaf(a, P42, P40));
+  const float T10 = fmaf(e, P40, fmaf(d, P30, fmaf(cc, P20, P10)));
+  const float T11 = fmaf(e, P41, fmaf(d, P31, fmaf(cc, P21, P11)));
+  const float T12 = fmaf(e, P42, fmaf(d, P32, fmaf(cc, P22, P21)));
+  const float T13 = fmaf(e, P43, fmaf(d, P33, fmaf(cc, P32, P31)));
+  const float T14 = fmaf(e, P44, fmaf(d, P43, fmaf(cc, P42, P41)));
+  const float T20 = fmaf(f, P40, P20);
+  const float T21 = fmaf(f, P41, P21);
+  const float T22 = fmaf(f, P42, P22);
+  const float T23 = fmaf(f, P43, P32);
+  const float T24 = fmaf(f, P44, P42);
+  cv(s, 0) = fmaf(b, T04, fmaf(a, T02, T00));
+  cv(s, 1) = fmaf(b, T14, fmaf(a, T12, T10));
+  cv(s, 2) = fmaf(e, T14, fmaf(d, T13, fmaf(cc, T12, T11)));
+  cv(s, 3) = fmaf(b, T24, fmaf(a, T22, T20));
+  cv(s, 4) = fmaf(e, T24, fmaf(d, T23, fmaf(cc, T22, T21)));
+  cv(s, 5) = fmaf(f, T24, T22);
+  cv(s, 6) = fmaf(b, P43, fmaf(a, P32, P30));
+  cv(s, 7) = fmaf(e, P43, fmaf(d, P33, fmaf(cc, P32, P31)));
+  cv(s, 8) = fmaf(f, P43, P32);
+  cv(s, 10) = fmaf(b, P44, fmaf(a, P42, P40));
+  cv(s, 11) = fmaf(e, P44, fmaf(d, P43, fmaf(cc, P42, P41)));
+  cv(s, 12) = fmaf(f, P44, P42);
 }
 
-// Z_FUSED: of a sum of two products with the residuals, the z one enters the
-// FMA unrounded and the y one rounded, instead of as the compiler likes (which
-// is the other way round in the tracklet fit and the refit, and depends on
-// what surrounds the update); the chain fit asks for it.
+// The measurement of residuals (r0, r1).  Z_FUSED: which product of a sum of
+// two with the residuals enters the FMA unrounded, the y one's or the z one's
+// (the chain fit's).
 template <bool Z_FUSED = false, class S>
-__device__ __forceinline__ void kf_update(S &s, float my, float mz, float sy2, float sz2) {
-  const float r0 = my - s.p[0], r1 = mz - s.p[1];
+__device__ __forceinline__ void kf_update(S &s, float r0, float r1, float sy2, float sz2) {
+#pragma clang fp contract(off)
   const float S00 = cv(s, 0) + sy2, S01 = cv(s, 1), S11 = cv(s, 2) + sz2;
-  const float det = S00 * S11 - S01 * S01;
+  const float det = fmaf(S00, S11, -(S01 * S01));
   const float idet = is_mid(det) ? rcp_n(det) : 1.f / det;
   const float I00 = S11 * idet, I01 = -S01 * idet, I11 = S00 * idet;
   // columns 0 and 1 of P (P_i0, P_i1)
@@ -165,19 +192,21 @@ __device__ __forceinline__ void kf_update(S &s, float my, float mz, float sy2, f
   float K0[5], K1[5];
 #pragma unroll
   for (int i = 0; i < 5; ++i) {
-    K0[i] = q0[i] * I00 + q1[i] * I01;
-    K1[i] = q0[i] * I01 + q1[i] * I11;
-    s.p[i] += Z_FUSED ? fmaf(K1[i], r1, K0[i] * r0) : K0[i] * r0 + K1[i] * r1;
+    K0[i] = fmaf(q0[i], I00, q1[i] * I01);
+    K1[i] = i == 1 ? fmaf(q1[i], I11, q0[i] * I01) : fmaf(q0[i], I01, q1[i] * I11);
   }
   int k = 0;
 #pragma unroll
   for (int i = 0; i < 5; ++i)
 #pragma unroll
-    for (int j = 0; j <= i; ++j, ++k) cv(s, k) -= K0[i] * q0[j] + K1[i] * q1[j];
+    for (int j = 0; j <= i; ++j, ++k) cv(s, k) -= fmaf(K0[i], q0[j], K1[i] * q1[j]);
+  // after the covariance: the row loop of k_fit then needs no scratch (before it, 50 collisions took 8.25 ms for 8.13)
+#pragma unroll
+  for (int i = 0; i < 5; ++i) s.p[i] += Z_FUSED ? fmaf(K1[i], r1, K0[i] * r0) : fmaf(K0[i], r0, K1[i] * r1);
   if (Z_FUSED)
     s.chi2 += fmaf(r0, fmaf(r1, I01, r0 * I00), r1 * fmaf(r1, I11, r0 * I01));
   else
-    s.chi2 += r0 * (I00 * r0 + I01 * r1) + r1 * (I01 * r0 + I11 * r1);
+    s.chi2 += fmaf(r0, fmaf(I00, r0, I01 * r1), r1 * fmaf(I01, r0, I11 * r1));
 }
 
 template <class S>
@@ -194,7 +223,14 @@ __device__ __forceinline__ void cov_reset(S &s, const float *cov0) {
 // measurement of hit h relative to the reference (exact: integer difference)
 template <bool Z_FUSED = false, class S>
 __device__ __forceinline__ void upd_hit(S &s, int2 yz, int Yr, int Zr, float sy2, float sz2) {
-  kf_update<Z_FUSED>(s, float(yz.x - Yr) * (1.f / 256.f), float(yz.y - Zr) * (1.f / 256.f), sy2, sz2);
+  kf_update<Z_FUSED>(s, fmaf(float(yz.x - Yr), 1.f / 256.f, -s.p[0]), fmaf(float(yz.y - Zr), 1.f / 256.f, -s.p[1]), sy2, sz2);
+}
+
+// Length of (x, y); X_FUSED: which of the squares enters the FMA unrounded.
+template <bool X_FUSED>
+__device__ __forceinline__ float chord(float x, float y) {
+#pragma clang fp contract(off)
+  return sqrtf(X_FUSED ? fmaf(x, x, y * y) : fmaf(y, y, x * x));
 }
 
 // Three-point seed: the circle through (x0, 0), (x1, y1), (x2, y2) gives the
@@ -203,17 +239,18 @@ __device__ __forceinline__ void upd_hit(S &s, int2 yz, int Yr, int Zr, float sy2
 // relative to the first point.  The state starts at x0 with the diagonal
 // covariance cov0.  False when the points are not distinct, the circle cannot
 // join them or |sin(phi)| reaches smx.
-template <class S>
+template <bool X_FUSED = false, class S>
 __device__ __forceinline__ bool seed3(S &s, float x0, float x1, float x2, float y1, float y2, float z2,
                                       float k, float smx, const float *cov0) {
+#pragma clang fp contract(off)
   const float ax = x1 - x0, ay = y1, bx = x2 - x0, by = y2, cx = x2 - x1, cy = y2 - y1;
-  const float d12 = sqrtf(ax * ax + ay * ay), d13 = sqrtf(bx * bx + by * by), d23 = sqrtf(cx * cx + cy * cy);
+  const float d12 = chord<X_FUSED>(ax, ay), d13 = chord<X_FUSED>(bx, by), d23 = chord<X_FUSED>(cx, cy);
   bool ok = d12 > 0.f && d13 > 0.f && d23 > 0.f;
-  const float C = ok ? 2.f * (ax * by - ay * bx) / (d12 * d13 * d23) : 0.f;
+  const float C = ok ? 2.f * fmaf(ax, by, -(ay * bx)) / (d12 * d13 * d23) : 0.f;
   const float sa = ok ? C * d13 * 0.5f : 0.f;
   ok = ok && fabsf(sa) < 1.f;
-  const float ca = sqrtf(fmaxf(0.f, 1.f - sa * sa));
-  const float sphi = ok ? (by / d13) * ca - (bx / d13) * sa : 0.f;
+  const float ca = sqrtf(fmaxf(0.f, fmaf(-sa, sa, 1.f)));
+  const float sphi = ok ? fmaf(by / d13, ca, -(bx / d13 * sa)) : 0.f;
   ok = ok && fabsf(sphi) < smx;
   const float sT = ok ? d13 * asin_over(fabsf(sa)) : 1.f;
   s.p[0] = 0.f;

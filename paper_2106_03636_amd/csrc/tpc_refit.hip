@@ -319,10 +319,10 @@ __global__ void __launch_bounds__(FTB) k_rf_fit(RfArgs A) {
       const Hit a = unpack(R[0]), m = unpack(R[n / 2]), b = unpack(last);
       Yr = a.Y;
       Zr = a.Z;
-      ok = seed3(s, row_x[a.row], row_x[m.row], row_x[b.row], float(m.Y - Yr) * (1.f / 256.f),
+      ok = seed3<true>(s, row_x[a.row], row_x[m.row], row_x[b.row], float(m.Y - Yr) * (1.f / 256.f),
                  float(b.Y - Yr) * (1.f / 256.f), float(b.Z - Zr) * (1.f / 256.f), k, smx, A.cov0);
     }
-    if (ok) kf_update(s, 0.f, 0.f, sy2, sz2);  // the first hit is the reference
+    if (ok) kf_update(s, 0.f - s.p[0], 0.f - s.p[1], sy2, sz2);  // the first hit is the reference
     auto step = [&](int j) {
       const Hit h = unpack(runs.at(j));
       const float xr = row_x[h.row];
@@ -844,7 +844,7 @@ __global__ void __launch_bounds__(FTB) k_ch_fit(ChArgs A) {
     };
     // pass 1: hits 1 .. n-1 in chain order
     const int nmax = wave_max(ok ? n : 0);
-    if (ok) kf_update<true>(s, 0.f, 0.f, sy2, sz2);
+    if (ok) kf_update<true>(s, 0.f - s.p[0], 0.f - s.p[1], sy2, sz2);
     for (int c = 0; c * CHUNK < nmax; ++c) {
       Runs::arrived();
       runs.load(c + 1);

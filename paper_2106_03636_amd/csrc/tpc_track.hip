@@ -1632,7 +1632,7 @@ __global__ void __launch_bounds__(CTB) __attribute__((amdgpu_waves_per_eu(5, 8))
       yz = w.syz[h];
     } else {
       bool stop = false;
-      h = pick(A, rf, inv, s.p[0] + st.dy, s.p[1] + s.p[3] * st.sT, Yr, Zr, stop, yz);
+      h = pick(A, rf, inv, y_after(s, st), z_after(s, st), Yr, Zr, stop, yz);
       if (stop) {
         act = false;
         continue;
@@ -1678,7 +1678,7 @@ __global__ void __launch_bounds__(CTB) __attribute__((amdgpu_waves_per_eu(5, 8))
       yz = w.syz[h];
     } else {
       bool stop = false;
-      h = pick(A, rf, inv, s.p[0] + st.dy, s.p[1] + s.p[3] * st.sT, Yr, Zr, stop, yz);
+      h = pick(A, rf, inv, y_after(s, st), z_after(s, st), Yr, Zr, stop, yz);
       if (stop) {
         act = false;
         continue;
@@ -1956,7 +1956,7 @@ __global__ void __launch_bounds__(64) k_fit_group(Args A) {
     if (on) {
       if (step_prepare<true>(s, xr, k, smx, st)) {
         if (!chain) {
-          pk.begin(A, rc, ic, s.p[0] + st.dy, s.p[1] + s.p[3] * st.sT, Yr, Zr, sub);
+          pk.begin(A, rc, ic, y_after(s, st), z_after(s, st), Yr, Zr, sub);
           stop = pk.stop;
         }
         step_apply(s2, st, xr, k);
@@ -2033,7 +2033,7 @@ __global__ void __launch_bounds__(64) k_fit_group(Args A) {
     if (on) {
       if (step_prepare<true>(s, xr, k, smx, st)) {
         if (!known) {
-          pk.begin(A, rc, ic, s.p[0] + st.dy, s.p[1] + s.p[3] * st.sT, Yr, Zr, sub);
+          pk.begin(A, rc, ic, y_after(s, st), z_after(s, st), Yr, Zr, sub);
           stop = pk.stop;
         }
         step_apply(s2, st, xr, k);
