@@ -14,6 +14,8 @@ SRC_COMPRESS = os.path.join(HERE, "csrc", "tpc_compress.hip")
 SRC_REFIT = os.path.join(HERE, "csrc", "tpc_refit.hip")
 SRC_MERGE = os.path.join(HERE, "csrc", "tpc_merge.hip")
 LIB = os.path.join(HERE, "_tpctrack.so")
+SRC_ROOTS = os.path.join(ROOT, "tests", "kalman_roots.hip")
+ROOTS_LIB = os.path.join(ROOT, "tests", "_kalman_roots.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -37,6 +39,14 @@ def build(verbose: bool = False) -> str:
     subprocess.check_call(cmd)
     os.replace(tmp, LIB)
     return LIB
+
+
+def build_roots() -> str:
+    """The check of the filter's arithmetic that the GPU tests load."""
+    tmp = ROOTS_LIB + ".tmp%d" % os.getpid()
+    subprocess.check_call([HIPCC] + FLAGS + ["-I" + os.path.join(HERE, "csrc"), "-o", tmp, SRC_ROOTS])
+    os.replace(tmp, ROOTS_LIB)
+    return ROOTS_LIB
 
 
 if __name__ == "__main__":

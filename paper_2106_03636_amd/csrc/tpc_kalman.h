@@ -35,10 +35,13 @@ __device__ __forceinline__ float &cv(KStateR &s, int k) { return s.c[k]; }
 // Square root, reciprocal and quotient of normal numbers far from overflow,
 // without the scaling and fix-up steps that the general forms spend on the
 // rest (5, 3 and 3 instructions here against about 13, 10 and 10): a hardware
-// approximation (1 ulp) and Newton corrections whose residuals an FMA forms
-// exactly.  Compared with sqrtf and 1.f / x on every float of 13 binades
-// (2^-87 .. 2^83): the same bits, all of them; quotients by div_by on 7e9
-// pairs: the same.
+// approximation (1 ulp), one Newton step whose residual an FMA forms exactly,
+// and for the quotient one correction by its remainder (Markstein, Computation
+// of elementary functions on the IBM RISC System/6000 processor, 1990).
+// tests/test_gpu_kalman_roots.py compares them with sqrtf, 1.f / x and a / b:
+// the same bits on every float between the limits of is_mid, and on 2^32
+// quotients by either kind of reciprocal, the divisor's own and the one refined
+// from its square root's approximation.
 __device__ __forceinline__ float sqrt_n(float x, float &rs) {  // rs: about 1 / sqrt(x)
   rs = __builtin_amdgcn_rsqf(x);
   const float g = x * rs;
