@@ -429,9 +429,9 @@ typedef struct tpc_refit {
                                   counts[1] entries of hits); outputs are valid only with TPC_OK */
 } tpc_refit_t;
 
-/* Bytes of device workspace that suffice for tpc_refit_tracks and for
- * tpc_fit_chains, with a batch of n_clusters clusters and an output of these
- * capacities (host-only, pure; 0 on bad arguments). */
+/* Bytes of device workspace tpc_refit_tracks needs for a batch of n_clusters
+ * clusters and an output of these capacities (host-only, pure; 0 on bad
+ * arguments). */
 size_t tpc_refit_workspace_size(int64_t n_clusters, int64_t cap_tracks, int64_t cap_hits);
 
 /* Refit the tracks of a tpc_track_sectors call: the same clusters, geometry,
@@ -441,8 +441,8 @@ size_t tpc_refit_workspace_size(int64_t n_clusters, int64_t cap_tracks, int64_t 
  * after the tracking call; the workspace (aligned to 256 bytes) holds no
  * state across calls.  Returns TPC_OK when the work was enqueued,
  * TPC_E_INVALID on bad arguments (a null or misaligned workspace among them),
- * TPC_E_NOMEM when the workspace is too small (tpc_refit_workspace_size()
- * bytes are enough), TPC_E_HIP on a launch failure. */
+ * TPC_E_NOMEM when the workspace is smaller than tpc_refit_workspace_size(),
+ * TPC_E_HIP on a launch failure. */
 int tpc_refit_tracks(const tpc_clusters_t *clusters, const tpc_geometry_t *geometry, const tpc_field_t *field,
                      const tpc_params_t *params, const tpc_tracks_t *tracks, tpc_refit_t *out, void *workspace,
                      size_t workspace_bytes, void *stream);

@@ -371,24 +371,18 @@ __global__ void __launch_bounds__(FTB) k_rf_fit(RfArgs A) {
 
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
-// The workspace of a refit, and behind it the arrays that only the chain fit
-// uses.  The 16-byte loads of the hit records may touch one record past the
-// last: the order follows them, which is never empty where there are records
-// to load.
+// The workspace of a refit or a chain fit.  The 16-byte loads of the hit
+// records may touch one record past the last: the order follows them, which is
+// never empty where there are records to load.
 struct Layout {
-  size_t cl, rec, order, refit;                // refit: where a refit's arrays end
-  size_t dst, next_side, prev_side, chains;    // chains: where the chain fit's end
+  size_t cl, rec, order, total;
 };
 Layout layout(int64_t n_clusters, int64_t cap_tracks, int64_t cap_hits) {
-  const size_t tracks = size_t(cap_tracks);
   Layout L;
   L.cl = align256(NB * 4 + 256);  // after the length buckets and the flags
   L.rec = L.cl + align256(size_t(n_clusters) * 8);
   L.order = L.rec + align256(size_t(cap_hits) * 8);
-  L.refit = L.dst = L.order + align256(tracks * 4);
-  L.next_side = L.dst + align256(tracks * 4);
-  L.prev_side = L.next_side + align256(tracks * 16);
-  L.chains = L.prev_side + align256(tracks * 16);
+  L.total = L.order + align256(size_t(cap_tracks) * 4);
   return L;
 }
 bool layout_ok(int64_t n_clusters, int64_t cap_tracks, int64_t cap_hits) {
@@ -399,7 +393,7 @@ bool layout_ok(int64_t n_clusters, int64_t cap_tracks, int64_t cap_hits) {
 }  // namespace
 
 extern "C" size_t tpc_refit_workspace_size(int64_t n_clusters, int64_t cap_tracks, int64_t cap_hits) {
-  return layout_ok(n_clusters, cap_tracks, cap_hits) ? layout(n_clusters, cap_tracks, cap_hits).chains : 0;
+  return layout_ok(n_clusters, cap_tracks, cap_hits) ? layout(n_clusters, cap_tracks, cap_hits).total : 0;
 }
 
 extern "C" int tpc_refit_tracks(const tpc_clusters_t *clusters, const tpc_geometry_t *geometry,
@@ -424,7 +418,7 @@ extern "C" int tpc_refit_tracks(const tpc_clusters_t *clusters, const tpc_geomet
   if (!layout_ok(clusters->n, tracks->cap_tracks, tracks->cap_hits)) return TPC_E_INVALID;
   const Layout L = layout(clusters->n, tracks->cap_tracks, tracks->cap_hits);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255)) return TPC_E_INVALID;
-  if (workspace_bytes < L.refit) return TPC_E_NOMEM;
+  if (workspace_bytes < L.total) return TPC_E_NOMEM;
   RfArgs A;
   A.y = clusters->y;
   A.z = clusters->z;
@@ -517,7 +511,7 @@ struct ChArgs {
   int32_t *n_chain;
   uint8_t *ok;
   int32_t *status;
-  // workspace (the refit's layout and two arrays more)
+  // workspace (the refit's layout)
   const uint64_t *cl;   // [n_clusters] packed (row, Y, Z) per cluster
   uint64_t *rec;        // [cap_hits] the same per chain hit, a segment's first one marked
   int32_t *order;       // [cap_tracks] slot -> chain head
@@ -525,15 +519,21 @@ struct ChArgs {
   int32_t *bad;         // [0] a hit out of range (the gather's flag), [1] number of heads,
                         // [2] the tracks' hit lists do not follow one another from 0 to the end
   unsigned long long *given;  // [1] records given out to the chains
-  int32_t *dst;         // [cap_tracks] place of a chain segment's first record, -1 for other tracks
-  struct Side *next_side, *prev_side;  // [cap_tracks] a chain segment's neighbours
 };
 // A neighbour of a chain segment, and the cosine and sine of the turn into its
-// frame: one 16-byte read when a walk enters the segment.
-struct __align__(16) Side {
+// frame: one read when a walk enters the segment.
+struct Side {
   float c, s;
-  int32_t q, pad;
+  int32_t q;
 };
+// What the fit has to know of a track is kept in the track's own output rows
+// until its results are known: the place of a chain segment's first record in
+// x_ref (-1: the track is in no chain), its neighbours in cov.
+__device__ __forceinline__ int32_t *place(const ChArgs &A, int64_t t) { return reinterpret_cast<int32_t *>(A.xref + t); }
+__device__ __forceinline__ Side *sides(const ChArgs &A, int64_t t) {  // the next segment, the one before
+  return reinterpret_cast<Side *>(A.cov + t * 15);
+}
+constexpr int SIDES = 2 * sizeof(Side) / 4;        // floats of the row that they take
 constexpr float SAME_FRAME = 2.f;                  // in place of the cosine: the segments share their unit
 constexpr uint64_t FIRST = uint64_t(1) << 56;      // mark of a segment's first record
 
@@ -670,14 +670,15 @@ __global__ void __launch_bounds__(TPB) k_ch_len(ChArgs A) {
       }
       A.n_chain[t] = int32_t(n);
       if (n == 0) {  // the outputs of a track that heads no chain
+        const bool none = nx < 0 && pv < 0;
         A.ok[t] = 0;
 #pragma unroll
         for (int q = 0; q < 5; ++q) A.par[t * 5 + q] = 0.f;
 #pragma unroll
-        for (int q = 0; q < 15; ++q) A.cov[t * 15 + q] = 0.f;
-        A.xref[t] = 0.f;
+        for (int q = 0; q < 15; ++q)
+          if (none || q >= SIDES) A.cov[t * 15 + q] = 0.f;
         A.chi2[t] = 0.f;
-        if (nx < 0 && pv < 0) A.dst[t] = -1;
+        if (none) *place(A, t) = -1;  // the rest of a chain segment's row is its head's until the fit has ended
       }
     }
     __syncthreads();
@@ -688,7 +689,7 @@ __global__ void __launch_bounds__(TPB) k_ch_len(ChArgs A) {
       int32_t from = 0, before = -1;
       int nseg = 0;
       for (int32_t q = int32_t(t); q >= 0 && q < T && nseg < MAX_CHAIN; q = A.next[q], ++nseg) {
-        A.dst[q] = int32_t(to);
+        *place(A, q) = int32_t(to);
         to += A.n_hits[q];
         const int u = A.unit[q];
         float c = SAME_FRAME, sn = 0.f;
@@ -698,8 +699,8 @@ __global__ void __launch_bounds__(TPB) k_ch_len(ChArgs A) {
           c = cosf(d);
           sn = sinf(d);
         }
-        if (before >= 0) A.next_side[before] = Side{c, sn, q, 0};
-        A.prev_side[q] = Side{c, -sn, before, 0};
+        if (before >= 0) sides(A, before)[0] = Side{c, sn, q};
+        sides(A, q)[1] = Side{c, -sn, before};
         from = u;
         before = q;
       }
@@ -762,7 +763,8 @@ __global__ void __launch_bounds__(TPB) k_ch_gather(ChArgs A) {
     if (t >= T) return;
     const int n = A.n_hits[t];
     const int64_t f = A.first_hit[t];
-    const int32_t d = A.dst[t];
+    const int32_t d = *place(A, t);
+    if (d < 0 && lane == 0) A.xref[t] = 0.f;
     for (int j = lane; j < n; j += 64) {
       const uint64_t r = record_of(A, A.hits[f + j]);
       if (room && d >= 0) A.rec[int64_t(d) + j] = j == 0 ? r | FIRST : r;
@@ -790,7 +792,7 @@ __global__ void __launch_bounds__(FTB) k_ch_fit(ChArgs A) {
     KStateR s;
     const int32_t t = valid ? A.order[i] : 0;
     const int n = valid ? A.n_chain[t] : 0;
-    const int64_t first = valid && room ? A.dst[t] : 0;
+    const int64_t first = valid && room ? *place(A, t) : 0;
     bool ok = valid && n >= 3;
     int Yr = 0, Zr = 0;
     uint64_t last = 0;
@@ -800,11 +802,11 @@ __global__ void __launch_bounds__(FTB) k_ch_fit(ChArgs A) {
     auto record = [&](int j) { return room ? A.rec[first + j] : walk_to(A, t, j); };
     // the segment the walk is in, and the one it comes to (loaded when the walk enters a segment)
     int32_t q = t;
-    Side to{SAME_FRAME, 0.f, -1, 0};
+    Side to{SAME_FRAME, 0.f, -1};
     if (ok) {  // seed in the first hit's frame
       last = record(n - 1);
       const Hit h0 = unpack(record(0)), hm = unpack(record(n / 2)), hl = unpack(last);
-      to = A.next_side[t];
+      to = sides(A, t)[0];
       const int cu = A.unit[t];
       Yr = h0.Y;
       Zr = h0.Z;
@@ -855,7 +857,7 @@ __global__ void __launch_bounds__(FTB) k_ch_fit(ChArgs A) {
         step(unpack(r), enter, to.c, to.s);
         if (enter) {
           q = to.q;
-          to = A.next_side[q];  // not read further in the last segment, where it is not written
+          to = sides(A, q)[0];  // not read further in the last segment, where it is not written
         }
       }
     }
@@ -867,7 +869,7 @@ __global__ void __launch_bounds__(FTB) k_ch_fit(ChArgs A) {
       const Hit hl = unpack(last);
       upd_hit<true>(s, make_int2(hl.Y, hl.Z), Yr, Zr, sy2, sz2);
       leave = last & FIRST;
-      to = A.prev_side[q];
+      to = sides(A, q)[1];
     }
     const int c1 = nmax >= 2 ? (nmax - 2) / CHUNK : -1;
     Runs::arrived();
@@ -879,7 +881,7 @@ __global__ void __launch_bounds__(FTB) k_ch_fit(ChArgs A) {
         if (!ok || j > n - 2) continue;
         const uint64_t r = room ? runs.at(j) : walk_to(A, t, j);
         step(unpack(r), leave, to.c, to.s);
-        if (leave) to = A.prev_side[to.q];
+        if (leave) to = sides(A, to.q)[1];
         leave = r & FIRST;
       }
     }
@@ -894,6 +896,11 @@ __global__ void __launch_bounds__(FTB) k_ch_fit(ChArgs A) {
     for (int e = 0; e < 15; ++e) cov[e] = ok ? s.c[e] : 0.f;
     A.xref[t] = ok ? s.x : 0.f;
     A.chi2[t] = ok ? s.chi2 : 0.f;
+    for (int32_t r = A.next[t]; r >= 0; r = A.next[r]) {  // the rows of the chain's other segments, which it used
+#pragma unroll
+      for (int e = 0; e < SIDES; ++e) A.cov[int64_t(r) * 15 + e] = 0.f;
+      A.xref[r] = 0.f;
+    }
   }
 }
 
@@ -922,7 +929,7 @@ extern "C" int tpc_fit_chains(const tpc_clusters_t *clusters, const tpc_geometry
   if (!layout_ok(clusters->n, tracks->cap_tracks, tracks->cap_hits)) return TPC_E_INVALID;
   const Layout L = layout(clusters->n, tracks->cap_tracks, tracks->cap_hits);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255)) return TPC_E_INVALID;
-  if (workspace_bytes < L.chains) return TPC_E_NOMEM;
+  if (workspace_bytes < L.total) return TPC_E_NOMEM;
   // the refit's workspace layout; its pack and gather fill the hit records
   char *w = static_cast<char *>(workspace);
   RfArgs R{};
@@ -979,10 +986,6 @@ extern "C" int tpc_fit_chains(const tpc_clusters_t *clusters, const tpc_geometry
   A.status = out->status;
   A.cl = R.cl;
   A.rec = R.rec;
-  static_assert(sizeof(Side) == 16, "as laid out");
-  A.dst = reinterpret_cast<int32_t *>(w + L.dst);
-  A.next_side = reinterpret_cast<Side *>(w + L.next_side);
-  A.prev_side = reinterpret_cast<Side *>(w + L.prev_side);
   A.order = R.order;
   A.bucket = R.bucket;
   A.bad = R.bad;
