@@ -606,7 +606,8 @@ __device__ __forceinline__ void scan_unit(const MgArgs &A, WaveScan &L, int64_t 
       r.s = float(q[2]);
       r.C = float(A.k * q[4]);
       r.c = __builtin_amdgcn_sqrtf(fmaxf(0.f, 1.f - r.s * r.s));
-      r.plain = fabsf(r.s) < 0.96f && fabsf(r.C) < 0.05f && fabsf(r.x) <= 8192.f && fabsf(r.y) <= 8192.f;
+      // |x|, |y| and |C| within their limits, by one comparison
+      r.plain = fabsf(r.s) < 0.96f && fmaxf(fmaxf(fabsf(r.x), fabsf(r.y)), fabsf(r.C) * (8192.f / 0.05f)) < 8192.f;
     }
   }
   const float dz = float(A.dz_max) * 1.000001f + 2e-3f, dy = float(A.dy_max) * 1.000001f + 6e-3f, smx = float(A.smx) + 1e-4f;
