@@ -18,14 +18,25 @@
 // A look-back waits for the slowest block before it, so the blocks have to
 // cost alike: the inner rows have a third of the outer rows' pads and nearly
 // as many clusters, and every row is cut into the same number of parts (runs
-// of a fixed number of pads: 912 us where equal parts take 651).
+// of a fixed number of pads: 912 us where equal parts take 651).  The number
+// follows from the batch's mean, so a part of a dense unit or row, or of a hot
+// region, may hold more than a block stages: such a part is taken a run of pads
+// at a time, all counted before the first is written.  36 units, one with 15 M
+// digits: 0.92 ms (all its parts swept in memory 3.4, the two passes below 1.37);
+// one of 5 M 0.35 - 0.51 (1.08 - 1.31, 1.20).  What it does not mend is the
+// wait: with 2 rows of 152 a hundred times denser than the others in every
+// unit, 1.88 ms (6.2, 1.34), since few dense parts are among the blocks that
+// run at one time.  (Cutting the rows at equal weights of digits and pads takes
+// 0.45, 0.33 and 0.49 ms for these, but 0.64 - 0.70 instead of 0.57 for an even
+// batch and 25 us instead of 22 for one unit: its blocks cost more to find.)
 // Peaks and charge sums are integer; the centre and position are FP64
 // expressions rounded once to FP32, so the result is exact.
 //
 // What bounds it: instruction issue (about 190 vector instructions per 64
-// digits, half of them the searches'), then the look-back (140 us of the 605)
-// and the tickets (45 us).  60 M digits of 540 k pads: 605 us, 0.7 TB/s of the
-// bytes it cannot do without; 0.49 M digits of 15 k pads: 25 us.  Before, two
+// digits, half of them the searches'), then the look-back and the tickets (140
+// and 45 us of the 605 that 27 k parts took).  63 M digits of 540 k pads: 566 us
+// with 22 k parts, 0.7 TB/s of the bytes it cannot do without; 0.48 M digits of
+// 15 k pads: 22 us.  Before, two
 // passes (count, emit) searched for every digit, a wave per pad: 2.39 ms and
 // 57 us.
 
@@ -209,8 +220,11 @@ __device__ __forceinline__ int slot_of(const Run &R, int32_t e) {
   return lo;
 }
 
-// np pads of row r of unit u from pad `first` on: their offsets, checked.  Run
-// by one wave.
+// np pads of row r of unit u from pad `first` on: their offsets, checked.  SOME:
+// as many of them as fit the block's LDS with the pads either side, and where
+// not even one does, the pads up to the next that does, with fits = false.
+// Run by one wave.
+template <bool SOME>
 __device__ __forceinline__ void load_run(const CluArgs &A, Run &R, int u, int r, int32_t first, int32_t np) {
   const int t = __lane_id();
   const int64_t j0 = int64_t(u) * A.pads_total + A.rbase[r] + first;
@@ -222,21 +236,33 @@ __device__ __forceinline__ void load_run(const CluArgs &A, Run &R, int u, int r,
   if (t == 0 && j0 == 0) good = good && A.off[0] == 0;
   if (t == 0 && j0 + np >= A.n_pads) good = good && A.off[A.n_pads] == A.n;
   const bool ok = __ballot(good) == ~uint64_t(0);
-  const int64_t at = __shfl(v, 0) & ~int64_t(3), last = __shfl(v, np + 2);  // loads of four start at a multiple of four
+  const int64_t at = __shfl(v, 0) & ~int64_t(3);  // loads of four start at a multiple of four
   int32_t len = ok && t < np + 2 ? int32_t(next - v) : 0;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) len = max(len, __shfl_xor(len, o));
+  const int64_t last = __shfl(v, np + 2);
+  int k = np;
+  bool fits = ok && last - at <= STAGE_DIGITS;
+  if (SOME && ok && !fits && np > 0) {
+    // slots 0 .. k + 1 end with the offset of lane k + 2
+    k = __popcll(__ballot(t < np + 3 && v - at <= STAGE_DIGITS)) - 3;
+    fits = k > 0;
+    if (!fits) {  // pad first + t by itself, with its neighbours
+      const bool one = __shfl_down(v, 3) - (v & ~int64_t(3)) <= STAGE_DIGITS;
+      k = min(np, __ffsll((unsigned long long)__ballot(one || t >= np)) - 1);
+    }
+  }
   if (t < np + 3) R.a[t] = ok ? int32_t(v - at) : 0;
   if (t == 0) {
     if (!ok) fail(A.status, TPC_E_INVALID);
     R.g0 = at;
     R.first = first;
-    R.np = np;
+    R.np = k;
     R.row = r;
     R.half = A.half[r];
     R.top = len > 0 ? 1 << (31 - __clz(len)) : 0;
     R.ok = ok;
-    R.fits = ok && last - at <= STAGE_DIGITS;
+    R.fits = fits;
   }
 }
 
@@ -305,8 +331,8 @@ __device__ __forceinline__ void lists(const Run &R, int s, F list, L &lo, L &hi)
   if (R.first + s == 2 * R.half) hi.n = 0;
 }
 
-// A run whose digits do not fit in LDS: a wave per pad reads the arrays, once
-// to count (EMIT false: into cnt) and once to write from place o0 on.
+// Pads that do not fit in LDS even one by one: a wave per pad reads the arrays,
+// once to count (EMIT false: into cnt) and once to write from place o0 on.
 template <bool EMIT>
 __device__ __forceinline__ void sweep(const CluArgs &A, const Run &R, int32_t *cnt, int64_t o0) {
   const int lane = __lane_id();
@@ -360,11 +386,32 @@ __global__ void __launch_bounds__(TPB) k_clu_find(CluArgs A) {
   const int part = int(vb % A.parts), r = int(vb / A.parts % A.n_rows), u = int(vb / A.parts / A.n_rows);
   const int32_t pads = min(max(2 * A.half[r], 0), A.pads_total), step = (pads + A.parts - 1) / A.parts;
   const int32_t first = min(part * step, pads), np = min(step, pads - first);
-  if (wave == 0) load_run(A, R, u, r, first, min(np, MAX_PADS));
+  if (wave == 0) load_run<false>(A, R, u, r, first, min(np, MAX_PADS));
   __syncthreads();
-  if (np <= MAX_PADS && R.fits) {
-    int32_t mine = 0;  // peaks of this wave
-    const int32_t m = R.a[np + 2];
+  const bool whole = np <= MAX_PADS && R.fits;
+
+  auto slot_list = [&](int s) {
+    Packed L;
+    L.d = dig + R.a[s];
+    L.n = R.a[s + 1] - R.a[s];
+    L.top = R.top;
+    return L;
+  };
+  auto peak = [&](int32_t e, int &s) {
+    s = slot_of(R, e);
+    const bool hb = e > R.a[s], ha = e + 1 < R.a[s + 1];
+    Peak k = own_pad(A.q_min, dig[e], hb, dig[max(e - 1, 0)], ha, dig[e + 1]);
+    Packed lo, hi;
+    lists(R, s, slot_list, lo, hi);
+    other_pads(k, lo, hi);
+    return k;
+  };
+  uint16_t *list;
+  // The peaks of the run's digits in this wave's share, `mine` of them in
+  // list; wcnt: those of each wave.
+  auto find = [&](int32_t n) -> int32_t {
+    int32_t mine = 0;
+    const int32_t m = R.a[n + 2];
     if (A.wide) {
       for (int32_t e = int32_t(threadIdx.x) * 4; e < m; e += TPB * 4) {
         const int64_t g = R.g0 + e;
@@ -386,16 +433,16 @@ __global__ void __launch_bounds__(TPB) k_clu_find(CluArgs A) {
         if (g < A.n) dig[e] = pack(A.time[g], A.q[g]);
       }
     }
-    if (int(threadIdx.x) <= np) {
+    if (int(threadIdx.x) <= n) {
       const int32_t e = R.a[threadIdx.x + 1];
       atomicOr(&starts[e >> 5], 1u << (e & 31));
     }
     __syncthreads();
     // the wave's share of the own digits: whole groups of 64
-    const int32_t e0 = R.a[1], e1 = R.a[np + 1];
+    const int32_t e0 = R.a[1], e1 = R.a[n + 1];
     const int32_t groups = (e1 - e0 + 63) >> 6, per = (groups + WAVES - 1) / WAVES;
     const int32_t w0 = min(e1, e0 + wave * per * 64), w1 = min(e1, w0 + per * 64);
-    uint16_t *list = found + (w0 - e0);
+    list = found + (w0 - e0);
     int32_t n_cand = 0;
     for (int32_t eb = w0; eb < w1; eb += 64) {
       const int32_t e = eb + lane;
@@ -410,22 +457,6 @@ __global__ void __launch_bounds__(TPB) k_clu_find(CluArgs A) {
       if (c) list[n_cand + __popcll(k & ((1ull << lane) - 1ull))] = uint16_t(e);
       n_cand += __popcll(k);
     }
-    auto slot_list = [&](int s) {
-      Packed L;
-      L.d = dig + R.a[s];
-      L.n = R.a[s + 1] - R.a[s];
-      L.top = R.top;
-      return L;
-    };
-    auto peak = [&](int32_t e, int &s) {
-      s = slot_of(R, e);
-      const bool hb = e > R.a[s], ha = e + 1 < R.a[s + 1];
-      Peak k = own_pad(A.q_min, dig[e], hb, dig[max(e - 1, 0)], ha, dig[e + 1]);
-      Packed lo, hi;
-      lists(R, s, slot_list, lo, hi);
-      other_pads(k, lo, hi);
-      return k;
-    };
     __builtin_amdgcn_wave_barrier();
     for (int32_t i0 = 0; i0 < n_cand; i0 += 64) {  // the peaks among them, kept in the list's front
       const int32_t i = i0 + lane;
@@ -443,67 +474,98 @@ __global__ void __launch_bounds__(TPB) k_clu_find(CluArgs A) {
     }
     if (lane == 0) wcnt[wave] = mine;
     __syncthreads();
-    if (wave == 0) {
-      int32_t all = 0;
-      for (int w = 0; w < WAVES; ++w) all += wcnt[w];
-      const int64_t before = look_back(A, vb, all);
-      if (lane == 0) s_before = before;
-    }
-    __syncthreads();
-    int64_t o = s_before;
+    return mine;
+  };
+  // and their clusters, from place o of the output on
+  auto write = [&](int32_t mine, int64_t o) {
     for (int w = 0; w < wave; ++w) o += wcnt[w];
     for (int32_t i = lane; i < mine; i += 64) {
       int s;
       const Peak k = peak(list[i], s);
       write_cluster(A, R, s, k, o + i);
     }
-  } else {  // MAX_PADS pads at a time, from the arrays
+  };
+  auto sum = [&]() {
     int32_t all = 0;
-    for (int32_t p = 0; p < np; p += MAX_PADS) {
-      if (wave == 0) load_run(A, R, u, r, first + p, min(np - p, MAX_PADS));
-      if (int(threadIdx.x) < MAX_PADS) cnt[threadIdx.x] = 0;
+    for (int w = 0; w < WAVES; ++w) all += wcnt[w];
+    return all;
+  };
+  auto place = [&](int32_t count) {  // of the block's first cluster, by wave 0
+    const int64_t before = look_back(A, vb, count);
+    if (lane == 0) s_before = before;
+  };
+  if (__builtin_expect(whole, 1)) {
+    const int32_t mine = find(np);
+    if (wave == 0) place(sum());
+    __syncthreads();
+    write(mine, s_before);
+  } else {
+    // Too many digits (a part of a row that holds far more than the batch's
+    // mean): a run at a time, once to count and once to write.
+    int32_t total = 0;
+    const bool keep = np <= MAX_PADS;  // cnt holds all of the part's pads
+    auto next_run = [&](int32_t p) {
       __syncthreads();
-      if (R.ok) sweep<false>(A, R, cnt, 0);
+      if (wave == 0) load_run<true>(A, R, u, r, first + p, min(np - p, MAX_PADS));
+      for (int i = threadIdx.x; i < STAGE_DIGITS / 32 + 2; i += TPB) starts[i] = 0;
       __syncthreads();
-      for (int x = 0; x < R.np; ++x) all += cnt[x];
-      __syncthreads();
+    };
+    for (int32_t p = 0; p < np;) {
+      next_run(p);
+      const int32_t got = R.np;
+      if (R.fits) {
+        find(got);
+        total += sum();
+      } else if (R.ok) {
+        int32_t *c = cnt + (keep ? p : 0);
+        sweep<false>(A, R, c, 0);
+        __syncthreads();
+        for (int x = 0; x < got; ++x) total += c[x];
+      }
+      p += got;
     }
-    if (wave == 0) {
-      const int64_t before = look_back(A, vb, all);
-      if (lane == 0) s_before = before;
-    }
-    if (threadIdx.x < WAVES) wcnt[threadIdx.x] = threadIdx.x == 0 ? all : 0;
+    if (wave == 0) place(total);
     __syncthreads();
     int64_t o = s_before;
-    for (int32_t p = 0; p < np; p += MAX_PADS) {
-      if (wave == 0) load_run(A, R, u, r, first + p, min(np - p, MAX_PADS));
-      if (int(threadIdx.x) < MAX_PADS) cnt[threadIdx.x] = 0;
-      __syncthreads();
-      if (R.ok) sweep<false>(A, R, cnt, 0);
-      __syncthreads();
-      if (R.ok) sweep<true>(A, R, cnt, o);
-      for (int x = 0; x < R.np; ++x) o += cnt[x];
-      __syncthreads();
+    for (int32_t p = 0; p < np;) {
+      next_run(p);
+      const int32_t got = R.np;
+      if (R.fits) {
+        const int32_t mine = find(got);
+        write(mine, o);
+        o += sum();
+      } else if (R.ok) {
+        int32_t *c = cnt + (keep ? p : 0);
+        if (!keep) sweep<false>(A, R, c, 0);
+        __syncthreads();
+        sweep<true>(A, R, c, o);
+        for (int x = 0; x < got; ++x) o += c[x];
+      }
+      p += got;
     }
+    __syncthreads();
+    if (threadIdx.x < WAVES) wcnt[threadIdx.x] = threadIdx.x == 0 ? total : 0;
+    __syncthreads();
   }
   if (r == 0 && part == 0 && threadIdx.x == 0) A.unit_offsets[u] = s_before;
   if (vb == A.n_blocks - 1 && threadIdx.x == 0) {
-    int64_t total = s_before;
-    for (int w = 0; w < WAVES; ++w) total += wcnt[w];
-    *A.count = total;
-    A.unit_offsets[A.n_units] = total;
-    if (total > A.cap) fail(A.status, TPC_E_CAPACITY);
+    const int64_t all = s_before + sum();
+    *A.count = all;
+    A.unit_offsets[A.n_units] = all;
+    if (all > A.cap) fail(A.status, TPC_E_CAPACITY);
   }
 }
 
 // Parts of a row: a block's digits, with the edge pads and the densest rows
-// (a third above the mean), should fit its LDS; a block whose digits do not
-// reads the arrays.  Rows may be longer than the mean: parts of at most
-// MAX_PADS pads there too, where that is possible.
+// (a third above the mean), should fit its LDS; otherwise a part takes several
+// runs (the quotient below at 2.2, 1.9, 1.7 and 1.5: an even batch of 63 M digits
+// 607, 558, 562 and 487 us, one unit of 5 M 100, 103, 105 and 145).  Rows may be
+// longer than the mean: parts of at most MAX_PADS pads there too, where that is
+// possible.
 int32_t parts_per_row(int64_t n, int64_t n_pads, int32_t n_units, int32_t n_rows) {
   const int64_t rows = int64_t(n_units) * n_rows, pads = n_pads / rows;  // pads: of a row, on average
   const int64_t most = pads / 2 > 1 ? pads / 2 : 1;
-  const int64_t by_digits = n / rows / (STAGE_DIGITS * 10 / 22) + 1, by_pads = pads * 8 / 5 / MAX_PADS + 1;
+  const int64_t by_digits = n / rows / (STAGE_DIGITS * 10 / 19) + 1, by_pads = pads * 8 / 5 / MAX_PADS + 1;
   const int64_t p = by_digits > by_pads ? by_digits : by_pads;
   return int32_t(p < most ? p : most);
 }
