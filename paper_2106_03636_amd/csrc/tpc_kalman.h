@@ -181,8 +181,12 @@ __device__ __forceinline__ void step_apply(S &s, const Step &t, float x2, float 
 
 // The measurement of residuals (r0, r1).  Z_FUSED: which product of a sum of
 // two with the residuals enters the FMA unrounded, the y one's or the z one's
-// (the chain fit's).
-template <bool Z_FUSED = false, class S>
+// (the chain fit's).  P_FIRST: the parameters before the covariance; the bits
+// are the same.  The next row waits for them, and the fit with several lanes a
+// seed has no other wave to run meanwhile: one chunk 451 us the whole call, 455
+// with the covariance first.  The row loop of k_fit needs no scratch with the
+// covariance first: 50 collisions 8.13 ms, so 8.25.
+template <bool Z_FUSED = false, bool P_FIRST = false, class S>
 __device__ __forceinline__ void kf_update(S &s, float r0, float r1, float sy2, float sz2) {
 #pragma clang fp contract(off)
   const float S00 = cv(s, 0) + sy2, S01 = cv(s, 1), S11 = cv(s, 2) + sz2;
@@ -198,14 +202,18 @@ __device__ __forceinline__ void kf_update(S &s, float r0, float r1, float sy2, f
     K0[i] = fmaf(q0[i], I00, q1[i] * I01);
     K1[i] = i == 1 ? fmaf(q1[i], I11, q0[i] * I01) : fmaf(q0[i], I01, q1[i] * I11);
   }
+  auto parameters = [&]() {
+#pragma clang fp contract(off)
+#pragma unroll
+    for (int i = 0; i < 5; ++i) s.p[i] += Z_FUSED ? fmaf(K1[i], r1, K0[i] * r0) : fmaf(K0[i], r0, K1[i] * r1);
+  };
+  if (P_FIRST) parameters();
   int k = 0;
 #pragma unroll
   for (int i = 0; i < 5; ++i)
 #pragma unroll
     for (int j = 0; j <= i; ++j, ++k) cv(s, k) -= fmaf(K0[i], q0[j], K1[i] * q1[j]);
-  // after the covariance: the row loop of k_fit then needs no scratch (before it, 50 collisions took 8.25 ms for 8.13)
-#pragma unroll
-  for (int i = 0; i < 5; ++i) s.p[i] += Z_FUSED ? fmaf(K1[i], r1, K0[i] * r0) : fmaf(K0[i], r0, K1[i] * r1);
+  if (!P_FIRST) parameters();
   if (Z_FUSED)
     s.chi2 += fmaf(r0, fmaf(r1, I01, r0 * I00), r1 * fmaf(r1, I11, r0 * I01));
   else
@@ -224,9 +232,9 @@ __device__ __forceinline__ void cov_reset(S &s, const float *cov0) {
 }
 
 // measurement of hit h relative to the reference (exact: integer difference)
-template <bool Z_FUSED = false, class S>
+template <bool Z_FUSED = false, bool P_FIRST = false, class S>
 __device__ __forceinline__ void upd_hit(S &s, int2 yz, int Yr, int Zr, float sy2, float sz2) {
-  kf_update<Z_FUSED>(s, fmaf(float(yz.x - Yr), 1.f / 256.f, -s.p[0]), fmaf(float(yz.y - Zr), 1.f / 256.f, -s.p[1]), sy2, sz2);
+  kf_update<Z_FUSED, P_FIRST>(s, fmaf(float(yz.x - Yr), 1.f / 256.f, -s.p[0]), fmaf(float(yz.y - Zr), 1.f / 256.f, -s.p[1]), sy2, sz2);
 }
 
 // Length of (x, y); X_FUSED: which of the squares enters the FMA unrounded.

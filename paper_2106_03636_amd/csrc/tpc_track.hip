@@ -1925,7 +1925,7 @@ __global__ void __launch_bounds__(64) k_fit_group(Args A) {
   int2 yzn = make_int2(0, 0), yz_out = yz0;
   if (ok) {
     col[r1 * 64] = h0;
-    upd_hit(s, yz0, Yr, Zr, sy2, sz2);
+    upd_hit<false, true>(s, yz0, Yr, Zr, sy2, sz2);
     hn = w.upc[h0];
     if (hn >= 0) {
       yzn = w.syz[hn];
@@ -1982,7 +1982,7 @@ __global__ void __launch_bounds__(64) k_fit_group(Args A) {
       }
       col[r * 64] = h;  // every lane of the group writes it, and reads its own write in pass 2
       if (h >= 0) {
-        upd_hit(s2, yz, Yr, Zr, sy2, sz2);
+        upd_hit<false, true>(s2, yz, Yr, Zr, sy2, sz2);
         s = s2;
         r_out = r;
         yz_out = yz;
@@ -1998,7 +1998,7 @@ __global__ void __launch_bounds__(64) k_fit_group(Args A) {
   if (ok) {
     cov_reset(s, P.cov0);
     s.chi2 = 0.f;
-    upd_hit(s, yz_out, Yr, Zr, sy2, sz2);
+    upd_hit<false, true>(s, yz_out, Yr, Zr, sy2, sz2);
     nfit = 1;
     rhi = r_out;
     rlo = r_out;
@@ -2059,7 +2059,7 @@ __global__ void __launch_bounds__(64) k_fit_group(Args A) {
         }
       }
       if (h >= 0) {
-        upd_hit(s2, yz, Yr, Zr, sy2, sz2);
+        upd_hit<false, true>(s2, yz, Yr, Zr, sy2, sz2);
         s = s2;
         ++nfit;
         rlo = r;
