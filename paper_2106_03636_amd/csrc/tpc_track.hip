@@ -649,7 +649,7 @@ struct BinGrid {
 // (few) hits of the bin with smaller numbers; y, z and ids then change places
 // in LDS and go out in whole lines.  Where a bin holds so many hits that this
 // would cost more, or the hits are more than NT * KR, one wave ranks them
-// with ballots, 64 at a time.  Rows past the pool take global cursors.
+// with ballots, 64 at a time.  Rows past the pool: bin_sort_rows.
 //   Measured (50 collisions, 4.6 k hits a row; 512 chunks, 80 a row): the
 // scatter straight to memory cost a write request per hit and array, which
 // bounded the first, and four waves of which one ranked the second: 705 and
@@ -813,29 +813,96 @@ __device__ __forceinline__ void bin_sort_lds(const Workspace &w, const BinGrid &
     if (tid + k * NT < n) w.perm[g.start + tid + k * NT] = slot[tid + k * NT];
 }
 
-// rows past the pool: cursors in the workspace (called by the whole block)
+// Rows past the pool, by the whole block: the same steps with each hit's turn
+// and slot in memory (the links of the cleaner, written only later), and the
+// counters there too where they do not fit the pool.  Three rows of 8 k hits
+// among 15 k of 20: 449 us the whole call before a wave sorted the small rows,
+// 847 with these ranked by one wave, 64 hits at a time with the counters in
+// memory, now 385.  hist: nbins counters.
 template <int NT>
-__device__ __forceinline__ void bin_sort_global(const Workspace &w, const BinGrid &g, int *tmp) {
-  int *hist = w.cursor + g.cbase;
+__device__ __forceinline__ void bin_sort_rows(const Workspace &w, const BinGrid &g, int *hist, int *tmp) {
   const int tid = threadIdx.x;
+  int32_t *turn = w.upc + g.start, *slot = w.dnc + g.start;
   for (int b = tid; b < g.nbins; b += NT) hist[b] = 0;
   __syncthreads();
-  for (int p = tid; p < g.count; p += NT) atomicAdd(&hist[g.bin(w.rs_yz[g.start + p])], 1);
+  constexpr int B = 4;  // hits of a thread on their way together
+  int2 yz[B];
+  int lo[B], v[B];
+  auto load = [&](int p0) {
+#pragma unroll
+    for (int k = 0; k < B; ++k) {
+      const int p = p0 + k * NT;
+      if (p < g.count) yz[k] = w.rs_yz[g.start + p];
+    }
+  };
+  for (int p0 = tid; p0 < g.count; p0 += NT * B) {
+    load(p0);
+#pragma unroll
+    for (int k = 0; k < B; ++k)
+      if (p0 + k * NT < g.count) v[k] = atomicAdd(&hist[g.bin(yz[k])], 1);
+#pragma unroll
+    for (int k = 0; k < B; ++k)
+      if (p0 + k * NT < g.count) turn[p0 + k * NT] = v[k];
+  }
   __syncthreads();
-  scan_bins<NT>(hist, g.nbins, w.cell + g.cbase, g.start, tid, tmp);
-  __syncthreads();
+  const int most = scan_bins<NT>(hist, g.nbins, w.cell + g.cbase, g.start, tid, tmp);
+  if (!__syncthreads_or(most > 16 + g.count / 64)) {  // as above; a look costs more here
+    for (int p0 = tid; p0 < g.count; p0 += NT * B) {
+      load(p0);
+#pragma unroll
+      for (int k = 0; k < B; ++k)
+        if (p0 + k * NT < g.count) v[k] = turn[p0 + k * NT];
+#pragma unroll
+      for (int k = 0; k < B; ++k)
+        if (p0 + k * NT < g.count) slot[hist[g.bin(yz[k])] + v[k]] = p0 + k * NT;
+    }
+    __syncthreads();
+    for (int p0 = tid; p0 < g.count; p0 += NT * B) {
+      load(p0);
+      int hi[B], id[B], longest = 0;
+#pragma unroll
+      for (int k = 0; k < B; ++k)
+        if (p0 + k * NT < g.count) id[k] = w.rs_idx[g.start + p0 + k * NT];
+#pragma unroll
+      for (int k = 0; k < B; ++k) {
+        lo[k] = hi[k] = v[k] = 0;
+        if (p0 + k * NT < g.count) {
+          const int b = g.bin(yz[k]);
+          lo[k] = v[k] = hist[b];
+          hi[k] = b + 1 < g.nbins ? hist[b + 1] : g.count;
+          longest = max(longest, hi[k] - lo[k]);
+        }
+      }
+      for (int q = 0; q < longest; ++q)
+#pragma unroll
+        for (int k = 0; k < B; ++k)
+          if (lo[k] + q < hi[k]) v[k] += slot[lo[k] + q] < p0 + k * NT;
+#pragma unroll
+      for (int k = 0; k < B; ++k)
+        if (p0 + k * NT < g.count) {
+          w.perm[g.start + v[k]] = id[k];
+          w.syz[g.start + v[k]] = yz[k];
+        }
+    }
+    return;
+  }
   if (tid >= 64) return;
   int nbits = 1;
   while ((1 << nbits) < g.nbins) ++nbits;
+  int2 yzn = make_int2(0, 0);  // the next 64 hits load early
+  int idn = 0;
+  if (tid < g.count) {
+    yzn = w.rs_yz[g.start + tid];
+    idn = w.rs_idx[g.start + tid];
+  }
   for (int c = 0; c < g.count; c += 64) {
     const int p = c + tid;
     const bool act = p < g.count;
-    int2 yz = make_int2(0, 0);
-    int idx = 0, bn = 0;
-    if (act) {
-      yz = w.rs_yz[g.start + p];
-      idx = w.rs_idx[g.start + p];
-      bn = g.bin(yz);
+    const int2 yz = yzn;
+    const int idx = idn, bn = act ? g.bin(yz) : 0;
+    if (p + 64 < g.count) {
+      yzn = w.rs_yz[g.start + p + 64];
+      idn = w.rs_idx[g.start + p + 64];
     }
     const uint64_t peers = peer_mask(uint32_t(bn), nbits, act);
     int pos = 0;
@@ -849,6 +916,11 @@ __device__ __forceinline__ void bin_sort_global(const Workspace &w, const BinGri
     }
   }
 }
+template <int NT, int POOL>
+__device__ __forceinline__ void bin_sort_memory(const Workspace &w, const BinGrid &g, int *pool, int *tmp) {
+  if (g.nbins <= POOL) bin_sort_rows<NT>(w, g, pool, tmp);
+  else bin_sort_rows<NT>(w, g, w.cursor + g.cbase, tmp);
+}
 
 // A block per (unit,row).
 constexpr int BIN_TPB = 512;
@@ -859,32 +931,37 @@ __global__ void __launch_bounds__(BIN_TPB) k_bin_sort(Args A) {
   if (*A.out.status != TPC_OK) return;
   const BinGrid g(w, blockIdx.x);
   if (g.nbins + 1 + g.count <= BIN_POOL) bin_sort_lds<BIN_TPB, 12>(w, g, threadIdx.x, pool, tmp);
-  else bin_sort_global<BIN_TPB>(w, g, tmp);
+  else bin_sort_memory<BIN_TPB, BIN_POOL>(w, g, pool, tmp);
 }
 
+constexpr int BIN_APART = 8;
 // Four (unit,row)s a block, a wave each where they are small enough for it;
-// the block then takes the larger ones together.
+// the block then takes the larger ones together.  Eight blocks of one XCD take
+// 32 consecutive (unit,row)s, eight apart in each: neighbours share cache lines,
+// and neighbouring dense rows go to different blocks.
 __global__ void __launch_bounds__(TPB) k_bin_sort_small(Args A) {
-  constexpr int WAVES = TPB / 64, POOL = WAVES * BIN_POOL_WAVE, KR = 8;
+  constexpr int WAVES = TPB / 64, POOL = WAVES * BIN_POOL_WAVE, KR = 8, APART = BIN_APART;
   __shared__ int pool[POOL];
   __shared__ int tmp[WAVES];
   const Workspace &w = A.w;
   if (*A.out.status != TPC_OK) return;
-  const int64_t s0 = int64_t(blockIdx.x) * WAVES;
+  // 64 blocks to 8 runs of 32, one run an XCD
+  const int64_t s0 = (int64_t(blockIdx.x >> 6) * 8 + (blockIdx.x & 7)) * (APART * WAVES) + (blockIdx.x >> 3 & 7);
   const int wave = threadIdx.x >> 6;
-  if (s0 + wave < w.S) {
-    const BinGrid g(w, s0 + wave);
+  if (s0 + wave * APART < w.S) {
+    const BinGrid g(w, s0 + wave * APART);
     if (g.nbins + 1 + g.count <= BIN_POOL_WAVE && g.count <= 64 * KR)
       bin_sort_lds<64, KR>(w, g, __lane_id(), pool + wave * BIN_POOL_WAVE, tmp);
   }
-  for (int i = 0; i < WAVES && s0 + i < w.S; ++i) {  // block-uniform
-    const BinGrid g(w, s0 + i);
+  for (int i = 0; i < WAVES && s0 + i * APART < w.S; ++i) {  // block-uniform
+    const BinGrid g(w, s0 + i * APART);
     if (g.nbins + 1 + g.count <= BIN_POOL_WAVE && g.count <= 64 * KR) continue;
     __syncthreads();
     if (g.nbins + 1 + g.count <= POOL) bin_sort_lds<TPB, KR>(w, g, threadIdx.x, pool, tmp);
-    else bin_sort_global<TPB>(w, g, tmp);
+    else bin_sort_memory<TPB, POOL>(w, g, pool, tmp);
   }
 }
+inline unsigned bin_small_blocks(int64_t S) { return unsigned((S + 8 * BIN_APART * (TPB / 64) - 1) / (8 * BIN_APART * (TPB / 64)) * 64); }
 // Hits a (unit,row) holds on average up to which k_bin_sort_small takes them.
 // A wave holds 512; the whole call takes, by the small kernel and by the other:
 // 91 hits a row 889 and 917 us, 274 a row 1203 and 1230, 548 a row 1519 and
@@ -2434,7 +2511,7 @@ int track_impl(const tpc_clusters_t *c, const tpc_geometry_t *g, const tpc_field
     mark();
     hipLaunchKernelGGL(k_tile_scatter, dim3(unsigned(w.T_max)), dim3(TPB), 0, st, A);
     mark();
-    if (c->n <= BIN_SMALL * w.S) hipLaunchKernelGGL(k_bin_sort_small, dim3(blocks_for(w.S, TPB / 64)), dim3(TPB), 0, st, A);
+    if (c->n <= BIN_SMALL * w.S) hipLaunchKernelGGL(k_bin_sort_small, dim3(bin_small_blocks(w.S)), dim3(TPB), 0, st, A);
     else hipLaunchKernelGGL(k_bin_sort, dim3(unsigned(w.S)), dim3(BIN_TPB), 0, st, A);
     mark();
     hipLaunchKernelGGL(k_neighbours, dim3(round8(w.CH_max)), dim3(NCH), 0, st, A);
