@@ -66,6 +66,7 @@ struct Workspace {
   int32_t *tmp_r1, *tmp_hm, *tmp_hb;  // per tracklet, k_chains -> k_compact_seeds (aliases the hit table)
   // per seed (tracklet with a chain of >= l_min hits), capacity S_cap
   int32_t *seed_list, *sd_r1, *sd_hm, *sd_hb, *sd_nfit, *sd_rlo, *sd_rhi, *sd_owned, *sd_keep, *sd_p1n;
+  uint32_t *sd_first, *sd_first4;  // the selector's, in place of sd_hm and sd_hb, which the fit has read
   uint32_t *sd_key;
   float *sd_par, *sd_cov, *sd_x, *sd_chi2;
   int32_t *trk_hits;  // seed hit table [S_cap / 64][n_rows][64]
@@ -145,6 +146,8 @@ bool layout(int64_t n, int32_t n_units, int32_t n_rows, const tpc_params_t *p, c
   L.sd_r1 = (int32_t *)take(4 * K);
   L.sd_hm = (int32_t *)take(4 * K);
   L.sd_hb = (int32_t *)take(4 * K);
+  L.sd_first = (uint32_t *)L.sd_hm;
+  L.sd_first4 = (uint32_t *)L.sd_hb;
   L.sd_nfit = (int32_t *)take(4 * K);
   L.sd_rlo = (int32_t *)take(4 * K);
   L.sd_rhi = (int32_t *)take(4 * K);
@@ -2186,22 +2189,23 @@ __global__ void __launch_bounds__(64) k_fit_group(Args A) {
 // hits and at least f_min of them; tracks keep the tracklet order; no refit.
 //
 // Both passes are over the seed list (tracklets that are not seeds own nothing
-// and are never kept; k_chains set their owned = keep = 0).  Seeds are in
-// tracklet order, so an exclusive scan over seed order numbers the tracks in
+// and are never kept).  Seeds are in tracklet order, so an exclusive scan over seed order numbers the tracks in
 // tracklet order.  A block takes 64 seeds, a column of the hit table each, and
 // its waves a share of the rows each (a batch of few seeds has few
 // blocks, and the rows are then what there is to share out).
-//   k_select  counts and marks each tracklet's owned hits, and adds the tracks
-//             and hits of 256 seeds to their word of sel_sum;
-//   k_emit    adds up the words before its seeds, stages its hits in LDS and
-//             writes the tracks and their hits in whole lines.
+//   k_select  counts and marks each tracklet's owned hits, stores how many of
+//             them lie before each wave's rows, and adds the tracks and hits of
+//             256 seeds to their word of sel_sum;
+//   k_emit    adds up the words before its seeds, stages its hits in LDS at the
+//             stored places and writes the tracks and their hits in whole lines.
 // What bounds them: gathers and scatters by hit (owner, id, the hit's track).
 // Neighbouring seeds share the cache lines of these, so each XCD takes one
 // contiguous range of seeds.  One kernel that numbered its blocks by ticket,
 // 256 seeds at a time, and so dealt neighbours to all XCDs, took 225 us for 512
-// chunks (these two 46 and 110), 43 for one (7 and 10) and 1340 for 50
-// collisions (475 and 890: there the tracks of the hits, whose ids are in no
-// order, leave the L2 in parts of lines).
+// chunks (these two 47 and 78), 43 for one (7 and 8) and 1340 for 50
+// collisions (480 and 660: there the tracks of the hits, whose ids are in no
+// order, leave the L2 in parts of lines).  A k_emit that walked the hit table
+// for the waves' places itself took 106, 10 and 887 us.
 
 // a word of sel_sum: kept tracks (bits 31-62), their hits (bits 0-30)
 __device__ __forceinline__ uint64_t sel_word(int tracks, int hits) {
@@ -2209,16 +2213,19 @@ __device__ __forceinline__ uint64_t sel_word(int tracks, int hits) {
 }
 constexpr int SELECT_BLOCKS = 2048;
 constexpr int SEL_RB = 20;    // rows of a round trip
+// Waves to 64 seeds: they share out the rows, which is what shortens a small
+// batch's walk.  Whole calls with eight and with four: one chunk 554 and 559 us,
+// a pp sector 584 and 587, 512 chunks 2932 and 2933, 50 collisions 8002 and 7990.
+constexpr int SEL_WAVES = 8;
 
-template <int WAVES>
-__global__ void __launch_bounds__(WAVES * 64) k_select(Args A) {
-  __shared__ int cnt[WAVES][64];
+__global__ void __launch_bounds__(SEL_WAVES * 64) k_select(Args A) {
+  __shared__ int cnt[SEL_WAVES][64];
   const Workspace &w = A.w;
   if (*A.out.status != TPC_OK) return;
   if (blockIdx.x == 0 && threadIdx.x == 0) w.ctr[C_SELECT] = 1;  // k_emit writes the status while others start
   const int64_t n_seeds = w.ctr[C_SEEDS], n_tiles = (n_seeds + 63) / 64;
   const int nr = A.n_rows, wave = threadIdx.x >> 6, lane = __lane_id();
-  const int part = (nr + WAVES - 1) / WAVES;
+  const int part = (nr + SEL_WAVES - 1) / SEL_WAVES;
   const int ra = wave * part, rz = min(nr, ra + part);  // the wave's rows
   for (int64_t b = blockIdx.x; b < ((n_tiles + 7) & ~int64_t(7)); b += gridDim.x) {
     const int64_t tile = xcd_chunk(b, n_tiles);
@@ -2251,12 +2258,18 @@ __global__ void __launch_bounds__(WAVES * 64) k_select(Args A) {
     __syncthreads();
     if (wave == 0) {
       owned = 0;
+      uint32_t first[2] = {0u, 0u};  // hits before each wave's rows, a byte each (255 rows at most)
 #pragma unroll
-      for (int v = 0; v < WAVES; ++v) owned += cnt[v][lane];
+      for (int v = 0; v < SEL_WAVES; ++v) {
+        first[v / 4] |= uint32_t(owned) << v % 4 * 8;
+        owned += cnt[v][lane];
+      }
       const int keep = has && owned >= A.p.n_min && int64_t(owned) * 256 >= int64_t(A.p.f_min_q8) * nfit;
       if (valid) {
         w.sd_owned[i] = owned;
         w.sd_keep[i] = keep;
+        w.sd_first[i] = first[0];
+        w.sd_first4[i] = first[1];
       }
       int hits = keep ? owned : 0;
 #pragma unroll
@@ -2270,24 +2283,27 @@ __global__ void __launch_bounds__(WAVES * 64) k_select(Args A) {
   }
 }
 
-template <int WAVES>
-__global__ void __launch_bounds__(WAVES * 64) k_emit(Args A) {
+__global__ void __launch_bounds__(SEL_WAVES * 64) k_emit(Args A) {
   extern __shared__ int32_t ids[];  // the tile's hits, in output order: 64 * n_rows
-  __shared__ int cnt[WAVES][64], dest[64];
-  __shared__ unsigned long long sums[WAVES];
+  __shared__ int dest[64];
+  __shared__ unsigned long long sums[SEL_WAVES];
   const Workspace &w = A.w;
   if (!w.ctr[C_SELECT]) return;
   const int64_t n_seeds = w.ctr[C_SEEDS], n_tiles = (n_seeds + 63) / 64;
   const int nr = A.n_rows, wave = threadIdx.x >> 6, lane = __lane_id();
-  const int part = (nr + WAVES - 1) / WAVES;
+  const int part = (nr + SEL_WAVES - 1) / SEL_WAVES;
   const int ra = wave * part, rz = min(nr, ra + part);
   const tpc_tracks_t &O = A.out;
+  // A block's tiles follow one another, so each of its threads goes through its
+  // share of the words once.
+  uint64_t before = 0;
+  int64_t word = threadIdx.x;
   for (int64_t b = blockIdx.x; b < ((n_tiles + 7) & ~int64_t(7)); b += gridDim.x) {
     const int64_t tile = xcd_chunk(b, n_tiles);
     if (tile >= n_tiles) continue;  // block-uniform
     // the tracks and hits before the tile: whole words, then the tiles of its own
-    uint64_t sum = 0;
-    for (int64_t j = threadIdx.x; j < (tile >> 2); j += WAVES * 64) sum += w.sel_sum[j];
+    for (; word < (tile >> 2); word += SEL_WAVES * 64) before += w.sel_sum[word];
+    uint64_t sum = before;
     if (int(threadIdx.x) < int(tile & 3) * 64) {
       const int64_t s = (tile >> 2) * 256 + threadIdx.x;
       if (w.sd_keep[s]) sum += sel_word(1, w.sd_owned[s]);
@@ -2300,26 +2316,14 @@ __global__ void __launch_bounds__(WAVES * 64) k_emit(Args A) {
     const int32_t *col = seed_column(w, i, nr);
     const int rb = wave_max(rhi);
     const int row_a = wave_min(keep ? rlo : nr);
-    int mine = 0;
-    for (int r0 = row_a; r0 <= rb; r0 += SEL_RB) {
-      int h[SEL_RB];
-#pragma unroll
-      for (int k = 0; k < SEL_RB; ++k) h[k] = (r0 + k >= rlo && r0 + k <= rhi) ? col[(r0 + k) * 64] : -1;
-#pragma unroll
-      for (int k = 0; k < SEL_RB; ++k) mine += h[k] >= 0 && (h[k] & OWNED);
-    }
+    int at = keep ? (wave < 4 ? w.sd_first : w.sd_first4)[i] >> (wave & 3) * 8 & 0xFF : 0;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor((unsigned long long)sum, o, 64);
     if (lane == 0) sums[wave] = sum;
-    cnt[wave][lane] = mine;
     __syncthreads();
     sum = 0;
-    int at = 0;
 #pragma unroll
-    for (int v = 0; v < WAVES; ++v) {
-      sum += sums[v];
-      at += v < wave ? cnt[v][lane] : 0;
-    }
+    for (int v = 0; v < SEL_WAVES; ++v) sum += sums[v];
     const int64_t t0 = int64_t(sum >> 31), h0 = int64_t(sum & 0x7FFFFFFF);
     const uint64_t kept = __ballot(keep);
     int eo = owned;
@@ -2369,12 +2373,12 @@ __global__ void __launch_bounds__(WAVES * 64) k_emit(Args A) {
         }
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < n_out; j += WAVES * 64) __builtin_nontemporal_store(ids[j], &O.hits[h0 + j]);
-    for (int j = threadIdx.x; j < 64 * 5; j += WAVES * 64)
+    for (int j = threadIdx.x; j < n_out; j += SEL_WAVES * 64) __builtin_nontemporal_store(ids[j], &O.hits[h0 + j]);
+    for (int j = threadIdx.x; j < 64 * 5; j += SEL_WAVES * 64)
       if (dest[j / 5] >= 0) __builtin_nontemporal_store(__builtin_nontemporal_load(&w.sd_par[tile * 320 + j]), &O.params[int64_t(dest[j / 5]) * 5 + j % 5]);
-    for (int j = threadIdx.x; j < 64 * 15; j += WAVES * 64)
+    for (int j = threadIdx.x; j < 64 * 15; j += SEL_WAVES * 64)
       if (dest[j / 15] >= 0) __builtin_nontemporal_store(__builtin_nontemporal_load(&w.sd_cov[tile * 960 + j]), &O.cov[int64_t(dest[j / 15]) * 15 + j % 15]);
-    __syncthreads();  // ids, cnt, dest and sums are the next tile's
+    __syncthreads();  // ids, dest and sums are the next tile's
   }
 }
 
@@ -2441,20 +2445,6 @@ void launch_fit(const Args &A, hipStream_t st) {
   else if (A.n <= 1800 * 1024) launch_fit_group<4, 16>(A, st);
   else if (A.n <= 3000 * 1024) launch_fit_group<2, 32>(A, st);
   else hipLaunchKernelGGL(k_fit, dim3(round8(blocks_for(A.w.S_cap, CTB))), dim3(CTB), 0, st, A);
-}
-
-// Waves to 64 seeds.  Eight shorten a small batch's walk over the rows; where
-// there are blocks enough, four leave the caches to fewer of them.
-// Whole calls with eight and with four, by clusters: 18 k 638 and 642 us, 0.5 M
-// 840 and 841, 3 M 1467 and 1480, 7 M 3016 and 3021, 12 M 4259 and 4262, 20 M
-// 6990 and 6942, 25 M 8655 and 8567.
-constexpr int64_t SELECT_WIDE = 8 << 20;
-template <int WAVES, class Mark>
-void launch_select(const Args &A, hipStream_t st, Mark mark) {
-  const unsigned blocks = round8(A.w.KW < SELECT_BLOCKS ? A.w.KW : SELECT_BLOCKS);
-  hipLaunchKernelGGL(k_select<WAVES>, dim3(blocks), dim3(WAVES * 64), 0, st, A);
-  mark();
-  hipLaunchKernelGGL(k_emit<WAVES>, dim3(blocks), dim3(WAVES * 64), unsigned(64 * 4 * A.n_rows), st, A);
 }
 
 int track_impl(const tpc_clusters_t *c, const tpc_geometry_t *g, const tpc_field_t *f,
@@ -2535,8 +2525,10 @@ int track_impl(const tpc_clusters_t *c, const tpc_geometry_t *g, const tpc_field
     mark();
     launch_fit(A, st);
     mark();
-    if (c->n <= SELECT_WIDE) launch_select<8>(A, st, mark);
-    else launch_select<4>(A, st, mark);
+    const unsigned select_blocks = round8(w.KW < SELECT_BLOCKS ? w.KW : SELECT_BLOCKS);
+    hipLaunchKernelGGL(k_select, dim3(select_blocks), dim3(SEL_WAVES * 64), 0, st, A);
+    mark();
+    hipLaunchKernelGGL(k_emit, dim3(select_blocks), dim3(SEL_WAVES * 64), unsigned(64 * 4 * A.n_rows), st, A);
   }
   while (ki <= kNumKernels) mark();  // empty batch: the remaining events mark the same point
   if (hipGetLastError() != hipSuccess) return TPC_E_HIP;
