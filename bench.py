@@ -134,11 +134,24 @@ def measured_counters(kernel, workload):
     return e
 
 
-def _short(name):
+def _instance(name):
+    """A kernel's name with its template arguments: "void k_fit_group<16, 1>(Args)" is k_fit_group<16, 1>."""
     n = name.replace("(anonymous namespace)::", "")
     if "neg_kernel" in n:
         return "copy_calib"
-    return n.split("(")[0].split("<")[0].split()[-1]  # "void k_fit_group<16, 1>": k_fit_group
+    n = n.split("(")[0]
+    head, angle, args = n.partition("<")
+    return head.split()[-1] + angle + args
+
+
+def _short(name):
+    return _instance(name).split("<")[0]
+
+
+def _dominant(rows):
+    """By short name, the statistics of the instance of the kernel that took the most time, and which that is."""
+    rows = sorted(rows, key=lambda r: float(r["totaldurationns"]))
+    return {_short(r["name"]): r for r in rows}, {_short(r["name"]): _instance(r["name"]) for r in rows}
 
 
 def _csv(pattern_dir, suffix):
@@ -151,18 +164,21 @@ def _csv(pattern_dir, suffix):
         return [{k.lower(): v for k, v in r.items()} for r in csv.DictReader(f)]
 
 
-def _counter_means(d, counter):
-    """Mean per dispatch of one counter (summed over its dimensions), by kernel name."""
+def _counter_means(d, counter, instances):
+    """Mean per dispatch of one counter (summed over its dimensions), by short kernel name, over the dispatches of the
+    instance of the kernel that `instances` names."""
     per, names = {}, {}
     for r in _csv(d, "counter_collection.csv"):
         if r["counter_name"] != counter:
             continue
         key = r["dispatch_id"]
         per[key] = per.get(key, 0.0) + float(r["counter_value"])
-        names[key] = _short(r["kernel_name"])
+        names[key] = r["kernel_name"]
     acc = {}
     for key, v in per.items():
-        acc.setdefault(names[key], []).append(v)
+        k = _short(names[key])
+        if instances.get(k) == _instance(names[key]):
+            acc.setdefault(k, []).append(v)
     return {k: sum(v) / len(v) for k, v in acc.items()}
 
 
@@ -178,10 +194,9 @@ def summarize_profiles(prof_dir, workload):
     out_dir = os.path.join(ROOT, "profiles")
     os.makedirs(out_dir, exist_ok=True)
     rows = _csv(os.path.join(prof_dir, "trace"), "kernel_stats.csv")
-    # of a template's instances the one that took most time
-    stats = {_short(r["name"]): r for r in sorted(rows, key=lambda r: float(r["totaldurationns"]))}
-    fetch = _counter_means(os.path.join(prof_dir, "fetch"), "FETCH_SIZE")
-    write = _counter_means(os.path.join(prof_dir, "write"), "WRITE_SIZE")
+    stats, instances = _dominant(rows)
+    fetch = _counter_means(os.path.join(prof_dir, "fetch"), "FETCH_SIZE", instances)
+    write = _counter_means(os.path.join(prof_dir, "write"), "WRITE_SIZE", instances)
     gib_kib = float(1 << 20)
     f_fac = fetch["copy_calib"] / gib_kib
     w_fac = write["copy_calib"] / gib_kib
@@ -189,7 +204,7 @@ def summarize_profiles(prof_dir, workload):
     sq = {}
     if os.path.isdir(sq_dir):
         for cn in SQ_COUNTERS:
-            for k, v in _counter_means(sq_dir, cn).items():
+            for k, v in _counter_means(sq_dir, cn, instances).items():
                 sq.setdefault(k, {})[cn] = v
     run = json.loads(open(os.path.join(prof_dir, "trace", "bench.json")).read().strip().splitlines()[-1])
     n = run["config"]["clusters"]
