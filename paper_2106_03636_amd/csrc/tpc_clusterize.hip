@@ -4,41 +4,42 @@
 // The operation is stated with tpc_clusterize in include/tpc_track.h.
 //
 // Two launches on the caller's stream:
-//   k_clu_init   status, count, the rows' first pads, the look-back words;
+//   k_clu_init   status, count, the rows' first pads, and for each block the
+//                row it works on, in its look-back word;
 //   k_clu_find   a block per part of a row (taken by ticket): the digits of its
 //                pads and of the pads either side go to LDS once; each wave
 //                filters a contiguous share of them (only a digit of q_min or
 //                more that its neighbours in time do not beat can be a peak:
 //                about 3 in 10), tests the survivors against the pads either
 //                side (a binary search over their time-ordered digits) and
-//                keeps the peaks' places in order; the blocks' counts are
-//                added up by a decoupled look-back, and the peaks are written
-//                at their places, so clusters come in (unit, row, pad, time)
-//                order.  Digits are read once (those of edge pads twice).
-// A look-back waits for the slowest block before it, so the blocks have to
-// cost alike: the inner rows have a third of the outer rows' pads and nearly
-// as many clusters, and every row is cut into the same number of parts (runs
-// of a fixed number of pads: 912 us where equal parts take 651).  The number
-// follows from the batch's mean, so a part of a dense unit or row, or of a hot
-// region, may hold more than a block stages: such a part is taken a run of pads
-// at a time, all counted before the first is written.  36 units, one with 15 M
-// digits: 0.92 ms (all its parts swept in memory 3.4, the two passes below 1.37);
-// one of 5 M 0.35 - 0.51 (1.08 - 1.31, 1.20).  What it does not mend is the
-// wait: with 2 rows of 152 a hundred times denser than the others in every
-// unit, 1.88 ms (6.2, 1.34), since few dense parts are among the blocks that
-// run at one time.  (Cutting the rows at equal weights of digits and pads takes
-// 0.45, 0.33 and 0.49 ms for these, but 0.64 - 0.70 instead of 0.57 for an even
-// batch and 25 us instead of 22 for one unit: its blocks cost more to find.)
+//                keeps the peaks, the first in registers, the rest by their
+//                places; the blocks' counts are added up by a decoupled
+//                look-back, and the peaks are written at their places, so
+//                clusters come in (unit, row, pad, time) order.  Digits are read
+//                once (those of edge pads twice).
+// A look-back waits for the slowest block before it, so the blocks have to cost
+// alike, whatever rows, units or regions are dense: a row has as many parts as
+// multiples of digits_per_part lie among its digits' numbers, and one more
+// (first_block: known for every row by itself, without a scan), and its pads are
+// cut at like many digits.  A part still holds more than a block stages where
+// single pads are very dense, or a sparse row is long: it is taken a run of
+// pads at a time, all counted before the first is written.  36 units of 1.75 M
+// digits each, evenly: 811 us; the same digits ten times denser in a tenth of
+// the pads: 857; 20 M digits with two rows of 152 a hundred times denser: 683;
+// one unit of 5 M among 35 of 50 k: 232; one unit of 0.48 M evenly, and with
+// two such rows: 31 and 67.  (With the same number of parts in every row, by
+// pads: 863, 2030, 6768, 379, 32 and 814; with a wave per pad and two passes:
+// 2272, 2645, 2322, 1443, 60 and 239.)
 // Peaks and charge sums are integer; the centre and position are FP64
 // expressions rounded once to FP32, so the result is exact.
 //
-// What bounds it: instruction issue (about 190 vector instructions per 64
-// digits, half of them the searches'), then the look-back and the tickets (140
-// and 45 us of the 605 that 27 k parts took).  63 M digits of 540 k pads: 566 us
-// with 22 k parts, 0.7 TB/s of the bytes it cannot do without; 0.48 M digits of
-// 15 k pads: 22 us.  Before, two
-// passes (count, emit) searched for every digit, a wave per pad: 2.39 ms and
-// 57 us.
+// What bounds it: instruction issue (half of it the searches'), then the
+// look-back and the tickets.  The verdicts of k_clu_init lie in another cache
+// line than the ticket, which all blocks add to (in its line: 1.58 ms for
+// 0.87).  Peaks kept in registers are not searched for a second time when they
+// are written: 63 M digits 849 to 811 us.  A slice of 15 collisions, 63 M digits
+// of 540 k pads: 532 us, 0.75 TB/s of the bytes it cannot do without; 0.48 M
+// digits of 15 k pads: 22 us.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -50,7 +51,8 @@ namespace {
 constexpr int TPB = 256;
 constexpr int WAVES = TPB / 64;
 constexpr int MAX_ROWS = 255;
-constexpr int MAX_PADS = 60;         // pads of a block (with one either side and an end: a wave's lanes)
+constexpr int MAX_PADS = 124;        // pads of a block (with one either side and an end: two to a wave's lane)
+constexpr int RUN_PADS = 60;         // pads of a run of a part that does not fit (one to a lane)
 // digits a block holds in LDS, with the pads either side (60 M digits: 817, 651 and 605 us with 3072, 4096 and 6144, 682
 // with 8192 and 512 threads; fewer blocks take fewer tickets, which one counter serves, but leave fewer waves)
 constexpr int STAGE_DIGITS = 6144;
@@ -71,12 +73,14 @@ struct CluArgs {
   int32_t *qtot;
   int64_t *unit_offsets, *count;
   int32_t *status;
-  int32_t parts;       // parts of a row, a block each
+  uint32_t share;      // digits of a part (see first_block)
+  int32_t init_blocks;
   int64_t n_blocks;
   bool wide;  // time and q allow loads of four digits (8-byte aligned)
   // workspace
   unsigned long long *ticket;
-  uint64_t *lookback;  // [n_blocks] flag (bits 62-63: 1 count, 2 inclusive sum), clusters
+  int32_t *verdict;    // [init_blocks] whether k_clu_init's block met offsets out of order
+  uint64_t *lookback;  // [n_blocks] flag (bits 62-63: 1 count, 2 inclusive sum), clusters; before (flag 0) unit << 8 | row
   int32_t *rbase;      // [n_rows] first pad of each row
 };
 
@@ -174,21 +178,37 @@ __device__ __forceinline__ void other_pads(Peak &k, const L &lo, const L &hi) {
   }
 }
 
+// First pad of row r of unit u (the rows' own first pads in rbase), and of the row after it.
+__device__ __forceinline__ int64_t row_start(const CluArgs &A, const int32_t *rbase, int u, int r) {
+  return min(max(int64_t(u) * A.pads_total + rbase[r], int64_t(0)), A.n_pads);
+}
+__device__ __forceinline__ int64_t next_start(const CluArgs &A, const int32_t *rbase, int u, int r) {
+  return r + 1 < A.n_rows ? row_start(A, rbase, u, r + 1) : row_start(A, rbase, u + 1, 0);
+}
+// First block of row j where the rows have parts by their digits, off the first
+// of these: at least a block each, and one more for each multiple of `share`
+// among its digits' numbers.  Known for every row by itself, and so is the sum.
+__device__ __forceinline__ int64_t first_block(const CluArgs &A, int64_t j, int64_t off) {
+  return int64_t(uint32_t(off) / A.share) + j;
+}
+
 __global__ void __launch_bounds__(TPB) k_clu_init(CluArgs A) {
-  const int64_t i0 = int64_t(blockIdx.x) * TPB + threadIdx.x;
-  if (blockIdx.x == 0) {  // exclusive sum of the rows' pads
-    __shared__ int32_t wsum[WAVES];
-    const int lane = __lane_id(), wave = threadIdx.x >> 6;
-    const int32_t v = int32_t(threadIdx.x) < A.n_rows ? 2 * A.half[threadIdx.x] : 0;
-    int32_t x = v;
+  __shared__ int32_t wsum[WAVES], rbase[TPB];
+  const int64_t i0 = int64_t(blockIdx.x) * TPB + threadIdx.x, stride = int64_t(gridDim.x) * TPB;
+  const int lane = __lane_id(), wave = threadIdx.x >> 6;
+  // exclusive sum of the rows' pads
+  const int32_t v = int32_t(threadIdx.x) < A.n_rows ? 2 * A.half[threadIdx.x] : 0;
+  int32_t x = v;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int32_t y = __shfl_up(x, o);
-      if (lane >= o) x += y;
-    }
-    if (lane == 63) wsum[wave] = x;
-    __syncthreads();
-    for (int w = 0; w < wave; ++w) x += wsum[w];
+  for (int o = 1; o < 64; o <<= 1) {
+    const int32_t y = __shfl_up(x, o);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) wsum[wave] = x;
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) x += wsum[w];
+  rbase[threadIdx.x] = x - v;
+  if (blockIdx.x == 0) {
     if (int32_t(threadIdx.x) < A.n_rows) A.rbase[threadIdx.x] = x - v;
     if (threadIdx.x == 0) {
       *A.status = TPC_OK;
@@ -196,7 +216,35 @@ __global__ void __launch_bounds__(TPB) k_clu_init(CluArgs A) {
       *A.ticket = 0ull;
     }
   }
-  for (int64_t i = i0; i < A.n_blocks; i += int64_t(gridDim.x) * TPB) A.lookback[i] = 0;
+  __syncthreads();
+  // every row writes its number to its blocks' words
+  const int64_t rows = int64_t(A.n_units) * A.n_rows;
+  bool bad = false;
+  for (int64_t jb = i0 - lane; jb < rows; jb += stride) {  // wave-uniform
+    const int64_t j = jb + lane;
+    int64_t lo = 0, hi = 0;
+    uint64_t word = 0;
+    if (j < rows) {
+      const int u = int(uint32_t(j) / uint32_t(A.n_rows)), r = int(uint32_t(j) - uint32_t(u) * uint32_t(A.n_rows));
+      const int64_t a = A.off[row_start(A, rbase, u, r)], b = j + 1 < rows ? A.off[next_start(A, rbase, u, r)] : A.n;
+      word = uint64_t(u) << 8 | uint64_t(r);
+      if (a < 0 || b < a || b > A.n || (j == 0 && a != 0)) {
+        bad = true;
+      } else {
+        lo = first_block(A, j, a);
+        hi = first_block(A, j + 1, b);
+      }
+    }
+    for (int k = 0; k < 16 && lo < hi; ++k) A.lookback[lo++] = word;
+    for (uint64_t m = __ballot(lo < hi); m; m &= m - 1) {  // long rows by the wave
+      const int l = __ffsll((unsigned long long)m) - 1;
+      const int64_t end = __shfl((long long)hi, l);
+      const uint64_t x = __shfl((unsigned long long)word, l);
+      for (int64_t k = __shfl((long long)lo, l) + lane; k < end; k += 64) A.lookback[k] = x;
+    }
+  }
+  const int any = __syncthreads_or(bad);
+  if (threadIdx.x == 0) A.verdict[blockIdx.x] = any;
 }
 
 // A block's run of pads: slot s holds pad first - 1 + s of the row, slots
@@ -225,45 +273,104 @@ __device__ __forceinline__ int slot_of(const Run &R, int32_t e) {
 // not even one does, the pads up to the next that does, with fits = false.
 // Run by one wave.
 template <bool SOME>
-__device__ __forceinline__ void load_run(const CluArgs &A, Run &R, int u, int r, int32_t first, int32_t np) {
+__device__ __forceinline__ void load_run(const CluArgs &A, Run &R, const int32_t *rbase, const int32_t *half, int u, int r,
+                                         int32_t first, int32_t np) {
+  constexpr int E = SOME ? 1 : 2;  // offsets of a lane
   const int t = __lane_id();
-  const int64_t j0 = int64_t(u) * A.pads_total + A.rbase[r] + first;
-  // the offset at the start of pad j0 - 1 + t (pads outside the arrays are empty)
-  const int64_t j = min(max(j0 - 1 + t, int64_t(0)), A.n_pads);
-  const int64_t v = t < np + 3 ? A.off[j] : 0;
-  const int64_t next = __shfl_down(v, 1);
-  bool good = t >= np + 3 || (v >= 0 && v <= A.n && (t == np + 2 || v <= next));
+  const int64_t j0 = int64_t(u) * A.pads_total + rbase[r] + first;
+  // the offset at the start of pad j0 - 1 + t + 64 e (pads outside the arrays are empty)
+  int64_t v[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int i = t + 64 * e;
+    v[e] = i < np + 3 ? A.off[min(max(j0 - 1 + i, int64_t(0)), A.n_pads)] : 0;
+  }
+  bool good = true;
+  int32_t len = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int i = t + 64 * e;
+    int64_t next = __shfl_down(v[e], 1);
+    if (e + 1 < E) {
+      const int64_t over = __shfl(v[E - 1], 0);
+      if (t == 63) next = over;
+    }
+    good = good && (i >= np + 3 || (v[e] >= 0 && v[e] <= A.n && (i == np + 2 || v[e] <= next)));
+    if (i < np + 2) len = max(len, int32_t(next - v[e]));
+  }
   if (t == 0 && j0 == 0) good = good && A.off[0] == 0;
   if (t == 0 && j0 + np >= A.n_pads) good = good && A.off[A.n_pads] == A.n;
   const bool ok = __ballot(good) == ~uint64_t(0);
-  const int64_t at = __shfl(v, 0) & ~int64_t(3);  // loads of four start at a multiple of four
-  int32_t len = ok && t < np + 2 ? int32_t(next - v) : 0;
+  const int64_t at = __shfl(v[0], 0) & ~int64_t(3);  // loads of four start at a multiple of four
+  if (!ok) len = 0;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) len = max(len, __shfl_xor(len, o));
-  const int64_t last = __shfl(v, np + 2);
+  const int64_t last = __shfl(E > 1 && np + 2 >= 64 ? v[E - 1] : v[0], (np + 2) & 63);
   int k = np;
   bool fits = ok && last - at <= STAGE_DIGITS;
   if (SOME && ok && !fits && np > 0) {
     // slots 0 .. k + 1 end with the offset of lane k + 2
-    k = __popcll(__ballot(t < np + 3 && v - at <= STAGE_DIGITS)) - 3;
+    k = __popcll(__ballot(t < np + 3 && v[0] - at <= STAGE_DIGITS)) - 3;
     fits = k > 0;
     if (!fits) {  // pad first + t by itself, with its neighbours
-      const bool one = __shfl_down(v, 3) - (v & ~int64_t(3)) <= STAGE_DIGITS;
+      const bool one = __shfl_down(v[0], 3) - (v[0] & ~int64_t(3)) <= STAGE_DIGITS;
       k = min(np, __ffsll((unsigned long long)__ballot(one || t >= np)) - 1);
     }
   }
-  if (t < np + 3) R.a[t] = ok ? int32_t(v - at) : 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+    if (t + 64 * e < np + 3) R.a[t + 64 * e] = ok ? int32_t(v[e] - at) : 0;
   if (t == 0) {
     if (!ok) fail(A.status, TPC_E_INVALID);
     R.g0 = at;
     R.first = first;
     R.np = k;
     R.row = r;
-    R.half = A.half[r];
+    R.half = half[r];
     R.top = len > 0 ? 1 << (31 - __clz(len)) : 0;
     R.ok = ok;
     R.fits = fits;
   }
+}
+
+// What a block does: np pads of row r of unit u from `first` on; lead: the
+// row's first ones.
+struct Part {
+  int32_t u, r, first, np;
+  bool lead;
+};
+
+// The part of block vb: of a row cut into parts of like many digits, a pad to
+// the part that its first digit lies in.  Run by one wave.
+__device__ __forceinline__ Part cut_part(const CluArgs &A, const int32_t *rbase, const int32_t *half, int64_t vb) {
+  const int lane = __lane_id();
+  const uint64_t word = A.lookback[vb];
+  Part P;
+  P.u = int32_t(word >> 8);
+  P.r = int32_t(word & 0xFF);
+  const int64_t j = int64_t(P.u) * A.n_rows + P.r, rows = int64_t(A.n_units) * A.n_rows;
+  const int32_t pads = min(max(2 * half[P.r], 0), A.pads_total);
+  const int64_t s = row_start(A, rbase, P.u, P.r), e = min(s + pads, A.n_pads);
+  const int64_t a = A.off[s], b = j + 1 < rows ? A.off[next_start(A, rbase, P.u, P.r)] : A.n;
+  int64_t v[2];  // most rows' pads, on their way with a and b
+#pragma unroll
+  for (int h = 0; h < 2; ++h) v[h] = s + 64 * h + lane < e ? A.off[s + 64 * h + lane] : INT64_MAX;
+  const int64_t b0 = first_block(A, j, a), k = vb - b0;
+  const uint32_t c = uint32_t(first_block(A, j + 1, b) - b0);
+  const int64_t step = int64_t(uint32_t(b - a) / c) + 1, from = a + k * step, to = from + step;
+  int32_t na = 0, nb = 0;
+  for (int64_t i = s; i < e; i += 128) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (i > s) v[h] = i + 64 * h + lane < e ? A.off[i + 64 * h + lane] : INT64_MAX;
+      na += __popcll(__ballot(v[h] < from));
+      nb += __popcll(__ballot(v[h] < to));
+    }
+  }
+  P.first = k == 0 ? 0 : na;
+  P.np = (k + 1 == int64_t(c) ? pads : nb) - P.first;
+  P.lead = k == 0;
+  return P;
 }
 
 // Clusters of the blocks before this one: publishes the block's count, adds
@@ -375,19 +482,33 @@ __global__ void __launch_bounds__(TPB) k_clu_find(CluArgs A) {
   __shared__ uint16_t found[STAGE_DIGITS];         // per wave, from its first digit's place: candidates, then peaks
   __shared__ uint32_t starts[STAGE_DIGITS / 32 + 2];  // bit e: digit e is the first of its pad
   __shared__ Run R;
+  __shared__ Part part;
+  __shared__ int32_t rbase[MAX_ROWS], half[MAX_ROWS];  // the rows' first pads and half pads
   __shared__ int32_t cnt[MAX_PADS];                // per pad (sweep)
   __shared__ int32_t wcnt[WAVES];
   __shared__ int64_t s_vb, s_before;
   const int lane = __lane_id(), wave = threadIdx.x >> 6;
   if (threadIdx.x == 0) s_vb = int64_t(atomicAdd(A.ticket, 1ull));
   for (int i = threadIdx.x; i < STAGE_DIGITS / 32 + 2; i += TPB) starts[i] = 0;
+  if (int32_t(threadIdx.x) < A.n_rows) {
+    rbase[threadIdx.x] = A.rbase[threadIdx.x];
+    half[threadIdx.x] = A.half[threadIdx.x];
+  }
+  const bool bad = lane < A.init_blocks && A.verdict[lane] != 0;
   __syncthreads();
   const int64_t vb = s_vb;
-  const int part = int(vb % A.parts), r = int(vb / A.parts % A.n_rows), u = int(vb / A.parts / A.n_rows);
-  const int32_t pads = min(max(2 * A.half[r], 0), A.pads_total), step = (pads + A.parts - 1) / A.parts;
-  const int32_t first = min(part * step, pads), np = min(step, pads - first);
-  if (wave == 0) load_run<false>(A, R, u, r, first, min(np, MAX_PADS));
+  if (__ballot(bad)) {  // the words say nothing then: every block sees it
+    if (threadIdx.x == 0) fail(A.status, TPC_E_INVALID);
+    return;
+  }
+  if (wave == 0) {
+    const Part P = cut_part(A, rbase, half, vb);
+    load_run<false>(A, R, rbase, half, P.u, P.r, P.first, min(P.np, MAX_PADS));
+    if (lane == 0) part = P;
+  }
   __syncthreads();
+  const int u = part.u, r = part.r;
+  const int32_t first = part.first, np = part.np;
   const bool whole = np <= MAX_PADS && R.fits;
 
   auto slot_list = [&](int s) {
@@ -407,8 +528,13 @@ __global__ void __launch_bounds__(TPB) k_clu_find(CluArgs A) {
     return k;
   };
   uint16_t *list;
-  // The peaks of the run's digits in this wave's share, `mine` of them in
-  // list; wcnt: those of each wave.
+  constexpr int KEPT = 4;
+  struct Kept {
+    int32_t at, where, Q, Sp, St;  // place among the wave's peaks (-1: none), digit << 8 | slot
+  } kept[KEPT];
+  int32_t n_kept = 0;
+  // The peaks of the run's digits in this wave's share, `mine` of them, the
+  // first n_kept in kept and the rest in list; wcnt: those of each wave.
   auto find = [&](int32_t n) -> int32_t {
     int32_t mine = 0;
     const int32_t m = R.a[n + 2];
@@ -458,7 +584,27 @@ __global__ void __launch_bounds__(TPB) k_clu_find(CluArgs A) {
       n_cand += __popcll(k);
     }
     __builtin_amdgcn_wave_barrier();
-    for (int32_t i0 = 0; i0 < n_cand; i0 += 64) {  // the peaks among them, kept in the list's front
+    // the peaks among them: the first KEPT * 64 candidates' in registers, the rest in the list's front
+#pragma unroll
+    for (int x = 0; x < KEPT; ++x) {
+      kept[x].at = -1;
+      if (x * 64 >= n_cand) continue;
+      const int32_t i = x * 64 + lane;
+      int32_t e = 0;
+      int s = 0;
+      Peak k;
+      k.is = false;
+      if (i < n_cand) {
+        e = list[i];
+        k = peak(e, s);
+      }
+      const uint64_t m = __ballot(k.is);
+      if (k.is) kept[x] = Kept{mine + int32_t(__popcll(m & ((1ull << lane) - 1ull))), e << 8 | s, k.Q, k.Sp, k.St};
+      mine += __popcll(m);
+    }
+    n_kept = mine;
+    __builtin_amdgcn_wave_barrier();
+    for (int32_t i0 = KEPT * 64; i0 < n_cand; i0 += 64) {
       const int32_t i = i0 + lane;
       int32_t e = 0;
       bool is = false;
@@ -479,7 +625,14 @@ __global__ void __launch_bounds__(TPB) k_clu_find(CluArgs A) {
   // and their clusters, from place o of the output on
   auto write = [&](int32_t mine, int64_t o) {
     for (int w = 0; w < wave; ++w) o += wcnt[w];
-    for (int32_t i = lane; i < mine; i += 64) {
+#pragma unroll
+    for (int x = 0; x < KEPT; ++x)
+      if (kept[x].at >= 0) {
+        const uint32_t d = dig[kept[x].where >> 8];
+        const Peak k{true, int32_t(d >> 16), int32_t(d & 0xFFFFu), kept[x].Q, kept[x].Sp, kept[x].St};
+        write_cluster(A, R, kept[x].where & 0xFF, k, o + kept[x].at);
+      }
+    for (int32_t i = n_kept + lane; i < mine; i += 64) {
       int s;
       const Peak k = peak(list[i], s);
       write_cluster(A, R, s, k, o + i);
@@ -500,13 +653,13 @@ __global__ void __launch_bounds__(TPB) k_clu_find(CluArgs A) {
     __syncthreads();
     write(mine, s_before);
   } else {
-    // Too many digits (a part of a row that holds far more than the batch's
-    // mean): a run at a time, once to count and once to write.
+    // Too many digits (single pads denser than a part is meant to be) or pads: a
+    // run at a time, once to count and once to write.
     int32_t total = 0;
     const bool keep = np <= MAX_PADS;  // cnt holds all of the part's pads
     auto next_run = [&](int32_t p) {
       __syncthreads();
-      if (wave == 0) load_run<true>(A, R, u, r, first + p, min(np - p, MAX_PADS));
+      if (wave == 0) load_run<true>(A, R, rbase, half, u, r, first + p, min(np - p, RUN_PADS));
       for (int i = threadIdx.x; i < STAGE_DIGITS / 32 + 2; i += TPB) starts[i] = 0;
       __syncthreads();
     };
@@ -547,7 +700,7 @@ __global__ void __launch_bounds__(TPB) k_clu_find(CluArgs A) {
     if (threadIdx.x < WAVES) wcnt[threadIdx.x] = threadIdx.x == 0 ? total : 0;
     __syncthreads();
   }
-  if (r == 0 && part == 0 && threadIdx.x == 0) A.unit_offsets[u] = s_before;
+  if (r == 0 && part.lead && threadIdx.x == 0) A.unit_offsets[u] = s_before;
   if (vb == A.n_blocks - 1 && threadIdx.x == 0) {
     const int64_t all = s_before + sum();
     *A.count = all;
@@ -556,18 +709,25 @@ __global__ void __launch_bounds__(TPB) k_clu_find(CluArgs A) {
   }
 }
 
-// Parts of a row: a block's digits, with the edge pads and the densest rows
-// (a third above the mean), should fit its LDS; otherwise a part takes several
-// runs (the quotient below at 2.2, 1.9, 1.7 and 1.5: an even batch of 63 M digits
-// 607, 558, 562 and 487 us, one unit of 5 M 100, 103, 105 and 145).  Rows may be
-// longer than the mean: parts of at most MAX_PADS pads there too, where that is
-// possible.
-int32_t parts_per_row(int64_t n, int64_t n_pads, int32_t n_units, int32_t n_rows) {
-  const int64_t rows = int64_t(n_units) * n_rows, pads = n_pads / rows;  // pads: of a row, on average
-  const int64_t most = pads / 2 > 1 ? pads / 2 : 1;
-  const int64_t by_digits = n / rows / (STAGE_DIGITS * 10 / 19) + 1, by_pads = pads * 8 / 5 / MAX_PADS + 1;
-  const int64_t p = by_digits > by_pads ? by_digits : by_pads;
-  return int32_t(p < most ? p : most);
+constexpr int INIT_BLOCKS = 32;  // verdicts: the words after the ticket's line
+
+// Digits of a part.  Many blocks: 4096, which leaves room for a dense part's
+// edge pads.  Fewer than some rounds of the chip's 1024: smaller parts, so that
+// the last round is not nearly empty (one unit of 5 M digits 100 us with 3234,
+// 112 with 4096, 152 with a fifth more).  A few hundred: by the mean row, so that a row's
+// pads are three parts, or two to three where these would hold under 2048
+// digits and cost little but their fixed part (one unit of 0.48 M: 24.6 and
+// 25.0 us; of 1 M 46 and 42).  Never more blocks than the workspace has words.
+uint32_t digits_per_part(int64_t n, int64_t n_pads, int64_t rows) {
+  const int64_t few = STAGE_DIGITS * 10 / 19, many = 4096, blocks = n / few + rows, mean = n / rows;
+  int64_t share = blocks > 4096 ? many : few;
+  if (blocks <= 512) {
+    const int64_t splits = n_pads / rows / 40 > 1 ? n_pads / rows / 40 : 1, low = mean * 2 / 3 < 2048 ? mean * 2 / 3 : 2048;
+    share = (mean / splits > low ? mean / splits : low) + 1;
+  }
+  const int64_t room = n_pads / 2 - rows;
+  if (room < 1) return uint32_t(1) << 31;  // a part a row: n is below it
+  return uint32_t(share > n / room + 1 ? share : n / room + 1);
 }
 
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
@@ -628,13 +788,15 @@ extern "C" int tpc_clusterize(const tpc_digits_t *digits, const tpc_pad_geometry
   A.ticket = reinterpret_cast<unsigned long long *>(ws);
   A.rbase = reinterpret_cast<int32_t *>(ws + 256);
   A.lookback = reinterpret_cast<uint64_t *>(ws + 256 + align256(sizeof(int32_t) * MAX_ROWS));
-  A.parts = parts_per_row(A.n, A.n_pads, A.n_units, A.n_rows);
-  A.n_blocks = int64_t(A.n_units) * A.n_rows * A.parts;
+  A.verdict = reinterpret_cast<int32_t *>(ws + 128);  // not in the line of the ticket
+  const int64_t rows = int64_t(A.n_units) * A.n_rows, rb = (rows + TPB - 1) / TPB;
+  A.share = digits_per_part(A.n, A.n_pads, rows);
+  A.n_blocks = A.n / A.share + rows;
+  A.init_blocks = int32_t(rb > INIT_BLOCKS ? INIT_BLOCKS : rb);
   A.wide = ((reinterpret_cast<uintptr_t>(A.time) | reinterpret_cast<uintptr_t>(A.q)) & 7) == 0;
 
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int64_t ib = (A.n_blocks + TPB - 1) / TPB;
-  hipLaunchKernelGGL(k_clu_init, dim3(unsigned(ib > 1024 ? 1024 : ib)), dim3(TPB), 0, st, A);
+  hipLaunchKernelGGL(k_clu_init, dim3(unsigned(A.init_blocks)), dim3(TPB), 0, st, A);
   hipLaunchKernelGGL(k_clu_find, dim3(unsigned(A.n_blocks)), dim3(TPB), 0, st, A);
   return hipGetLastError() == hipSuccess ? TPC_OK : TPC_E_HIP;
 }
