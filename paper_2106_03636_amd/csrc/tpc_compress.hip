@@ -20,7 +20,7 @@
 // are therefore one 16-byte and one 4-byte load, and four clusters' states are
 // on their way together: 24 M clusters 363 us instead of 540 (one cluster a
 // thread with the wide load: 392; four with the narrow ones: 516 - 784), and
-// with each XCD on a contiguous range 343.
+// with each XCD on a contiguous range 310.
 // Each block adds its residuals to the same few hundred histogram bins, one
 // after the other: 512 blocks.  1024 cost more (374 against 363; with 1 M
 // clusters 50 us against 42), 256 leave too few loads in flight.
