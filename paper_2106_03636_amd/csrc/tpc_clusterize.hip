@@ -34,7 +34,7 @@
 // expressions rounded once to FP32, so the result is exact.
 //
 // What bounds it: instruction issue (half of it the searches'), then the
-// look-back and the tickets.  The verdicts of k_clu_init lie in another cache
+// look-back and the tickets.  What k_clu_init found lies in another cache
 // line than the ticket, which all blocks add to (in its line: 1.58 ms for
 // 0.87).  Peaks kept in registers are not searched for a second time when they
 // are written: 63 M digits 849 to 811 us.  A slice of 15 collisions, 63 M digits
@@ -79,7 +79,7 @@ struct CluArgs {
   bool wide;  // time and q allow loads of four digits (8-byte aligned)
   // workspace
   unsigned long long *ticket;
-  int32_t *verdict;    // [init_blocks] whether k_clu_init's block met offsets out of order
+  int32_t *misordered; // [init_blocks] whether the block of k_clu_init met offsets out of order
   uint64_t *lookback;  // [n_blocks] flag (bits 62-63: 1 count, 2 inclusive sum), clusters; before (flag 0) unit << 8 | row
   int32_t *rbase;      // [n_rows] first pad of each row
 };
@@ -244,7 +244,7 @@ __global__ void __launch_bounds__(TPB) k_clu_init(CluArgs A) {
     }
   }
   const int any = __syncthreads_or(bad);
-  if (threadIdx.x == 0) A.verdict[blockIdx.x] = any;
+  if (threadIdx.x == 0) A.misordered[blockIdx.x] = any;
 }
 
 // A block's run of pads: slot s holds pad first - 1 + s of the row, slots
@@ -494,7 +494,7 @@ __global__ void __launch_bounds__(TPB) k_clu_find(CluArgs A) {
     rbase[threadIdx.x] = A.rbase[threadIdx.x];
     half[threadIdx.x] = A.half[threadIdx.x];
   }
-  const bool bad = lane < A.init_blocks && A.verdict[lane] != 0;
+  const bool bad = lane < A.init_blocks && A.misordered[lane] != 0;
   __syncthreads();
   const int64_t vb = s_vb;
   if (__ballot(bad)) {  // the words say nothing then: every block sees it
@@ -709,15 +709,17 @@ __global__ void __launch_bounds__(TPB) k_clu_find(CluArgs A) {
   }
 }
 
-constexpr int INIT_BLOCKS = 32;  // verdicts: the words after the ticket's line
+constexpr int INIT_BLOCKS = 32;  // their findings take the words after the line of the ticket
 
 // Digits of a part.  Many blocks: 4096, which leaves room for a dense part's
-// edge pads.  Fewer than some rounds of the chip's 1024: smaller parts, so that
-// the last round is not nearly empty (one unit of 5 M digits 100 us with 3234,
-// 112 with 4096, 152 with a fifth more).  A few hundred: by the mean row, so that a row's
-// pads are three parts, or two to three where these would hold under 2048
-// digits and cost little but their fixed part (one unit of 0.48 M: 24.6 and
-// 25.0 us; of 1 M 46 and 42).  Never more blocks than the workspace has words.
+// edge pads (63 M digits evenly: 889, 877, 877 and 865 us with 3600, 4096, 4608
+// and 5120; 20 M mostly of one unit 464, 465, 514 and 540).  Up to four times the 1024
+// blocks that run at a time: 3234, or the last ones are too few to fill the
+// chip (one unit of 5 M: 103 us, with 4096 112, with 5632 127).  A few hundred
+// blocks: by the mean row, whose pads are three parts (one unit of 1 M: 42 us, in two
+// to three 46), or two to three where three would hold under 2048 digits and
+// cost little but their fixed part (one unit of 0.48 M: 25.0 and 24.6 us).
+// Never more blocks than the workspace has words.
 uint32_t digits_per_part(int64_t n, int64_t n_pads, int64_t rows) {
   const int64_t few = STAGE_DIGITS * 10 / 19, many = 4096, blocks = n / few + rows, mean = n / rows;
   int64_t share = blocks > 4096 ? many : few;
@@ -788,7 +790,7 @@ extern "C" int tpc_clusterize(const tpc_digits_t *digits, const tpc_pad_geometry
   A.ticket = reinterpret_cast<unsigned long long *>(ws);
   A.rbase = reinterpret_cast<int32_t *>(ws + 256);
   A.lookback = reinterpret_cast<uint64_t *>(ws + 256 + align256(sizeof(int32_t) * MAX_ROWS));
-  A.verdict = reinterpret_cast<int32_t *>(ws + 128);  // not in the line of the ticket
+  A.misordered = reinterpret_cast<int32_t *>(ws + 128);  // not in the line of the ticket
   const int64_t rows = int64_t(A.n_units) * A.n_rows, rb = (rows + TPB - 1) / TPB;
   A.share = digits_per_part(A.n, A.n_pads, rows);
   A.n_blocks = A.n / A.share + rows;
